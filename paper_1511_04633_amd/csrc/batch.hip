@@ -71,7 +71,7 @@ View view_of(lbmx_batch *b, int k)
     char *base = b->ws + b->off[k];
     const size_t lat = b->L[k].lattice;
     return make_view(base + (size_t)b->cur[k] * lat, base + (size_t)(1 - b->cur[k]) * lat, lat, p,
-                     b->d[k], true, b->stream);
+                     b->d[k], b->stream);
 }
 
 double *scratch_of(lbmx_batch *b, int k) { return reinterpret_cast<double *>(b->ws + b->scr[k]); }
@@ -94,7 +94,7 @@ lbmx_status upload_cavs(lbmx_batch *b)
         BatchCav<T> &c = h[k];
         c.lat[0] = b->ws + b->off[k];
         c.lat[1] = b->ws + b->off[k] + b->L[k].lattice;
-        c.geo = geometry<St>(make_view(c.lat[0], c.lat[1], b->L[k].lattice, b->p[k], b->d[k], true,
+        c.geo = geometry<St>(make_view(c.lat[0], c.lat[1], b->L[k].lattice, b->p[k], b->d[k],
                                        b->stream));
         c.rates = make_rates<T>(&b->p[k], b->d[k]);
         c.cells = uint32_t(b->p[k].n) * b->p[k].n * b->p[k].n;

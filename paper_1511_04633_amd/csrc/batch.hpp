@@ -7,7 +7,7 @@
 // block takes tiles blockIdx.x, blockIdx.x + gridDim.x, ... (grid-stride
 // "persistent" blocks when gridDim.x is smaller than the tile count, one
 // tile per block when equal).  Consecutive nodes of a tile are consecutive
-// in every population segment (up to a slab boundary), so loads and stores
+// in every population segment (up to a plane boundary), so loads and stores
 // stay coalesced across row boundaries, and every wavefront is full except
 // at the end of a cavity.  The per-cavity table (lattice pointers, geometry,
 // relaxation rates) is read with wavefront-uniform loads.
@@ -30,19 +30,6 @@ struct Tile {
     uint32_t cav;        // index into the cavity table
     uint32_t start;      // first node (flat index x + n (y + n z))
 };
-
-// floor(c / n) for c < 2^24: the float quotient is within 1/2 of the true
-// one, so a single correction by one is exact.
-__device__ __forceinline__ uint32_t div_small(uint32_t c, uint32_t n, float inv_n)
-{
-    uint32_t q = uint32_t(float(c) * inv_n);
-    const int32_t r = int32_t(c) - int32_t(q * n);
-    if (r < 0)
-        q -= 1;
-    else if (r >= int32_t(n))
-        q += 1;
-    return q;
-}
 
 // Each cavity's time step lives on the device, in two arrays used by turns:
 // a launch of parity p reads cavity k's step from t_in[k] (the stochastic-
@@ -72,10 +59,14 @@ __global__ __launch_bounds__(1024) void k_step_batch(const BatchCav<typename St:
         const uint32_t z = div_small(q, n, cv->inv_n);
         const int x = int(c - q * n), y = int(q - z * n);
         const Geometry<T> geo = cv->geo;
+        Site s = site_in_plane<St>(int(n), x, y, int(z));
+        const uint32_t plane = z * Plane<St>(n).bytes;
+        s.vF += plane;
+        s.vG += plane;
         T f[19], g[7];
-        pull<St, true>(cv->lat[parity], geo, x, y, int(z), f, g);
+        pull<St, true>(cv->lat[parity], geo, s, y, f, g);
         collide<T, kForce>(f, g, cv->rates);
-        put<St, true>(cv->lat[parity ^ 1], c, step, f, g, geo.inv_escale);
+        put<St>(cv->lat[parity ^ 1], s, c, step, geo, f, g);
     }
 }
 

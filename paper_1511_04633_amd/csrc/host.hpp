@@ -211,8 +211,9 @@ Rates<T> make_rates(const lbmx_params *p, const Derived &d)
 }
 
 struct Layout {
-    size_t slab_nodes;   // nodes per slab, 2^slab_shift_for(flow element bytes)
-    size_t lattice;      // bytes per lattice
+    size_t slab_nodes;   // nodes per slab of a checkpoint file, 2^slab_shift_for(flow element bytes)
+    size_t file;         // bytes of a lattice in a checkpoint file (whole slabs)
+    size_t lattice;      // bytes per lattice: n planes, and room for the file's slabs
     size_t scratch_off;  // byte offset of the Nu scratch
     size_t total;
 };
@@ -223,7 +224,12 @@ inline Layout layout_of(const lbmx_params *p)
     const size_t cells = (size_t)p->n * p->n * p->n;
     L.slab_nodes = size_t(1) << slab_shift_for(flow_size(p->storage));
     const size_t slabs = (cells + L.slab_nodes - 1) / L.slab_nodes;
-    L.lattice = slabs * L.slab_nodes * (19 * flow_size(p->storage) + 7 * energy_size(p->storage));
+    const size_t bf = flow_size(p->storage), bg = energy_size(p->storage);
+    const size_t nn = (size_t)p->n * p->n;
+    L.file = slabs * L.slab_nodes * (19 * bf + 7 * bg);
+    const size_t planes = (size_t)p->n * (19 * (size_t)segment_bytes(uint32_t(nn * bf)) +
+                                          7 * (size_t)segment_bytes(uint32_t(nn * bg)));
+    L.lattice = align_up(std::max(L.file, planes), 256);
     L.scratch_off = 2 * L.lattice;
     L.total = L.scratch_off + align_up(sizeof(double) * (4 * (size_t)p->n + 8), 256);
     return L;
@@ -231,7 +237,7 @@ inline Layout layout_of(const lbmx_params *p)
 
 
 // A lattice seen by the launchers: `lat` is the lattice holding the current
-// state, `off32` selects 32-bit offsets.  `spare` is the cavity's other
+// state.  `spare` is the cavity's other
 // lattice (spare_bytes long): the next step overwrites all of it, so between
 // steps it serves as the staging buffer of transfers and readbacks, which
 // therefore allocate no device memory.  A lattice holds at least 52 bytes
@@ -242,7 +248,6 @@ struct View {
     size_t spare_bytes;
     int n, wall_type;
     double theta_hot, theta_cold;
-    bool off32;
     hipStream_t stream;
     double vshift;     // g beta / 2 for Guo's forcing (reported velocity), else 0
     double theta_ref;
@@ -251,7 +256,7 @@ struct View {
 };
 
 inline View make_view(char *lat, char *spare, size_t spare_bytes, const lbmx_params &p,
-                      const Derived &d, bool off32, hipStream_t stream)
+                      const Derived &d, hipStream_t stream)
 {
     View v;
     v.lat = lat;
@@ -261,7 +266,6 @@ inline View make_view(char *lat, char *spare, size_t spare_bytes, const lbmx_par
     v.wall_type = p.wall_type;
     v.theta_hot = p.theta_hot;
     v.theta_cold = p.theta_cold;
-    v.off32 = off32;
     v.stream = stream;
     v.vshift = p.force_model == LBMX_FORCE_GUO ? 0.5 * d.gbeta * p.buoyancy_scale : 0.0;
     v.theta_ref = p.theta_ref;
@@ -294,19 +298,33 @@ Geometry<typename St::T> geometry(const View &v)
     return g;
 }
 
+// Grid of the kernels that take one thread per node of plane blockIdx.y in
+// blocks of 256.
+inline dim3 plane_grid(int n) { return dim3((unsigned(n) * unsigned(n) + 255) / 256, unsigned(n)); }
+
 constexpr uint32_t kAllPops = (1u << 26) - 1;
 
 template <class St, typename Src>
 lbmx_status launch_unstream(const View &v, const Src &src, uint32_t mask = kAllPops)
 {
+    hipLaunchKernelGGL((k_unstream<St, Src>), plane_grid(v.n), dim3(256), 0, v.stream, v.lat,
+                       geometry<St>(v), src, mask);
+    HIP_TRY(hipGetLastError());
+    return LBMX_OK;
+}
+
+// The lattice at v.lat into checkpoint-file slabs in the spare lattice (save),
+// or the slabs in the spare lattice into the planes at v.lat.
+template <class St>
+lbmx_status launch_relayout(const View &v, const Layout &L, bool save)
+{
     const size_t cells = (size_t)v.n * v.n * v.n;
-    const unsigned blocks = (unsigned)((cells + 255) / 256);
-    if (v.off32)
-        hipLaunchKernelGGL((k_unstream<St, true, Src>), dim3(blocks), dim3(256), 0, v.stream, v.lat,
-                           geometry<St>(v), src, mask);
+    const size_t slots = (cells + L.slab_nodes - 1) / L.slab_nodes * L.slab_nodes;
+    const dim3 grid(unsigned((slots + 255) / 256));
+    if (save)
+        hipLaunchKernelGGL((k_relayout<St, true>), grid, dim3(256), 0, v.stream, v.lat, v.spare, v.n, slots);
     else
-        hipLaunchKernelGGL((k_unstream<St, false, Src>), dim3(blocks), dim3(256), 0, v.stream, v.lat,
-                           geometry<St>(v), src, mask);
+        hipLaunchKernelGGL((k_relayout<St, false>), grid, dim3(256), 0, v.stream, v.lat, v.spare, v.n, slots);
     HIP_TRY(hipGetLastError());
     return LBMX_OK;
 }
@@ -314,14 +332,8 @@ lbmx_status launch_unstream(const View &v, const Src &src, uint32_t mask = kAllP
 template <class St>
 lbmx_status launch_macro(const View &v, double *r, double *u, double *w3, double *w, double *th)
 {
-    const size_t cells = (size_t)v.n * v.n * v.n;
-    const unsigned blocks = (unsigned)((cells + 255) / 256);
-    if (v.off32)
-        hipLaunchKernelGGL((k_macro<St, true>), dim3(blocks), dim3(256), 0, v.stream, v.lat,
-                           geometry<St>(v), v.vshift, v.theta_ref, r, u, w3, w, th);
-    else
-        hipLaunchKernelGGL((k_macro<St, false>), dim3(blocks), dim3(256), 0, v.stream, v.lat,
-                           geometry<St>(v), v.vshift, v.theta_ref, r, u, w3, w, th);
+    hipLaunchKernelGGL((k_macro<St>), plane_grid(v.n), dim3(256), 0, v.stream, v.lat,
+                       geometry<St>(v), v.vshift, v.theta_ref, r, u, w3, w, th);
     HIP_TRY(hipGetLastError());
     return LBMX_OK;
 }
@@ -329,14 +341,8 @@ lbmx_status launch_macro(const View &v, double *r, double *u, double *w3, double
 template <class St>
 lbmx_status launch_pops(const View &v, int first, int count, double *out)
 {
-    const size_t cells = (size_t)v.n * v.n * v.n;
-    const unsigned blocks = (unsigned)((cells + 255) / 256);
-    if (v.off32)
-        hipLaunchKernelGGL((k_pops<St, true>), dim3(blocks), dim3(256), 0, v.stream, v.lat,
-                           geometry<St>(v), first, count, out);
-    else
-        hipLaunchKernelGGL((k_pops<St, false>), dim3(blocks), dim3(256), 0, v.stream, v.lat,
-                           geometry<St>(v), first, count, out);
+    hipLaunchKernelGGL((k_pops<St>), plane_grid(v.n), dim3(256), 0, v.stream, v.lat,
+                       geometry<St>(v), first, count, out);
     HIP_TRY(hipGetLastError());
     return LBMX_OK;
 }
@@ -449,12 +455,8 @@ lbmx_status launch_nu(const View &v, double *scratch, double *map)
     const int n = v.n;
     double *out = scratch + 4 * (size_t)n;
     const int threads = n <= 64 ? 64 : (n <= 128 ? 128 : 256);
-    if (v.off32)
-        hipLaunchKernelGGL((k_nu_rows<St, true>), dim3(n), dim3(threads), 0, v.stream, v.lat,
-                           geometry<St>(v), v.theta_hot, v.nu_stencil, v.d_yy, scratch, map);
-    else
-        hipLaunchKernelGGL((k_nu_rows<St, false>), dim3(n), dim3(threads), 0, v.stream, v.lat,
-                           geometry<St>(v), v.theta_hot, v.nu_stencil, v.d_yy, scratch, map);
+    hipLaunchKernelGGL((k_nu_rows<St>), dim3(n), dim3(threads), 0, v.stream, v.lat,
+                       geometry<St>(v), v.theta_hot, v.nu_stencil, v.d_yy, scratch, map);
     hipLaunchKernelGGL(k_nu_final<0>, dim3(1), dim3(256), 0, v.stream, scratch, n, out);
     HIP_TRY(hipGetLastError());
     return LBMX_OK;

@@ -1,15 +1,15 @@
 // kernels.hpp -- HIP kernels of the double-MRT cavity step for gfx950.
 //
 // Data layout in HBM: two lattices (ping-pong).  Nodes are numbered
-// c = x + n*(y + n*z), x fastest.  A lattice is a sequence of slabs of 2^L
-// consecutive nodes; a slab holds 19 D3Q19 segments of 2^L flow elements
-// followed by 7 D3Q7 segments of 2^L energy elements (segment i holds
-// population i of the slab's nodes, in node order).  A wavefront therefore
-// reads and writes 64 consecutive elements per population, and the 26
-// population streams of a block of rows lie within one slab (a few hundred
-// KB) instead of 26 planes n^3 elements apart, which measured about 6%
-// faster on the pull pattern than whole-lattice planes.  L is fixed per
-// storage format so that a flow segment is 8 KB.
+// c = x + n*(y + n*z), x fastest.  A lattice is a sequence of n planes (one
+// per z); a plane holds 19 D3Q19 segments of n^2 flow elements followed by 7
+// D3Q7 segments of n^2 energy elements (segment i holds population i of the
+// plane's nodes, x fastest).  A wavefront therefore reads and writes 64
+// consecutive elements per population, the 26 streams of a block lie within
+// three planes (a few MB) instead of 26 regions n^3 elements apart, and the
+// address of "population i of the node e_i upstream" is a uniform base (which
+// plane, which segment, which shift) plus a per-lane offset that is the same
+// for every population: the addresses cost no vector instruction per access.
 //
 // What a lattice holds: the post-collision populations f*(t-1), g*(t-1).
 // The step kernel gathers ("pulls") them from the upstream neighbours, which
@@ -88,8 +88,9 @@ struct Codec<__hip_bfloat16> {
     }
 };
 
-// log2 of the nodes per slab for a flow element of `flow_bytes` bytes:
-// 8 KB flow segments (2^10 FP64, 2^11 FP32, 2^12 16-bit elements).
+// Checkpoint files hold a lattice in slabs of 2^L consecutive nodes (19 flow
+// segments of 2^L elements, then 7 energy segments); L by the flow element's
+// bytes: 8 KB flow segments (2^10 FP64, 2^11 FP32, 2^12 16-bit elements).
 __host__ __device__ constexpr int slab_shift_for(size_t flow_bytes)
 {
     return flow_bytes >= 8 ? 10 : (flow_bytes == 4 ? 11 : 12);
@@ -248,176 +249,275 @@ __device__ __forceinline__ bool x_wall_dirichlet(int wall_type) { return wall_ty
 __device__ __forceinline__ bool z_wall_dirichlet(int wall_type) { return wall_type == 2; }
 
 // ----------------------------------------------------------------- access
-// Byte offsets are 32-bit when a whole lattice spans less than 4 GiB: a load
-// is then a uniform 64-bit base plus a 32-bit per-lane offset (one VALU add
-// per population instead of 64-bit address arithmetic); larger lattices use
-// 64-bit offsets.  Stores are non-temporal: the written lattice is read back
-// only in the next step, long after it has left the caches.
-template <bool kOff32>
-struct Access {
-    using I = typename std::conditional<kOff32, uint32_t, size_t>::type;
-    // Lattices live in device global memory; saying so lets pointers read from
-    // a table (batch kernel) use global rather than flat instructions.
-    template <typename S>
-    using gptr = __attribute__((address_space(1))) S *;
-    // Loads return the storage bits (Codec<S>::Raw); Codec<S>::dec converts.
-    // 8-byte populations (FP64 storage) are read non-temporally as well
-    // (measured 2.5 % faster at 256^3); narrower ones are not (slower: a
-    // wavefront's x-shifted reads share cache lines with its neighbours').
-    template <typename S>
-    static __device__ __forceinline__ typename Codec<S>::Raw ld(const char *base, I byte)
-    {
-        using R = typename Codec<S>::Raw;
-        if constexpr (sizeof(R) == 8)
-            return __builtin_nontemporal_load((gptr<const R>)((gptr<const char>)base + byte));
-        else
-            return *(gptr<const R>)((gptr<const char>)base + byte);
-    }
-    template <typename S>
-    static __device__ __forceinline__ void st(char *base, I byte, typename Codec<S>::Raw v)
-    {
-        using R = typename Codec<S>::Raw;
-        __builtin_nontemporal_store(v, (gptr<R>)((gptr<char>)base + byte));
-    }
-};
-
-// Byte offsets of population i of node c inside a lattice (slab layout
-// above): slab (c >> L) * slab_bytes + segment i + slot (c mod 2^L), written
-// as c * b + (c >> L) * (slab_bytes - segment_bytes) + i * segment_bytes.
-// Every term is below the lattice size, so 32-bit offsets cannot wrap.
-template <class St, bool kOff32>
-struct Lat {
-    using I = typename Access<kOff32>::I;
-    static constexpr int L = St::kSlabShift;
-    static constexpr I bF = I(sizeof(typename St::F)), bG = I(sizeof(typename St::G));
-    static constexpr I segF = bF << L, segG = bG << L;
-    static constexpr I slab = 19 * segF + 7 * segG;
-    static __device__ __forceinline__ I f(I c, int i)
-    {
-        return c * bF + (c >> L) * (slab - segF) + I(i) * segF;
-    }
-    static __device__ __forceinline__ I g(I c, int i)
-    {
-        return c * bG + (c >> L) * (slab - segG) + 19 * segF + I(i) * segG;
-    }
-};
-
-// ------------------------------------------------------------------- pull
-// Gather the populations of node (x, y, z) at time t from the post-collision
-// lattice `src` (time t-1): streaming plus wall conditions.
-template <class St, bool kOff32>
-__device__ __forceinline__ void pull(const char *__restrict__ src,
-                                     const Geometry<typename St::T> &geo, int x, int y, int z,
-                                     typename St::T f[19], typename St::T g[7])
+// Populations are read and written with buffer instructions: a uniform base
+// (the resource), a uniform 32-bit offset (which population of which plane,
+// shifted by which neighbour) and a per-lane 32-bit offset that is the same
+// for every population, so an access costs no vector arithmetic.  The
+// resource spans 4 GiB from its base; every address formed lies inside the
+// lattice.
+using Buffer = __amdgpu_buffer_rsrc_t;
+__device__ __forceinline__ Buffer make_buffer(const char *base)
 {
-    using T = typename St::T;
-    using SF = typename St::F;
-    using SG = typename St::G;
-    using A = Access<kOff32>;
-    using Lt = Lat<St, kOff32>;
-    using I = typename A::I;
-    const int n = geo.n;
-    const I idx = I(x) + I(n) * (I(y) + I(n) * I(z));
-    const bool xl = x == 0, xh = x == n - 1;
-    const bool yl = y == 0, yh = y == n - 1;
-    const bool zl = z == 0, zh = z == n - 1;
-    const I sy = I(n), sz = I(n) * I(n);
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(base), short(0), int(0xffffffffu), 0x00020000);
+}
+constexpr int kNonTemporal = 2;  // the nt bit of a buffer instruction
 
-#pragma unroll
-    for (int i = 0; i < 19; ++i) {
-        const int ex = ex19(i), ey = ey19(i), ez = ez19(i);
-        const bool out = (ex > 0 && xl) || (ex < 0 && xh) || (ey > 0 && yl) || (ey < 0 && yh) ||
-                         (ez > 0 && zl) || (ez < 0 && zh);
-        // upstream node x - e_i (unsigned wrap-around arithmetic is exact here;
-        // a wrapped value only occurs where `out` discards it)
-        const I up = idx - I(ex) - I(ey) * sy - I(ez) * sz;
-        // Inside: f*_i(x - e_i).  Outside: f*_ibar(x) reflected at the wall.
-        const I e = out ? Lt::f(idx, opp19(i)) : Lt::f(up, i);
-        f[i] = Codec<SF>::dec(A::template ld<SF>(src, e), T(w19(i)));
+// Loads return the storage bits (Codec<S>::Raw); Codec<S>::dec converts.
+// 8-byte populations (FP64 storage) are read non-temporally (measured 2.5 %
+// faster at 256^3); narrower ones are not (slower: a wavefront's x-shifted
+// reads share cache lines with its neighbours').
+template <typename S>
+__device__ __forceinline__ typename Codec<S>::Raw ld(Buffer b, uint32_t lane, uint32_t uniform)
+{
+    using R = typename Codec<S>::Raw;
+    if constexpr (sizeof(R) == 8) {
+        typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+        return __builtin_bit_cast(R, u2(__builtin_amdgcn_raw_buffer_load_b64(b, lane, uniform, kNonTemporal)));
+    } else if constexpr (sizeof(R) == 4)
+        return __builtin_bit_cast(R, __builtin_amdgcn_raw_buffer_load_b32(b, lane, uniform, 0));
+    else
+        return __builtin_bit_cast(R, __builtin_amdgcn_raw_buffer_load_b16(b, lane, uniform, 0));
+}
+// Stores are non-temporal: the written lattice is read back only in the next
+// step, long after it has left the caches.
+template <typename S>
+__device__ __forceinline__ void st(Buffer b, uint32_t lane, uint32_t uniform, typename Codec<S>::Raw v)
+{
+    using R = typename Codec<S>::Raw;
+    if constexpr (sizeof(R) == 8) {
+        typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, v), b, lane, uniform, kNonTemporal);
+    } else if constexpr (sizeof(R) == 4)
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), b, lane, uniform, kNonTemporal);
+    else
+        __builtin_amdgcn_raw_buffer_store_b16(v, b, lane, uniform, kNonTemporal);
+}
+
+// Bytes of a segment of n^2 elements: whole 128-byte lines, so that a
+// wavefront's 64 consecutive nodes start on a line in every segment and its
+// stores cover whole lines (FP32 steps at 75^3: 20.3 us unpadded, 18.2 us;
+// 16-bit at 100^3: 24.9, 21.3 us), and one line more where a segment of 64 KB
+// or above is a multiple of 4 KB: the 26 streams then do not start on the same
+// memory channel (256^3: FP32 589 -> 583 us, FP16 + FP32 384 -> 365 us; small
+// segments gain nothing, at 64^3 FP64 the line costs 5 %).
+__host__ __device__ __forceinline__ constexpr uint32_t segment_bytes(uint32_t bytes)
+{
+    const uint32_t lines = (bytes + 127) / 128 * 128;
+    return lines >= 65536 && lines % 4096 == 0 ? lines + 128 : lines;
+}
+
+// A plane: flow segment i at i * segF, energy segment i at offG + i * segG,
+// the next plane at `bytes`.
+template <class St>
+struct Plane {
+    static constexpr uint32_t bF = uint32_t(sizeof(typename St::F)), bG = uint32_t(sizeof(typename St::G));
+    uint32_t segF, segG, offG, bytes;
+    __host__ __device__ __forceinline__ explicit Plane(uint32_t n)
+        : segF(segment_bytes(n * n * bF)), segG(segment_bytes(n * n * bG)), offG(19 * segF),
+          bytes(offG + 7 * segG)
+    {
     }
+};
 
+// Where a thread's node lies: the uniform address `base` and the lane's byte
+// offsets from it in a flow and in an energy segment 0.  Either base is the
+// node's plane (z uniform over the block) or the lattice (z per lane, whose
+// offsets then include z planes; the lattice is below 4 GiB).
+struct Site {
+    uint32_t vF, vG;
+    bool xl, xh, yl, yh, zl, zh;  // on the walls x = 0, x = H, ...
+};
+
+template <class St>
+__device__ __forceinline__ Site site_in_plane(int n, int x, int y, int z)
+{
+    Site s;
+    s.vF = uint32_t(x + n * y) * Plane<St>::bF;
+    s.vG = uint32_t(x + n * y) * Plane<St>::bG;
+    s.xl = x == 0, s.xh = x == n - 1;
+    s.yl = y == 0, s.yh = y == n - 1;
+    s.zl = z == 0, s.zh = z == n - 1;
+    return s;
+}
+
+// The energy populations that came from a wall: v, the reflected value, turns
+// into 2 w_T theta_W - v at a Dirichlet wall and stays at an adiabatic one.
+// kXY, kZ: whether a lane may be at an x or y wall, at a z wall.
+template <typename T, bool kXY, bool kZ>
+__device__ __forceinline__ void wall_energy(const Geometry<T> &geo, const Site &s, int y, T g[7])
+{
     const T two_w = T(0.25);  // 2 w_T,i for the moving directions
-    const T th_lin = theta_linear(geo, y);
-    const bool xd = x_wall_dirichlet(geo.wall_type);
-    const bool zd = z_wall_dirichlet(geo.wall_type);
-    const T es = St::kScaledG ? geo.escale : T(1);
-    const T wg = T(w7(1)) * es;
-    auto ldg = [&](I e) { return Codec<SG>::dec(A::template ld<SG>(src, e), wg); };
-    g[0] = Codec<SG>::dec(A::template ld<SG>(src, Lt::g(idx, 0)), T(w7(0)) * es);
-    {   // +x from x-1 | wall x = 0
-        const T v = ldg(xl ? Lt::g(idx, 2) : Lt::g(idx - 1, 1));
-        g[1] = xl ? (xd ? two_w * th_lin - v : v) : v;
+    if (kXY) {
+        if (s.yl)  // +y from the hot wall y = 0 (Eq. 6)
+            g[3] = two_w * geo.theta_hot - g[3];
+        if (s.yh)  // -y from the cold wall y = H (Eq. 7)
+            g[4] = two_w * geo.theta_cold - g[4];
     }
-    {   // -x from x+1 | wall x = H
-        const T v = ldg(xh ? Lt::g(idx, 1) : Lt::g(idx + 1, 2));
-        g[2] = xh ? (xd ? two_w * th_lin - v : v) : v;
-    }
-    {   // +y from y-1 | hot wall y = 0 (Eq. 6)
-        const T v = ldg(yl ? Lt::g(idx, 4) : Lt::g(idx - sy, 3));
-        g[3] = yl ? two_w * geo.theta_hot - v : v;
-    }
-    {   // -y from y+1 | cold wall y = H (Eq. 7)
-        const T v = ldg(yh ? Lt::g(idx, 3) : Lt::g(idx + sy, 4));
-        g[4] = yh ? two_w * geo.theta_cold - v : v;
-    }
-    {   // +z from z-1 | wall z = 0
-        const T v = ldg(zl ? Lt::g(idx, 6) : Lt::g(idx - sz, 5));
-        g[5] = zl ? (zd ? two_w * th_lin - v : v) : v;
-    }
-    {   // -z from z+1 | wall z = H
-        const T v = ldg(zh ? Lt::g(idx, 5) : Lt::g(idx + sz, 6));
-        g[6] = zh ? (zd ? two_w * th_lin - v : v) : v;
+    const bool xd = kXY && x_wall_dirichlet(geo.wall_type), zd = kZ && z_wall_dirichlet(geo.wall_type);
+    if ((xd && (s.xl || s.xh)) || (zd && (s.zl || s.zh))) {
+        const T th_lin = theta_linear(geo, y);
+        if (xd && s.xl)
+            g[1] = two_w * th_lin - g[1];
+        if (xd && s.xh)
+            g[2] = two_w * th_lin - g[2];
+        if (zd && s.zl)
+            g[5] = two_w * th_lin - g[5];
+        if (zd && s.zh)
+            g[6] = two_w * th_lin - g[6];
     }
 }
 
-// Write node c's 26 populations (post-collision values of step `step`).
-template <class St, bool kOff32>
-__device__ __forceinline__ void put(char *__restrict__ dst, size_t node, uint32_t step,
-                                    const typename St::T f[19], const typename St::T g[7],
-                                    typename St::T inv_es)
+// ------------------------------------------------------------------- pull
+// Gather the populations of the node at `s` (height y) at time t from the
+// post-collision lattice (time t-1): streaming plus wall conditions.
+//
+// Population i comes from the node x - e_i, or, where that is outside, from
+// population ibar of the node itself (reflected at the wall).  Inside, the
+// address is base + d_i + lane offset with a uniform d_i; a lane at a wall
+// takes the offset that undoes d_i and selects segment ibar.  kLaneZ: z varies
+// over the lanes (base is the lattice) instead of being uniform (base is the
+// plane).  kEdge = false: no lane is at an x or y wall (kLaneZ: at any wall).
+template <class St>
+struct RawPops {
+    typename Codec<typename St::F>::Raw f[19];
+    typename Codec<typename St::G>::Raw g[7];
+};
+
+template <class St, bool kLaneZ, bool kEdge>
+__device__ __forceinline__ void load_pops(const char *__restrict__ base, int n, const Site &s, RawPops<St> &r)
+{
+    Plane<St> pl{uint32_t(n)};
+    uint32_t row = uint32_t(n);
+    // keep the uniform offsets out of the registers between uses: they are
+    // recomputed by the scalar unit (a caller's loop would hoist all of them)
+    asm volatile("" : "+s"(pl.segF), "+s"(pl.segG), "+s"(pl.offG), "+s"(pl.bytes), "+s"(row));
+    // Both offsets carry a bias of two planes, taken off the base, so that
+    // neither is negative: the uniform one lies up to a plane and a row below
+    // the node's plane, and a wall lane's undoes up to two planes.
+    const uint32_t P = pl.bytes, bias = 2 * P;
+    const Buffer buf = make_buffer(base - 4 * size_t(P));
+    const uint32_t vF = s.vF + bias, vG = s.vG + bias;
+
+    auto source = [&](int ex, int ey, int ez, uint32_t seg, uint32_t seg_opp, uint32_t el, uint32_t v,
+                      uint32_t &d) -> uint32_t {
+        d = bias + seg - ez * P - (ex + ey * row) * el;
+        if (!kLaneZ && ((ez > 0 && s.zl) || (ez < 0 && s.zh)))
+            d = bias + seg_opp;
+        if (!kEdge || (ex == 0 && ey == 0 && (!kLaneZ || ez == 0)))
+            return v;
+        const bool out = (ex > 0 && s.xl) || (ex < 0 && s.xh) || (ey > 0 && s.yl) || (ey < 0 && s.yh) ||
+                         (kLaneZ && ((ez > 0 && s.zl) || (ez < 0 && s.zh)));
+        return out ? v + (bias + seg_opp - d) : v;
+    };
+#pragma unroll
+    for (int i = 0; i < 19; ++i) {
+        uint32_t d;
+        const uint32_t v = source(ex19(i), ey19(i), ez19(i), i * pl.segF, opp19(i) * pl.segF, pl.bF, vF, d);
+        r.f[i] = ld<typename St::F>(buf, v, d);
+    }
+#pragma unroll
+    for (int i = 0; i < 7; ++i) {  // D3Q7 directions are the first 7 of D3Q19
+        uint32_t d;
+        const uint32_t v = source(ex19(i), ey19(i), ez19(i), pl.offG + i * pl.segG,
+                                  pl.offG + opp19(i) * pl.segG, pl.bG, vG, d);
+        r.g[i] = ld<typename St::G>(buf, v, d);
+    }
+}
+
+template <class St, bool kLaneZ, bool kEdge>
+__device__ __forceinline__ void decode_pops(const RawPops<St> &r, const Geometry<typename St::T> &geo,
+                                            const Site &s, int y, typename St::T f[19], typename St::T g[7])
+{
+    using T = typename St::T;
+#pragma unroll
+    for (int i = 0; i < 19; ++i)
+        f[i] = Codec<typename St::F>::dec(r.f[i], T(w19(i)));
+    const T es = St::kScaledG ? geo.escale : T(1);
+#pragma unroll
+    for (int i = 0; i < 7; ++i)
+        g[i] = Codec<typename St::G>::dec(r.g[i], T(w7(i)) * es);
+    wall_energy<T, kEdge, kEdge || !kLaneZ>(geo, s, y, g);
+}
+
+template <class St, bool kLaneZ, bool kEdge = true>
+__device__ __forceinline__ void pull(const char *__restrict__ base, const Geometry<typename St::T> &geo,
+                                     const Site &s, int y, typename St::T f[19], typename St::T g[7])
+{
+    RawPops<St> r;
+    load_pops<St, kLaneZ, kEdge>(base, geo.n, s, r);
+    decode_pops<St, kLaneZ, kEdge>(r, geo, s, y, f, g);
+}
+
+// Write the 26 populations of node number `node` at `s` (post-collision values
+// of step `step`).
+template <class St>
+__device__ __forceinline__ void put(char *__restrict__ base, const Site &s, uint32_t node, uint32_t step,
+                                    const Geometry<typename St::T> &geo, const typename St::T f[19],
+                                    const typename St::T g[7])
 {
     using T = typename St::T;
     using SF = typename St::F;
     using SG = typename St::G;
-    using A = Access<kOff32>;
-    using Lt = Lat<St, kOff32>;
-    using I = typename A::I;
-    const I c = I(node);
+    Plane<St> pl{uint32_t(geo.n)};
+    asm volatile("" : "+s"(pl.segF), "+s"(pl.segG), "+s"(pl.offG));  // as in load_pops
+    const Buffer buf = make_buffer(base);
 #pragma unroll
     for (int i = 0; i < 19; ++i)
-        A::template st<SF>(dst, Lt::f(c, i), Codec<SF>::enc(f[i], T(inv_w19(i))));
+        st<SF>(buf, s.vF, i * pl.segF, Codec<SF>::enc(f[i], T(inv_w19(i))));
     if constexpr (std::is_same<SG, Fix16>::value) {
-        const RoundBits rb(uint32_t(node), step);
+        const RoundBits rb(node, step);
 #pragma unroll
         for (int i = 0; i < 7; ++i)
-            A::template st<SG>(dst, Lt::g(c, i),
-                               Codec<SG>::enc_r(g[i], T(inv_w7(i)) * inv_es, rb.u16(i)));
+            st<SG>(buf, s.vG, pl.offG + i * pl.segG,
+                   Codec<SG>::enc_r(g[i], T(inv_w7(i)) * geo.inv_escale, rb.u16(i)));
     } else {
 #pragma unroll
         for (int i = 0; i < 7; ++i)
-            A::template st<SG>(dst, Lt::g(c, i), Codec<SG>::enc(g[i], T(inv_w7(i))));
+            st<SG>(buf, s.vG, pl.offG + i * pl.segG, Codec<SG>::enc(g[i], T(inv_w7(i))));
     }
 }
 
 // -------------------------------------------------------------- step kernel
-// One thread per node; block (bx, by) over (x, y), grid.z = z.  kForce is
-// the force model (LBMX_FORCE_*).
-template <class St, bool kOff32, int kForce>
+// floor(c / n) for c < 2^24: the float quotient is within 1/2 of the true
+// one, so a single correction by one is exact.
+__device__ __forceinline__ uint32_t div_small(uint32_t c, uint32_t n, float inv_n)
+{
+    uint32_t q = uint32_t(float(c) * inv_n);
+    const int32_t r = int32_t(c) - int32_t(q * n);
+    if (r < 0)
+        q -= 1;
+    else if (r >= int32_t(n))
+        q += 1;
+    return q;
+}
+
+// One thread per node, grid.z = z.  kFlat: the blocks take the plane's n^2
+// nodes in storage order, so that every wavefront but the last is full for any
+// n (rows of 300 nodes in blocks of 256 would leave 41 % of the lanes idle);
+// otherwise a block covers (bx, by) nodes over (x, y).  kForce is the force
+// model (LBMX_FORCE_*).
+template <class St, int kForce, bool kFlat>
 __global__ __launch_bounds__(1024) void k_step(const char *__restrict__ src, char *__restrict__ dst,
                                                Geometry<typename St::T> geo,
-                                               Rates<typename St::T> rates)
+                                               Rates<typename St::T> rates, float inv_n)
 {
     using T = typename St::T;
-    const int x = blockIdx.x * blockDim.x + threadIdx.x;
-    const int y = blockIdx.y * blockDim.y + threadIdx.y;
+    int x = blockIdx.x * blockDim.x + threadIdx.x;
+    int y = blockIdx.y * blockDim.y + threadIdx.y;
     const int z = blockIdx.z;
+    if (kFlat) {
+        y = int(div_small(uint32_t(x), uint32_t(geo.n), inv_n));
+        x -= y * geo.n;
+    }
     if (x >= geo.n || y >= geo.n)
         return;
+    const size_t plane = size_t(Plane<St>(uint32_t(geo.n)).bytes) * z;
+    const Site s = site_in_plane<St>(geo.n, x, y, z);
     T f[19], g[7];
-    pull<St, kOff32>(src, geo, x, y, z, f, g);
+    pull<St, false>(src + plane, geo, s, y, f, g);
     collide<T, kForce>(f, g, rates);
-    put<St, kOff32>(dst, size_t(x) + size_t(geo.n) * (size_t(y) + size_t(geo.n) * z), geo.step, f, g,
-                    geo.inv_escale);
+    put<St>(dst + plane, s, uint32_t(x) + uint32_t(geo.n) * (uint32_t(y) + uint32_t(geo.n) * z), geo.step,
+            geo, f, g);
 }
 
 // --------------------------------------------------------- state sources
@@ -559,7 +659,8 @@ struct SourceTwoFields {
 // otherwise P_i(y) is the value that the wall turns into S_ibar(y).  Only
 // the populations whose bit is set in `mask` (bit p: population p, flow
 // 0..18, energy 19..25) are written.
-template <class St, bool kOff32, typename Src>
+// One thread per node of plane blockIdx.y.
+template <class St, typename Src>
 __global__ __launch_bounds__(256) void k_unstream(char *__restrict__ dst,
                                                   Geometry<typename St::T> geo, Src srcS,
                                                   uint32_t mask)
@@ -567,22 +668,21 @@ __global__ __launch_bounds__(256) void k_unstream(char *__restrict__ dst,
     using T = typename St::T;
     using SF = typename St::F;
     using SG = typename St::G;
-    using A = Access<kOff32>;
-    using Lt = Lat<St, kOff32>;
-    using I = typename A::I;
     const int n = geo.n;
-    const long long cells = (long long)n * n * n;
-    const long long c = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= cells)
+    const int cp = blockIdx.x * blockDim.x + threadIdx.x;
+    if (cp >= n * n)
         return;
-    const int x = int(c % n), y = int((c / n) % n), z = int(c / ((long long)n * n));
+    const int x = cp % n, y = cp / n, z = blockIdx.y;
+    const int c = x + n * (y + n * z);
+    const Plane<St> pl{uint32_t(geo.n)};
+    const Buffer plane = make_buffer(dst + size_t(pl.bytes) * z);
     for (int i = 0; i < 19; ++i) {
         if (!((mask >> i) & 1u))
             continue;
         const int tx = x + ex19(i), ty = y + ey19(i), tz = z + ez19(i);
         const bool in = tx >= 0 && tx < n && ty >= 0 && ty < n && tz >= 0 && tz < n;
-        double v = in ? srcS.f(i, tx + n * (ty + n * tz)) : srcS.f(opp19(i), int(c));
-        A::template st<SF>(dst, Lt::f(I(c), i), Codec<SF>::enc(T(v), T(inv_w19(i))));
+        double v = in ? srcS.f(i, tx + n * (ty + n * tz)) : srcS.f(opp19(i), c);
+        st<SF>(plane, uint32_t(cp) * pl.bF, i * pl.segF, Codec<SF>::enc(T(v), T(inv_w19(i))));
     }
     const double th_lin = double(geo.theta_hot) +
                           double(geo.theta_cold - geo.theta_hot) * (y + 0.5) / n;
@@ -596,7 +696,7 @@ __global__ __launch_bounds__(256) void k_unstream(char *__restrict__ dst,
         if (tx >= 0 && tx < n && ty >= 0 && ty < n && tz >= 0 && tz < n) {
             v = srcS.g(i, tx + n * (ty + n * tz));
         } else {
-            const double s_in = srcS.g(go[i], int(c));
+            const double s_in = srcS.g(go[i], c);
             bool dir;
             double tw = 0.0;
             if (ty < 0) { dir = true; tw = double(geo.theta_hot); }
@@ -607,15 +707,47 @@ __global__ __launch_bounds__(256) void k_unstream(char *__restrict__ dst,
             v = dir ? 2.0 * w7(go[i]) * tw - s_in : s_in;
         }
         const T inv_w = St::kScaledG ? T(inv_w7(i)) * geo.inv_escale : T(inv_w7(i));
-        A::template st<SG>(dst, Lt::g(I(c), i), Codec<SG>::enc(T(v), inv_w));
+        st<SG>(plane, uint32_t(cp) * pl.bG, pl.offG + i * pl.segG, Codec<SG>::enc(T(v), inv_w));
     }
+}
+
+// Copy a lattice from its planes into the slabs of a checkpoint file (kSave;
+// slots past the last node become 0) or back.  One thread per slab slot.
+template <class St, bool kSave>
+__global__ __launch_bounds__(256) void k_relayout(char *__restrict__ planes, char *__restrict__ slabs, int n,
+                                                  size_t slots)
+{
+    using RF = typename Codec<typename St::F>::Raw;
+    using RG = typename Codec<typename St::G>::Raw;
+    constexpr int L = St::kSlabShift;
+    constexpr size_t segF = sizeof(RF) << L, segG = sizeof(RG) << L, slab = 19 * segF + 7 * segG;
+    const size_t c = size_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (c >= slots)
+        return;
+    const size_t nn = size_t(n) * n, slot = c & ((size_t(1) << L) - 1);
+    const bool node = c < nn * n;
+    const Plane<St> pl{uint32_t(n)};
+    char *const sl = slabs + (c >> L) * slab;
+    char *const pp = planes + c / nn * pl.bytes;
+    const size_t cp = c % nn;
+    auto move = [&](auto *file, auto *lat) {
+        if (kSave)
+            *file = node ? *lat : 0;
+        else if (node)
+            *lat = *file;
+    };
+    for (int i = 0; i < 19; ++i)
+        move(reinterpret_cast<RF *>(sl + i * segF) + slot, reinterpret_cast<RF *>(pp + size_t(i) * pl.segF) + cp);
+    for (int i = 0; i < 7; ++i)
+        move(reinterpret_cast<RG *>(sl + 19 * segF + i * segG) + slot,
+             reinterpret_cast<RG *>(pp + pl.offG + size_t(i) * pl.segG) + cp);
 }
 
 // ------------------------------------------------------------ read kernels
 // Macroscopic fields at time t: rho, u = j / rho, theta (double outputs).
 // Guo's forcing reports u_z = j_z / rho + vshift (theta - theta_ref) with
 // vshift = g beta / 2 (the half-force velocity); vshift = 0 otherwise.
-template <class St, bool kOff32>
+template <class St>
 __global__ __launch_bounds__(256) void k_macro(const char *__restrict__ src,
                                                Geometry<typename St::T> geo, double vshift,
                                                double theta_ref, double *rho, double *ux,
@@ -623,13 +755,14 @@ __global__ __launch_bounds__(256) void k_macro(const char *__restrict__ src,
 {
     using T = typename St::T;
     const int n = geo.n;
-    const long long cells = (long long)n * n * n;
-    const long long c = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= cells)
+    const int cp = blockIdx.x * blockDim.x + threadIdx.x;
+    if (cp >= n * n)
         return;
-    const int x = int(c % n), y = int((c / n) % n), z = int(c / ((long long)n * n));
+    const int x = cp % n, y = cp / n, z = blockIdx.y;
+    const size_t c = size_t(cp) + size_t(n) * n * z;
     T f[19], g[7];
-    pull<St, kOff32>(src, geo, x, y, z, f, g);
+    pull<St, false>(src + size_t(Plane<St>(uint32_t(geo.n)).bytes) * z, geo, site_in_plane<St>(n, x, y, z), y, f,
+                    g);
     double dr = 0.0, j[3] = {0.0, 0.0, 0.0}, th = 0.0;
     for (int i = 0; i < 19; ++i) {
         dr += double(f[i]);
@@ -649,20 +782,22 @@ __global__ __launch_bounds__(256) void k_macro(const char *__restrict__ src,
 
 // Populations first .. first + count - 1 (flow 0..18, energy 19..25) at
 // time t as plain doubles: out[(p - first) * n^3 + c].
-template <class St, bool kOff32>
+template <class St>
 __global__ __launch_bounds__(256) void k_pops(const char *__restrict__ src,
                                               Geometry<typename St::T> geo, int first, int count,
                                               double *out)
 {
     using T = typename St::T;
     const int n = geo.n;
-    const long long cells = (long long)n * n * n;
-    const long long c = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= cells)
+    const int cp = blockIdx.x * blockDim.x + threadIdx.x;
+    if (cp >= n * n)
         return;
-    const int x = int(c % n), y = int((c / n) % n), z = int(c / ((long long)n * n));
+    const int x = cp % n, y = cp / n, z = blockIdx.y;
+    const size_t c = size_t(cp) + size_t(n) * n * z;
     T f[19], g[7];
-    pull<St, kOff32>(src, geo, x, y, z, f, g);
+    pull<St, false>(src + size_t(Plane<St>(uint32_t(geo.n)).bytes) * z, geo, site_in_plane<St>(n, x, y, z), y, f,
+                    g);
+    const size_t cells = size_t(n) * n * n;
     for (int k = 0; k < count; ++k) {
         const int p = first + k;
         out[(size_t)k * cells + c] = p < 19 ? w19(p) + double(f[p]) : double(g[p - 19]);
@@ -727,7 +862,7 @@ __device__ __forceinline__ void block_reduce4(double &sum, double &line, double 
 //   2  energy crossing the wall links, q = 2 (g_+y - th_w / 8), as -q / D_yy
 //      (g_+y at the wall node is the population that came from the wall).
 // partial[z] = {sum over x, X = 0.5 line contribution, max, non-finite count}.
-template <class St, bool kOff32>
+template <class St>
 __global__ __launch_bounds__(256) void k_nu_rows(const char *__restrict__ src,
                                                  Geometry<typename St::T> geo, double theta_hot,
                                                  int stencil, double d_yy, double *partial,
@@ -736,10 +871,11 @@ __global__ __launch_bounds__(256) void k_nu_rows(const char *__restrict__ src,
     using T = typename St::T;
     const int n = geo.n;
     const int z = blockIdx.x;
+    const char *const plane = src + size_t(Plane<St>(uint32_t(geo.n)).bytes) * z;
     double sum = 0.0, line = 0.0, mx = -1.0e300, bad = 0.0;
     for (int x = threadIdx.x; x < n; x += blockDim.x) {
         T f[19], g0[7], g1[7];
-        pull<St, kOff32>(src, geo, x, 0, z, f, g0);
+        pull<St, false>(plane, geo, site_in_plane<St>(n, x, 0, z), 0, f, g0);
         double th0 = 0.0, th1 = 0.0;
         for (int i = 0; i < 7; ++i)
             th0 += double(g0[i]);
@@ -749,7 +885,7 @@ __global__ __launch_bounds__(256) void k_nu_rows(const char *__restrict__ src,
         } else if (stencil == 2) {
             nu = double(n) * 2.0 * (double(g0[3]) - 0.125 * theta_hot) / d_yy;
         } else {
-            pull<St, kOff32>(src, geo, x, 1, z, f, g1);
+            pull<St, false>(plane, geo, site_in_plane<St>(n, x, 1, z), 1, f, g1);
             for (int i = 0; i < 7; ++i)
                 th1 += double(g1[i]);
             nu = -double(n) * (9.0 * th0 - th1 - 8.0 * theta_hot) / 3.0;

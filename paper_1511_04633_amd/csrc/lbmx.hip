@@ -66,8 +66,7 @@ struct lbmx_cavity {
     bool own_ws;
     int cur;
     int64_t t;
-    int bx, by;
-    bool off32;  // a lattice spans < 4 GiB: kernels use 32-bit byte offsets
+    int bx, by;  // block of the step kernel; 0, 0: the default launch
     // The state is unusable: a Nu evaluation found non-finite values, or a
     // device call failed while the state was being changed.  Stepping,
     // saving and using the cavity as a source return LBMX_ESTATE until an
@@ -83,13 +82,15 @@ double *nu_scratch(lbmx_cavity *h) { return reinterpret_cast<double *>(h->ws + h
 
 View view(lbmx_cavity *h)
 {
-    return make_view(lattice(h, h->cur), lattice(h, 1 - h->cur), h->L.lattice, h->p, h->d, h->off32,
-                     h->stream);
+    return make_view(lattice(h, h->cur), lattice(h, 1 - h->cur), h->L.lattice, h->p, h->d, h->stream);
 }
 
-// One row of up to 256 nodes along x per block row; up to 256 threads per
-// block (at 256^3, 256 x 1 blocks measured 1% faster than 256 x 2 and 5%
-// faster than half-row 128 x 2 blocks).
+// Threads per block of the default launch (blocks over a plane's nodes in
+// storage order).  At 256^3 FP32 this is the 256 x 1 block, which measured 1 %
+// faster than 256 x 2 and 5 % faster than 128 x 2.
+constexpr int kFlatBlock = 256;
+
+// The rows-by-columns shape reported for the default launch.
 void default_launch(int n, int *bx, int *by)
 {
     *bx = n < 256 ? n : 256;
@@ -106,17 +107,20 @@ void launch_step_kernels(lbmx_cavity *h, int64_t nsteps)
     const Geometry<T> geo = geometry<St>(view(h));
     const Rates<T> rates = make_rates<T>(&h->p, h->d);
     const int n = h->p.n;
-    dim3 block(h->bx, h->by, 1);
-    dim3 grid((n + h->bx - 1) / h->bx, (n + h->by - 1) / h->by, n);
+    const float inv_n = 1.0f / float(n);
+    const bool flat = h->bx == 0;  // the default launch
+    const dim3 block = flat ? dim3(kFlatBlock) : dim3(h->bx, h->by);
+    const dim3 grid = flat ? dim3((n * n + kFlatBlock - 1) / kFlatBlock, 1, n)
+                           : dim3((n + h->bx - 1) / h->bx, (n + h->by - 1) / h->by, n);
     Geometry<T> g = geo;
     for (int64_t s = 0; s < nsteps; ++s) {
         g.step = uint32_t(h->t);
-        if (h->off32)
-            hipLaunchKernelGGL((k_step<St, true, kForce>), grid, block, 0, h->stream,
-                               lattice(h, h->cur), lattice(h, 1 - h->cur), g, rates);
+        if (flat)
+            hipLaunchKernelGGL((k_step<St, kForce, true>), grid, block, 0, h->stream, lattice(h, h->cur),
+                               lattice(h, 1 - h->cur), g, rates, inv_n);
         else
-            hipLaunchKernelGGL((k_step<St, false, kForce>), grid, block, 0, h->stream,
-                               lattice(h, h->cur), lattice(h, 1 - h->cur), g, rates);
+            hipLaunchKernelGGL((k_step<St, kForce, false>), grid, block, 0, h->stream, lattice(h, h->cur),
+                               lattice(h, 1 - h->cur), g, rates, inv_n);
         h->cur = 1 - h->cur;
         h->t += 1;
     }
@@ -314,8 +318,7 @@ lbmx_status lbmx_create(const lbmx_params *p, void *dev_workspace, size_t ws_byt
     h->cur = 0;
     h->t = 0;
     h->failed = false;
-    h->off32 = double(L.lattice) <= 4294967295.0;
-    default_launch(p->n, &h->bx, &h->by);
+    h->bx = h->by = 0;
     if (stream) {
         h->stream = reinterpret_cast<hipStream_t>(stream);
         h->own_stream = false;
@@ -418,7 +421,7 @@ lbmx_status lbmx_save(lbmx_cavity *h, const char *path)
     hd.params_bytes = sizeof(lbmx_params);
     hd.p = canonical(h->p);
     hd.t = h->t;
-    hd.lattice_bytes = h->L.lattice;
+    hd.lattice_bytes = h->L.file;
     hd.slab_nodes = h->L.slab_nodes;
     File f(std::fopen(path, "wb"));
     if (!f.f)
@@ -426,11 +429,15 @@ lbmx_status lbmx_save(lbmx_cavity *h, const char *path)
     if (std::fwrite(&hd, sizeof hd, 1, f.f) != 1)
         return fail(LBMX_EIO, "writing the header of %s failed", path);
     HostBuf stage;
-    const size_t chunk = std::min<size_t>(h->L.lattice, kCkptChunk);
+    const size_t chunk = std::min<size_t>(h->L.file, kCkptChunk);
     HIP_TRY(hipHostMalloc(&stage.p, chunk, hipHostMallocDefault));
-    const char *lat = lattice(h, h->cur);
-    for (size_t off = 0; off < h->L.lattice; off += chunk) {
-        const size_t len = std::min(chunk, h->L.lattice - off);
+    // the file holds slabs of nodes: the spare lattice takes that layout
+    s = LBMX_DISPATCH(h->p.storage, launch_relayout, view(h), h->L, true);
+    if (s != LBMX_OK)
+        return s;
+    const char *lat = lattice(h, 1 - h->cur);
+    for (size_t off = 0; off < h->L.file; off += chunk) {
+        const size_t len = std::min(chunk, h->L.file - off);
         HIP_TRY(hipMemcpyAsync(stage.p, lat + off, len, hipMemcpyDeviceToHost, h->stream));
         HIP_TRY(hipStreamSynchronize(h->stream));
         if (std::fwrite(stage.p, 1, len, f.f) != len)
@@ -462,35 +469,39 @@ lbmx_status lbmx_load(lbmx_cavity *h, const char *path)
     const lbmx_params mine = canonical(h->p);
     if (std::memcmp(&hd.p, &mine, sizeof mine) != 0)
         return fail(LBMX_EINVAL, "%s was written for another parameter set", path);
-    if (hd.lattice_bytes != h->L.lattice || hd.slab_nodes != h->L.slab_nodes || hd.t < 0)
+    if (hd.lattice_bytes != h->L.file || hd.slab_nodes != h->L.slab_nodes || hd.t < 0)
         return fail(LBMX_EINVAL, "%s: lattice of %llu bytes in slabs of %llu nodes at t = %lld, "
                     "need %zu bytes in slabs of %zu", path, (unsigned long long)hd.lattice_bytes,
-                    (unsigned long long)hd.slab_nodes, (long long)hd.t, h->L.lattice, h->L.slab_nodes);
+                    (unsigned long long)hd.slab_nodes, (long long)hd.t, h->L.file, h->L.slab_nodes);
     if (std::fseek(f.f, 0, SEEK_END) != 0)
         return fail(LBMX_EIO, "cannot seek in %s", path);
     const long end = std::ftell(f.f);
-    if (end < 0 || (unsigned long)end != sizeof hd + h->L.lattice)
+    if (end < 0 || (unsigned long)end != sizeof hd + h->L.file)
         return fail(LBMX_EIO, "%s holds %ld bytes, a checkpoint of this cavity %zu", path, end,
-                    sizeof hd + h->L.lattice);
+                    sizeof hd + h->L.file);
     if (std::fseek(f.f, (long)sizeof hd, SEEK_SET) != 0)
         return fail(LBMX_EIO, "cannot seek in %s", path);
-    // Read into the spare lattice and switch to it only once every byte has
-    // arrived: a failed read leaves the current state as it was.
+    // Read into the spare lattice (in the file's slabs) and replace the current
+    // state only once every byte has arrived: a failed read leaves it as it was.
     HostBuf stage;
-    const size_t chunk = std::min<size_t>(h->L.lattice, kCkptChunk);
+    const size_t chunk = std::min<size_t>(h->L.file, kCkptChunk);
     HIP_TRY(hipHostMalloc(&stage.p, chunk, hipHostMallocDefault));
     char *lat = lattice(h, 1 - h->cur);
-    for (size_t off = 0; off < h->L.lattice; off += chunk) {
-        const size_t len = std::min(chunk, h->L.lattice - off);
+    for (size_t off = 0; off < h->L.file; off += chunk) {
+        const size_t len = std::min(chunk, h->L.file - off);
         if (std::fread(stage.p, 1, len, f.f) != len)
             return fail(LBMX_EIO, "reading %s failed at byte %zu", path, sizeof hd + off);
         HIP_TRY(hipMemcpyAsync(lat + off, stage.p, len, hipMemcpyHostToDevice, h->stream));
         HIP_TRY(hipStreamSynchronize(h->stream));
     }
-    h->cur = 1 - h->cur;
-    h->t = hd.t;
-    h->failed = false;
-    return LBMX_OK;
+    return reinit(h, [&]() -> lbmx_status {
+        lbmx_status r = LBMX_DISPATCH(h->p.storage, launch_relayout, view(h), h->L, false);
+        if (r != LBMX_OK)
+            return r;
+        HIP_TRY(hipStreamSynchronize(h->stream));
+        h->t = hd.t;
+        return LBMX_OK;
+    });
 }
 
 lbmx_status lbmx_init_fields(lbmx_cavity *h, const float *dev_u, const float *dev_v,
@@ -699,7 +710,7 @@ lbmx_status lbmx_set_launch(lbmx_cavity *h, int32_t bx, int32_t by)
     if (s != LBMX_OK)
         return s;
     if (bx == 0 && by == 0) {
-        default_launch(h->p.n, &h->bx, &h->by);
+        h->bx = h->by = 0;
         return LBMX_OK;
     }
     if (bx < 1 || by < 1 || (long)bx * by > 1024)
@@ -718,6 +729,8 @@ lbmx_status lbmx_get_launch(const lbmx_cavity *h, int32_t *bx, int32_t *by)
         return fail(LBMX_EINVAL, "NULL output");
     *bx = h->bx;
     *by = h->by;
+    if (h->bx == 0)
+        default_launch(h->p.n, bx, by);
     return LBMX_OK;
 }
 

@@ -1,6 +1,6 @@
 // pull.hip -- the lattice Boltzmann step's access pattern without arithmetic:
-// 26 population streams of a 256^3 FP32 lattice in the slab layout of
-// kernels.hpp (2048 nodes per slab), each node reading its 26 values from
+// 26 population streams of a 256^3 FP32 lattice in slabs of consecutive nodes
+// (2048 nodes per slab), each node reading its 26 values from
 // the upstream neighbours (x-shifted streams unaligned) and writing them at
 // itself with non-temporal stores, with 1, 2 or 4 consecutive nodes per
 // thread (4-, 8- and 16-byte accesses).  Indices are clamped into the
