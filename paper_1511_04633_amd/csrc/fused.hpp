@@ -1,22 +1,21 @@
 // fused.hpp -- two time steps of one cavity in one pass over memory.
+//
+// k_step is bound by HBM from about 100^3 on (26 populations in and out per
+// node and step, at the rate its access pattern reaches) and by its launch
+// below about 40^3.  The kernels here take a block of nodes through two steps
+// between one read and one write of the lattice: step A (time t) on the block
+// and a one-node halo, its post-collision populations into LDS, step B (time
+// t + 1) from LDS.  Halo nodes are updated by every block that needs them; each
+// node update is the same inlined code as k_step and the values in LDS are the
+// values k_step would have stored, so the result is k_step's bit for bit (the
+// storage must hold populations in the arithmetic type: FP32 and FP64).
 #pragma once
+
+#include <algorithm>
 
 #include "kernels.hpp"
 
 namespace lbmx {
-
-// Slots of the plane buffers in LDS: populations with e_z = -1 (one plane),
-// e_z = 0 (one plane), e_z = +1 (two planes, by the parity of z).
-__device__ __forceinline__ constexpr int slot19(int i, int par)
-{
-    constexpr int v[19] = {5, 6, 7, 8, 9, 14, 0, 10, 11, 12, 13, 15, 16, 1, 2, 17, 18, 3, 4};
-    return ez19(i) > 0 ? v[i] + 5 * par : v[i];
-}
-__device__ __forceinline__ constexpr int slot7(int i, int par)
-{
-    constexpr int v[7] = {1, 2, 3, 4, 5, 6, 0};
-    return i == 5 ? v[i] + par : v[i];
-}
 
 // Keep a node's values in registers at this point: nothing that computes them
 // moves past it, so that the compiler contracts multiplications and additions
@@ -32,22 +31,30 @@ __device__ __forceinline__ void pin(T (&f)[19], T (&g)[7])
         asm volatile("" : "+v"(g[i]));
 }
 
-template <class St, int kForce, int NT, int WEU>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WEU))) void
+// The work item of a block: workgroup i runs on XCD i mod 8, and each XCD takes
+// a contiguous eighth of the items, so that neighbouring tiles, whose halos
+// overlap, are read through one L2.
+__device__ __forceinline__ int xcd_item()
+{
+    const int b = int(blockIdx.x), nb = int(gridDim.x), xcd = b % 8;
+    return xcd * (nb / 8) + min(xcd, nb % 8) + b / 8;
+}
+
+// ------------------------------------------------------------- small grids
+// One tile of tx x ty x tz nodes per block; step A runs on the tile and its
+// halo (clipped at the walls) with one thread per node, at most NT of them.
+// Bound by launch and memory latency: 16^3 FP32 3.65 us per step with k_step,
+// 2.52 us here; 32^3 4.25 -> 3.0 us.
+template <class St, int kForce, int NT>
+__global__ __launch_bounds__(NT) void
 k_step2_tile(const char *__restrict__ src, char *__restrict__ dst, Geometry<typename St::T> geo,
              Rates<typename St::T> rates, int tx, int ty, int tz, int ntx, int nty)
 {
     using T = typename St::T;
-    using SF = typename St::F;
-    using SG = typename St::G;
-    __shared__ typename Codec<SF>::Raw lf[19 * NT];
-    __shared__ typename Codec<SG>::Raw lg[7 * NT];
+    __shared__ T lf[19 * NT], lg[7 * NT];
     const int n = geo.n, tid = threadIdx.x;
-    int bid = blockIdx.x;
-    const int nb = gridDim.x;
-    if (nb % 8 == 0)
-        bid = (bid % 8) * (nb / 8) + bid / 8;
-    const int bz = bid / (ntx * nty), bt = bid - bz * (ntx * nty), by = bt / ntx, bx = bt - by * ntx;
+    const int item = xcd_item();
+    const int bz = item / (ntx * nty), bt = item - bz * (ntx * nty), by = bt / ntx, bx = bt - by * ntx;
     const int x0 = bx * tx, y0 = by * ty, z0 = bz * tz;
     const int xl = max(x0 - 1, 0), yl = max(y0 - 1, 0), zl = max(z0 - 1, 0);
     const int hw = min(x0 + tx + 1, n) - xl, hh = min(y0 + ty + 1, n) - yl, hd = min(z0 + tz + 1, n) - zl;
@@ -65,17 +72,10 @@ k_step2_tile(const char *__restrict__ src, char *__restrict__ dst, Geometry<type
             pin(f, g);
 #pragma unroll
             for (int i = 0; i < 19; ++i)
-                lf[i * NT + tid] = Codec<SF>::enc(f[i], T(inv_w19(i)));
-            if constexpr (std::is_same<SG, Fix16>::value) {
-                const RoundBits rb(uint32_t(x) + uint32_t(n) * (uint32_t(y) + uint32_t(n) * uint32_t(z)), geo.step);
+                lf[i * NT + tid] = f[i];
 #pragma unroll
-                for (int i = 0; i < 7; ++i)
-                    lg[i * NT + tid] = Codec<SG>::enc_r(g[i], T(inv_w7(i)) * geo.inv_escale, rb.u16(i));
-            } else {
-#pragma unroll
-                for (int i = 0; i < 7; ++i)
-                    lg[i * NT + tid] = Codec<SG>::enc(g[i], T(inv_w7(i)));
-            }
+            for (int i = 0; i < 7; ++i)
+                lg[i * NT + tid] = g[i];
         }
     }
     __syncthreads();
@@ -86,13 +86,13 @@ k_step2_tile(const char *__restrict__ src, char *__restrict__ dst, Geometry<type
     const int x = x0 + cx, y = y0 + cy, z = z0 + cz;
     Site s = site_in_plane<St>(n, x, y, z);
     const int q0 = (x - xl) + hw * ((y - yl) + hh * (z - zl));
-    RawPops<St> raw;
-    auto at = [&](int i) {
+    auto at = [&](int i) {  // the slot of population i's source, as in load_pops
         const int ex = ex19(i), ey = ey19(i), ez = ez19(i);
         const bool out = (ex > 0 && s.xl) || (ex < 0 && s.xh) || (ey > 0 && s.yl) || (ey < 0 && s.yh) ||
                          (ez > 0 && s.zl) || (ez < 0 && s.zh);
         return out ? opp19(i) * NT + q0 : i * NT + q0 - ex - hw * (ey + hh * ez);
     };
+    RawPops<St> raw;
 #pragma unroll
     for (int i = 0; i < 19; ++i)
         raw.f[i] = lf[at(i)];
@@ -108,159 +108,231 @@ k_step2_tile(const char *__restrict__ src, char *__restrict__ dst, Geometry<type
             uint32_t(x) + uint32_t(n) * (uint32_t(y) + uint32_t(n) * uint32_t(z)), geo.step + 1u, geo, f, g);
 }
 
-template <class St, int kForce, int TX, int TY, int NW, int WEU, bool PF>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WEU))) void
-k_step2(const char *__restrict__ src, char *__restrict__ dst, Geometry<typename St::T> geo,
-        Rates<typename St::T> rates, int ntx, int nty, int zc)
+// ------------------------------------------------------------- large grids
+// A block marches through planes z0 - 1 .. z1 of a column of TX x TY nodes: in
+// one turn it runs step A on plane z (TX + 2 by TY + 2 nodes, one thread each)
+// and step B on plane z - 1 (TX by TY).  LDS holds what step B still needs:
+// the populations with e_z = -1 of plane z, those with e_z = 0 of plane z - 1
+// and those with e_z = +1 of planes z - 2 and z - 1 (by the parity of z): 32
+// values per node of the halo rectangle instead of 3 x 26, so that 990 FP32
+// nodes fit one CU's 160 KB.  A turn: step A in registers, its e_z = -1 values
+// to LDS, barrier, step B gathers, barrier, the other values to LDS over those
+// just read, step B collides and stores.  The next plane's populations are
+// loaded before step B's collision and waited for after it and before its
+// stores, so that their latency overlaps the arithmetic and no load waits
+// behind a store.
+//
+// Walls: step A writes a population that step B would pull from outside (the
+// reflected opposite one, with the wall temperature applied) into the slot in
+// which step B looks for it; step B has no wall conditions.
+//
+// Bound by HBM and by the memory phases that the barriers keep apart from the
+// arithmetic (vector unit busy about half of the time; 256^3 FP32 reads 1.89 GB
+// for 1.74 GB of lattice).  256^3: FP32 581 -> 382 us per step, FP64 1179 ->
+// 910 us; 128^3 FP32 74 -> 64 us.  64 x 13 tiles rather than 32 x 28 or
+// 32 x 13: the rows' end columns cost a memory line each (FP32 256^3 with an
+// earlier alignment: 405, 477 and 430 us); loading the next plane before step A
+// instead spills registers.
+__device__ __forceinline__ constexpr int slot19(int i)
+{
+    constexpr int v[19] = {5, 6, 7, 8, 9, 14, 0, 10, 11, 12, 13, 15, 16, 1, 2, 17, 18, 3, 4};
+    return v[i];  // + 5 for e_z = +1 and odd planes
+}
+__device__ __forceinline__ constexpr int slot7(int i)
+{
+    constexpr int v[7] = {1, 2, 3, 4, 5, 6, 0};
+    return v[i];  // + 1 for e_z = +1 and odd planes
+}
+
+template <class St, int TX, int TY>
+struct MarchTile {
+    static constexpr int HW = TX + 2, HH = TY + 2, NH = HW * HH;
+    static constexpr int NS = NH + 1;                  // slot NH takes the idle lanes' writes
+    static constexpr int kWaves = (NH + 63) / 64;      // step A
+    static constexpr int kWavesB = (TX * TY + 63) / 64;
+    typename St::T f[24 * NS], g[8 * NS];
+};
+
+template <class St, int kForce, int TX, int TY, bool kEdge>
+__device__ __forceinline__ void march2(const char *__restrict__ src, char *__restrict__ dst,
+                                       const Geometry<typename St::T> &geo,
+                                       const Rates<typename St::T> &rates, int x0, int y0, int z0, int z1,
+                                       MarchTile<St, TX, TY> &lds)
 {
     using T = typename St::T;
-    using SF = typename St::F;
-    using SG = typename St::G;
-    using RF = typename Codec<SF>::Raw;
-    static_assert(std::is_same<typename Codec<SG>::Raw, T>::value, "energy held in T");
-    constexpr int HW = TX + 2, HH = TY + 2, NH = HW * HH, NS = NH + 1;  // slot NH takes the idle lanes' writes
-    constexpr int WB = (TX * TY + 63) / 64;
-    static_assert(NW * 64 >= NH, "");
-    __shared__ RF lf[24 * NS];
-    __shared__ T lg[8 * NS];
-    const int n = geo.n;
-    int bid = blockIdx.x;
-    const int nb = gridDim.x;
-    if (nb % 8 == 0)
-        bid = (bid % 8) * (nb / 8) + bid / 8;
-    const int bt = bid % (ntx * nty), ck = bid / (ntx * nty);
-    const int x0 = (bt % ntx) * TX, y0 = (bt / ntx) * TY;
-    const int z0 = ck * zc, z1 = min(z0 + zc, n);
-    const int za = max(z0 - 1, 0);
+    using Tile = MarchTile<St, TX, TY>;
+    constexpr int HW = Tile::HW, HH = Tile::HH, NH = Tile::NH, NS = Tile::NS;
+    const int n = geo.n, tid = threadIdx.x;
     const size_t plane = Plane<St>(uint32_t(n)).bytes;
-    const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
-
-    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // step A: node (x, y) of the halo rectangle; lanes outside the cavity
+    // repeat the nearest node and write to slot NH
     const int hx = tid % HW, hy = tid / HW;
     const int x = x0 - 1 + hx, y = y0 - 1 + hy;
     const bool inA = tid < NH && x >= 0 && x < n && y >= 0 && y < n;
     const int xc = min(max(x, 0), n - 1), yc = min(max(y, 0), n - 1);
     const int pw = inA ? tid : NH;
-    const bool wall_xy = x0 == 0 || x0 + TX >= n || y0 == 0 || y0 + TY >= n;  // uniform
+    // step B: node (x0 + bx, y0 + by)
     const int bx = tid % TX, by = tid / TX;
     const bool inB = tid < TX * TY && x0 + bx < n && y0 + by < n;
     const int pb = inB ? (by + 1) * HW + bx + 1 : HW + 1;
     const Site sB = site_in_plane<St>(n, x0 + bx, y0 + by, 1);
 
-    auto march = [&](auto edge) {
-        constexpr bool kEdge = decltype(edge)::value;
-        Site s = site_in_plane<St>(n, xc, yc, 1);
-        RawPops<St> raw;
-        auto load = [&](int z) {
-            s.zl = z == 0, s.zh = z == n - 1;
-            load_pops<St, false, kEdge>(src + plane * z, n, s, raw);
-        };
-        auto touch = [&]() {
+    Site s = site_in_plane<St>(n, xc, yc, 1);
+    RawPops<St> raw;
+    auto load = [&](int z) {
+        s.zl = z == 0, s.zh = z == n - 1;
+        load_pops<St, false, kEdge>(src + plane * z, n, s, raw);
+    };
+    const int za = max(z0 - 1, 0), zlast = min(z1, n - 1);
+    load(za);
+    pin(raw.f, raw.g);
+    for (int z = za; z <= z1; ++z) {
+        T f[19], g[7];
+        s.zl = z == 0, s.zh = z == n - 1;
+        decode_pops<St, false, kEdge>(raw, geo, s, yc, f, g);
+        collide<T, kForce>(f, g, rates);
+        pin(f, g);
+        if (z < n) {
 #pragma unroll
             for (int i = 0; i < 19; ++i)
-                asm volatile("" : "+v"(raw.f[i]));
+                if (ez19(i) < 0)
+                    lds.f[slot19(i) * NS + pw] = f[i];
+            lds.g[slot7(6) * NS + pw] = g[6];
+        }
+        const int par = z & 1;
+        __syncthreads();
+        T f2[19], g2[7];
+        if (wave < Tile::kWavesB) {
+#pragma unroll
+            for (int i = 0; i < 19; ++i)
+                f2[i] = lds.f[slot19(i) * NS + (ez19(i) > 0 ? 5 * NS * par : 0) + pb - ex19(i) - HW * ey19(i)];
 #pragma unroll
             for (int i = 0; i < 7; ++i)
-                asm volatile("" : "+v"(raw.g[i]));
-        };
-        if (PF)
-            load(za);
-        if (PF)
-            touch();
-        for (int z = za; z <= z1; ++z) {
-            T f[19], g[7];
-            if (!PF)
-                load(min(z, n - 1));
-            s.zl = z == 0, s.zh = z == n - 1;
-            decode_pops<St, false, kEdge>(raw, geo, s, yc, f, g);
-            collide<T, kForce>(f, g, rates);
-            pin(f, g);
-            if (z < n) {
+                g2[i] = lds.g[slot7(i) * NS + (ez19(i) > 0 ? NS * par : 0) + pb - ex19(i) - HW * ey19(i)];
+        }
+        __syncthreads();
+        if (z < n) {
 #pragma unroll
-                for (int i = 0; i < 19; ++i)
-                    if (ez19(i) < 0)
-                        lf[slot19(i, 0) * NS + pw] = Codec<SF>::enc(f[i], T(inv_w19(i)));
-                lg[slot7(6, 0) * NS + pw] = g[6];
-            }
-            const int par = z & 1;
-            __syncthreads();
-            T f2[19], g2[7];
-            if (wave < WB) {
+            for (int i = 0; i < 19; ++i)
+                if (ez19(i) >= 0)
+                    lds.f[slot19(i) * NS + (ez19(i) > 0 ? 5 * NS * par : 0) + pw] = f[i];
 #pragma unroll
-            for (int i = 0; i < 19; ++i) {
-                const int q = pb - ex19(i) - HW * ey19(i);
-                f2[i] = Codec<SF>::dec(lf[slot19(i, 0) * NS + (ez19(i) > 0 ? 5 * NS * par : 0) + q], T(w19(i)));
-            }
+            for (int i = 0; i < 6; ++i)
+                lds.g[slot7(i) * NS + (ez19(i) > 0 ? NS * par : 0) + pw] = g[i];
+            if (kEdge || z == 0 || z == n - 1) {
+                const int pm = par ^ 1;  // parity of plane z - 1
+                const T th_lin = theta_linear(geo, yc);
+                const bool xd = x_wall_dirichlet(geo.wall_type), zd = z_wall_dirichlet(geo.wall_type);
+                const T two_w = T(0.25);
 #pragma unroll
-            for (int i = 0; i < 7; ++i) {
-                const int q = pb - ex19(i) - HW * ey19(i);
-                g2[i] = lg[slot7(i, 0) * NS + (i == 5 ? NS * par : 0) + q];
-            }
-            }
-            __syncthreads();
-            if (z < n) {
-#pragma unroll
-                for (int i = 0; i < 19; ++i)
-                    if (ez19(i) >= 0)
-                        lf[slot19(i, 0) * NS + (ez19(i) > 0 ? 5 * NS * par : 0) + pw] =
-                            Codec<SF>::enc(f[i], T(inv_w19(i)));
-#pragma unroll
-                for (int i = 0; i < 6; ++i)
-                    lg[slot7(i, 0) * NS + (i == 5 ? NS * par : 0) + pw] = g[i];
-                if ((kEdge || z == 0 || z == n - 1)) {
-                    // reflected populations, written where step B will look for them
-                    const int pm = par ^ 1;  // parity of plane z - 1
-                    const T th_lin = theta_linear(geo, yc);
-                    const bool xd = x_wall_dirichlet(geo.wall_type), zd = z_wall_dirichlet(geo.wall_type);
-                    const T two_w = T(0.25);
-#pragma unroll
-                    for (int i = 1; i < 19; ++i) {
-                        const int ex = ex19(i), ey = ey19(i), ez = ez19(i);
-                        const bool out = (ex > 0 && x == 0) || (ex < 0 && x == n - 1) || (ey > 0 && y == 0) ||
-                                         (ey < 0 && y == n - 1) || (ez > 0 && z == 0) || (ez < 0 && z == n - 1);
-                        const bool in_tile = !((ex > 0 && hx == 0) || (ex < 0 && hx == HW - 1) ||
-                                               (ey > 0 && hy == 0) || (ey < 0 && hy == HH - 1));
-                        if (inA && out && in_tile)
-                            lf[slot19(i, 0) * NS + (ez > 0 ? 5 * NS * pm : 0) + tid - ex - HW * ey] =
-                                Codec<SF>::enc(f[opp19(i)], T(inv_w19(opp19(i))));
-                    }
-#pragma unroll
-                    for (int i = 1; i < 7; ++i) {
-                        const int ex = ex19(i), ey = ey19(i), ez = ez19(i);
-                        const bool out = (ex > 0 && x == 0) || (ex < 0 && x == n - 1) || (ey > 0 && y == 0) ||
-                                         (ey < 0 && y == n - 1) || (ez > 0 && z == 0) || (ez < 0 && z == n - 1);
-                        const bool in_tile = !((ex > 0 && hx == 0) || (ex < 0 && hx == HW - 1) ||
-                                               (ey > 0 && hy == 0) || (ey < 0 && hy == HH - 1));
-                        if (inA && out && in_tile) {
-                            const T v = g[opp19(i)];
-                            T r;
-                            if (ey != 0)
-                                r = two_w * (ey > 0 ? geo.theta_hot : geo.theta_cold) - v;
-                            else
-                                r = (ex != 0 ? xd : zd) ? two_w * th_lin - v : v;
-                            lg[slot7(i, 0) * NS + (i == 5 ? NS * pm : 0) + tid - ex - HW * ey] = r;
-                        }
+                for (int i = 1; i < 19; ++i) {
+                    const int ex = ex19(i), ey = ey19(i), ez = ez19(i);
+                    const bool out = (ex > 0 && x == 0) || (ex < 0 && x == n - 1) || (ey > 0 && y == 0) ||
+                                     (ey < 0 && y == n - 1) || (ez > 0 && z == 0) || (ez < 0 && z == n - 1);
+                    const bool in_tile = !((ex > 0 && hx == 0) || (ex < 0 && hx == HW - 1) ||
+                                           (ey > 0 && hy == 0) || (ey < 0 && hy == HH - 1));
+                    if (!(inA && out && in_tile))
+                        continue;
+                    const int q = tid - ex - HW * ey;
+                    lds.f[slot19(i) * NS + (ez > 0 ? 5 * NS * pm : 0) + q] = f[opp19(i)];
+                    if (i < 7) {
+                        const T v = g[opp19(i)];
+                        T r;
+                        if (ey != 0)  // hot wall y = 0, cold wall y = H (Eqs. 6, 7)
+                            r = two_w * (ey > 0 ? geo.theta_hot : geo.theta_cold) - v;
+                        else
+                            r = (ex != 0 ? xd : zd) ? two_w * th_lin - v : v;
+                        lds.g[slot7(i) * NS + (ez > 0 ? NS * pm : 0) + q] = r;
                     }
                 }
             }
-            if (PF)
-                load(min(z + 1, n - 1));
-            if (wave < WB) {
-                collide<T, kForce>(f2, g2, rates);
-                pin(f2, g2);
-            }
-            if (PF)
-                touch();
-            if (z > z0 && inB)
-                put<St>(dst + plane * (z - 1), sB,
-                        uint32_t(x0 + bx) + uint32_t(n) * (uint32_t(y0 + by) + uint32_t(n) * uint32_t(z - 1)),
-                        geo.step + 1u, geo, f2, g2);
         }
-    };
-    if (wall_xy)
-        march(std::true_type{});
+        load(min(z + 1, zlast));
+        if (wave < Tile::kWavesB) {
+            collide<T, kForce>(f2, g2, rates);
+            pin(f2, g2);
+        }
+        pin(raw.f, raw.g);  // the loads have landed: the stores below are waited for by nothing
+        if (z > z0 && inB)
+            put<St>(dst + plane * (z - 1), sB,
+                    uint32_t(x0 + bx) + uint32_t(n) * (uint32_t(y0 + by) + uint32_t(n) * uint32_t(z - 1)),
+                    geo.step + 1u, geo, f2, g2);
+    }
+}
+
+// Waves per SIMD that the registers must allow: 4 in FP32 (128 registers, 16
+// waves per CU: one 64 x 13 block or two 32 x 13), 2 in FP64.
+template <class St>
+constexpr int march_waves() { return sizeof(typename St::T) == 8 ? 2 : 4; }
+
+// Blocks: ntx x nty columns by chunks of zc planes (two more are read).
+template <class St, int kForce, int TX, int TY>
+__global__ __launch_bounds__(64 * (MarchTile<St, TX, TY>::kWaves))
+    __attribute__((amdgpu_waves_per_eu(march_waves<St>()))) void
+k_step2_march(const char *__restrict__ src, char *__restrict__ dst, Geometry<typename St::T> geo,
+              Rates<typename St::T> rates, int ntx, int nty, int zc)
+{
+    __shared__ MarchTile<St, TX, TY> lds;
+    const int item = xcd_item();
+    const int bt = item % (ntx * nty), ck = item / (ntx * nty);
+    const int x0 = (bt % ntx) * TX, y0 = (bt / ntx) * TY, z0 = ck * zc, z1 = min(z0 + zc, geo.n);
+    // kEdge: a wall node lies in the tile or its halo
+    if (x0 == 0 || x0 + TX >= geo.n - 1 || y0 == 0 || y0 + TY >= geo.n - 1)
+        march2<St, kForce, TX, TY, true>(src, dst, geo, rates, x0, y0, z0, z1, lds);
     else
-        march(std::false_type{});
+        march2<St, kForce, TX, TY, false>(src, dst, geo, rates, x0, y0, z0, z1, lds);
+}
+
+// ------------------------------------------------------------------- rule
+// How two steps of an n^3 cavity are taken (kSingle: by k_step twice).
+struct Step2Plan {
+    enum Kind { kSingle, kTile, kWide, kNarrow } kind;
+    int tx, ty, tz, ntx, nty;  // tz: planes per tile or chunk
+    unsigned blocks;
+};
+
+// Tiles while a launch costs more than the halo's arithmetic (measured us per
+// step, k_step -> tiles: FP32 16^3 3.65 -> 2.6, 32^3 4.2 -> 3.1, 40^3 5.1 ->
+// 4.7, 44^3 5.7 -> 5.8; FP64 16^3 4.5 -> 3.3, 32^3 5.0 -> 4.1, 36^3 5.8 ->
+// 7.2).  Above, the shape and chunk length that take the fewest turns, a partly
+// filled round of blocks counting as a full one: a turn of the 64 x 13 tile
+// took 8.6 to 9.9 us over 96^3 .. 320^3, of two 32 x 13 blocks on one CU 9.6 to
+// 10.5 us (FP64, one block: 9.0 to 11.2 us); where rows do not start on 64-byte
+// boundaries 10.0 to 11.6, 10.8 to 17.8 and 10.9 to 14.3 us.  k_step, at the
+// memory rate it reaches, where that is shorter (FP32: 96^3 33.3 us against
+// 32.7, 136^3 90 against 101; 144^3 106 against 100, 192^3 242 against 183).
+template <typename T>
+inline Step2Plan plan_step2(int n, int cus)
+{
+    constexpr bool f64 = sizeof(T) == 8;
+    auto up = [](int a, int b) { return (a + b - 1) / b; };
+    auto make = [&](Step2Plan::Kind k, int tx, int ty, int tz) {
+        const int ntx = up(n, tx), nty = up(n, ty);
+        return Step2Plan{k, tx, ty, tz, ntx, nty, unsigned(ntx * nty * up(n, tz))};
+    };
+    if (n <= 32)
+        return make(Step2Plan::kTile, n, 2, 2);
+    if (!f64 && n <= 40)
+        return make(Step2Plan::kTile, up(n, 2), 3, 2);
+    const double single = 2.0 + double(n) * n * n * (f64 ? 416.0 / 5.65e6 : 208.0 / 5.95e6);
+    Step2Plan best = make(Step2Plan::kSingle, 1, 1, 1);
+    double best_us = 0.98 * single;
+    const bool aligned = n % (f64 ? 8 : 16) == 0;
+    for (int k = f64 ? 1 : 0; k < 2; ++k) {
+        const int tx = k == 0 ? 64 : 32, ty = 13, slots = (k == 1 && !f64 ? 2 : 1) * cus;
+        const double turn = f64 ? (aligned ? 10.2 : 13.3) : k == 0 ? (aligned ? 9.2 : 10.7) : (aligned ? 10.2 : 15.0);
+        const int tiles = up(n, tx) * up(n, ty);
+        for (int nz = 1; nz <= n / 4; ++nz) {
+            const int zc = up(n, nz);
+            const double us = 0.5 * turn * up(tiles * up(n, zc), slots) * (zc + 2);
+            if (us < best_us) {
+                best_us = us;
+                best = make(k == 0 ? Step2Plan::kWide : Step2Plan::kNarrow, tx, ty, zc);
+            }
+        }
+    }
+    return best;
 }
 
 }  // namespace lbmx

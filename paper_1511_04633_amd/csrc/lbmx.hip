@@ -17,6 +17,7 @@
 #include <new>
 #include <string>
 
+#include "fused.hpp"
 #include "host.hpp"
 
 using namespace lbmx;
@@ -67,6 +68,7 @@ struct lbmx_cavity {
     int cur;
     int64_t t;
     int bx, by;  // block of the step kernel; 0, 0: the default launch
+    int cus;     // compute units of the device
     // The state is unusable: a Nu evaluation found non-finite values, or a
     // device call failed while the state was being changed.  Stepping,
     // saving and using the cavity as a source return LBMX_ESTATE until an
@@ -100,6 +102,40 @@ void default_launch(int n, int *bx, int *by)
     *by = b;
 }
 
+// Pairs of steps by the kernels that take two steps per pass (fused.hpp), for
+// the storages that hold populations in the arithmetic type; returns the steps
+// taken (0 where k_step is the better one).  Guo's forcing stays with k_step:
+// its registers exceed the marching kernel's.
+template <class St, int kForce>
+int64_t launch_step_pairs(lbmx_cavity *h, int64_t nsteps, Geometry<typename St::T> g,
+                          const Rates<typename St::T> &rates)
+{
+    using T = typename St::T;
+    const Step2Plan p = plan_step2<T>(h->p.n, h->cus);
+    if (p.kind == Step2Plan::kSingle)
+        return 0;
+    auto run = [&](auto kernel, int threads, auto... args) {
+        for (int64_t s = 0; s + 2 <= nsteps; s += 2) {
+            g.step = uint32_t(h->t);
+            hipLaunchKernelGGL(kernel, dim3(p.blocks), dim3(threads), 0, h->stream,
+                               (const char *)lattice(h, h->cur), lattice(h, 1 - h->cur), g, rates, args...);
+            h->cur = 1 - h->cur;
+            h->t += 2;
+        }
+    };
+    if (p.kind == Step2Plan::kTile) {
+        if (h->p.n <= 16)
+            run(k_step2_tile<St, kForce, 256>, 256, p.tx, p.ty, p.tz, p.ntx, p.nty);
+        else
+            run(k_step2_tile<St, kForce, 512>, 512, p.tx, p.ty, p.tz, p.ntx, p.nty);
+    } else if (p.kind == Step2Plan::kNarrow) {
+        run(k_step2_march<St, kForce, 32, 13>, 64 * MarchTile<St, 32, 13>::kWaves, p.ntx, p.nty, p.tz);
+    } else if constexpr (sizeof(T) == 4) {
+        run(k_step2_march<St, kForce, 64, 13>, 64 * MarchTile<St, 64, 13>::kWaves, p.ntx, p.nty, p.tz);
+    }
+    return nsteps / 2 * 2;
+}
+
 template <class St, int kForce>
 void launch_step_kernels(lbmx_cavity *h, int64_t nsteps)
 {
@@ -107,6 +143,11 @@ void launch_step_kernels(lbmx_cavity *h, int64_t nsteps)
     const Geometry<T> geo = geometry<St>(view(h));
     const Rates<T> rates = make_rates<T>(&h->p, h->d);
     const int n = h->p.n;
+    if constexpr (kForce != LBMX_FORCE_GUO && (std::is_same<St, Store<float, float>>::value ||
+                                               std::is_same<St, Store<double, double>>::value)) {
+        if (h->bx == 0 && nsteps >= 2)
+            nsteps -= launch_step_pairs<St, kForce>(h, nsteps, geo, rates);
+    }
     const float inv_n = 1.0f / float(n);
     const bool flat = h->bx == 0;  // the default launch
     const dim3 block = flat ? dim3(kFlatBlock) : dim3(h->bx, h->by);
@@ -319,6 +360,10 @@ lbmx_status lbmx_create(const lbmx_params *p, void *dev_workspace, size_t ws_byt
     h->t = 0;
     h->failed = false;
     h->bx = h->by = 0;
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&h->cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || h->cus < 1)
+        h->cus = 256;
     if (stream) {
         h->stream = reinterpret_cast<hipStream_t>(stream);
         h->own_stream = false;
