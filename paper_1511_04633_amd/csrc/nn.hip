@@ -10,10 +10,8 @@
 // Convolution = implicit GEMM on the matrix cores: out[p][co] =
 // sum_{tap, ci} W[co][tap][ci] in[p + off(tap)][ci] with M = co, N = voxels,
 // K = (tap, ci), FP32 accumulation.  Both convolution kernels run on
-// v_mfma_f32_16x16x32_bf16 (gfx950) over bricks of 16 x 4 x 4 voxels staged
-// in LDS, so that MFMA operands are aligned 16-byte LDS reads (the weight
-// gradient's x-shifted taps take them one word on or one element on, by a
-// byte permute) and each staged element serves all 27 taps; blocks walk the
+// v_mfma_f32_16x16x32_bf16 (gfx950) over bricks of voxels staged in LDS (forward:
+// 16 x 4 x 4), so that each staged element serves all 27 taps; blocks walk the
 // bricks in an XCD-aware order (brick_walk):
 //   - forward (and the data gradient, the same convolution of the output
 //     gradient with the flipped, transposed weights W'[ci][26-tap][co] =
@@ -24,12 +22,11 @@
 //     a decoder's upsampled-and-concatenated tensor read in place; details
 //     at k_conv_fwd;
 //   - weight gradient: a block owns one (output-channel tile, input-channel
-//     tile) pair, walks the bricks, stages output gradient and input halo
-//     transposed to [channel][voxel] (one copy of the input); K = 32 covers
-//     two brick rows of voxels; two LDS reads feed the three taps that differ
-//     only in dx; the bias gradient is one more MFMA against ones; the
-//     block's sums are added to the global gradient atomically; details at
-//     k_conv_wgrad.
+//     tile) pair, walks bricks of 16 x 8 x 8 voxels and brings output gradient
+//     and input halo into LDS as they lie in memory; transposing LDS reads give
+//     the operands, K = 32 covering two rows of voxels; the bias gradient is one
+//     more MFMA against ones; the block's sums are added to the global gradient
+//     atomically; details at k_conv_wgrad.
 // MFMA operand layout of v_mfma_f32_16x16x32_bf16 (checked on the device):
 // lane l holds A[l%16][8(l/16) .. 8(l/16)+7] and B[8(l/16) .. 8(l/16)+7][l%16]
 // and gets D[4(l/16)+j][l%16], j < 4.
@@ -599,260 +596,233 @@ __global__ __launch_bounds__(256) void k_conv_flip_many(const bf *__restrict__ w
 
 // gw[co][tap][ci] += sum_p gout[p][co] in[p + off(tap)][ci], gb[co] += sum_p gout[p][co].
 //
-// A block owns one (co tile, ci tile) pair (blockIdx.y) and walks bricks of
-// 16 x 4 x 4 voxels (in the order of brick_walk), all 27 taps per brick, so
-// each operand is read from global memory once per brick instead of once
-// per tap.  The reduction runs over voxels, so both MFMA operands need 8
-// consecutive voxels of one channel: per brick the block stages in LDS,
-// transposed to [channel][voxel]:
-//   gT: the brick's gout tile, 16 channels x 256 voxels;
-//   iT: the input tile on the brick plus a one-voxel halo, 36 halo rows
-//       (y, z) of 18 voxels (x0 - 1 .. x0 + 16) per channel, each row
-//       starting on a 16-byte boundary (24-element stride).
-// The transpose packs two x-neighbours of one channel into each 32-bit LDS
-// word, and consecutive lanes write consecutive words.
-// The products run on v_mfma_f32_16x16x32_bf16 with K = 32 voxels, two brick
-// rows (lanes 0-31 row 2q, lanes 32-63 row 2q + 1, 8 voxels per lane).  The
-// 27 taps form 9 groups (dy, dz) of three x offsets: a lane reads the 10
-// halo voxels from x = 8 h - 1 on (an aligned 16-byte read and the 32-bit
-// word after it) and takes the operand of dx = -1 as the 16-byte read, dx = +1
-// as words 1-4 and dx = 0 as those words shifted by one element
-// (v_perm_b32), so two LDS reads feed three products.  Wave w runs groups w and w + 4 (wave 0 also group 8),
-// reusing the gout operand across its taps; wave 3 accumulates the bias
-// gradient as a product with a register operand of ones.  Each lane's
-// operand addresses are computed once per launch, a row pair step is an
-// immediate offset, so the inner loop is LDS reads, permutes and MFMAs.
-// Partial sums stay in registers across the block's bricks and are added to
-// gw / gb atomically at the end.  Voxel and element indices are 32-bit (the
-// host checks B D H W C < 2^31 and the plane extents).
-constexpr int WB_X = 16, WB_Y = 4, WB_Z = 4, WB_V = WB_X * WB_Y * WB_Z;
-constexpr int WB_HROWS = (WB_Y + 2) * (WB_Z + 2);   // halo rows (y, z)
-constexpr int WB_RW = 24;                           // LDS row: 18 halo voxels, 16-byte aligned stride
-constexpr int WB_PLANE = WB_HROWS * WB_RW + 8;      // one input channel; the 8 padding elements put the
-                                                    // channels of one 8-lane phase of a 16-byte read on
-                                                    // distinct banks
-constexpr int WB_GROW = WB_V + 8;                   // one channel of the gout tile
-constexpr int WB_XP = (WB_X + 2) / 2;               // voxel pairs per halo row
-constexpr int WB_ITASKS = WB_HROWS * WB_XP * 2;     // (halo row, x pair, channel half) = 648
-constexpr int WB_ITERS = (WB_ITASKS + 255) / 256;
-constexpr long long WG_MIN_BRICKS = 3;              // bricks per block, at least (where there are)
+// A block owns one (co tile, ci tile) pair (blockIdx.y) and walks bricks of 16 x
+// 8 x 8 voxels in the order of brick_walk.  Per brick it brings the gout tile
+// (1024 voxels of 16 channels) and the input tile with a one-voxel halo (18 x 10
+// x 10 voxels) from memory straight into LDS, channel-last as they lie in
+// memory (buffer loads to LDS; voxels outside the volume are out of the
+// buffer's range and arrive as zeros).  Four teams of three waves take the
+// brick's 16 x 4 x 4 quarters.  The reduction runs over voxels, so both MFMA operands need several voxels of one channel
+// per lane: ds_read_b64_tr_b16 transposes on the way out of LDS (lane layout
+// checked on the device: 16 voxels of 16 channels, 512 consecutive bytes read
+// at lane * 8, give lane l channel l % 16 of voxels 4 (l / 16) .. + 3).  K = 32
+// of v_mfma_f32_16x16x32_bf16 is two rows of 16 voxels, one read each, so any
+// tap's operand is two reads at lane * 8 plus a constant, and the inner loop is
+// LDS reads and MFMAs only.
+// Wave dx of a team accumulates the 9 taps of its x offset: it holds the row
+// pairs of gout in registers and reads the 5 row pairs (Y, Y + 1) of each halo
+// plane once; a row pair serves every (dy, dz) it lies at: 72 products for 76
+// reads.  Wave 0 also accumulates the bias gradient against ones.  At the end
+// the teams' sums meet in LDS and the block adds them to gw / gb atomically,
+// each block from another place on.
+// Bound by the chain load, wait, products of a brick (one block's 90 KB tile per
+// CU) and by the 256 blocks' atomic adds to the same elements (6 us at 64^3).
+// Batch 4: 64^3 16 -> 16 51.5 us (bricks transposed through registers, two
+// 4-wave blocks per CU) -> 31.1, 48 -> 16 86 -> 53, 32^3 96 -> 32 48.8 -> 34.9,
+// 16^3 64 -> 64 19.3 -> 14.6, 8^3 64 -> 96 11.9 -> 9.3.  Two blocks of half the
+// brick per CU overlap loads and products but add twice the atomics: 42 us.
+// Element indices are 32-bit (the host checks B D H W C < 2^31 and the plane
+// extents).
+constexpr int WB_X = 16, WB_Y = 8, WB_Z = 8, WB_V = WB_X * WB_Y * WB_Z;
+constexpr int WB_HX = WB_X + 2, WB_HY = WB_Y + 2, WB_HZ = WB_Z + 2;
+constexpr int WB_HV = WB_HX * WB_HY * WB_HZ;        // 1800 halo voxels
+constexpr int WB_QY = 4, WB_QZ = 4;                 // a team's part of the brick: 16 x 4 x 4
+constexpr int WB_TEAMS = (WB_Y / WB_QY) * (WB_Z / WB_QZ), WB_WAVES = 3 * WB_TEAMS;
+constexpr int WB_ILOADS = (2 * WB_HV + 63) / 64;    // wave loads of 64 16-byte pieces: input tile
+constexpr int WB_GLOADS = 2 * WB_V / 64;            // and gout tile
+constexpr int WB_IITERS = (WB_ILOADS + WB_WAVES - 1) / WB_WAVES;  // per wave
+constexpr int WB_GITERS = (WB_GLOADS + WB_WAVES - 1) / WB_WAVES;
 
-// 32-bit words (channel c of voxel A, channel c of voxel B) for the 8
-// channels of two 16-byte channel-last pieces, low voxel in the low half:
-// one v_perm_b32 per word (selector bytes 0-3 pick from the second operand,
-// 4-7 from the first).
-__device__ __forceinline__ void pair_words(const uint4 &a, const uint4 &b, uint32_t w[8])
+// The operand of two rows of 16 voxels: this lane's channel, 4 voxels of each.
+__device__ __forceinline__ bf8v read_rows(const bf *row0, const bf *row1)
 {
-    const uint32_t av[4] = {a.x, a.y, a.z, a.w}, bv[4] = {b.x, b.y, b.z, b.w};
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        w[2 * k] = __builtin_amdgcn_perm(bv[k], av[k], 0x05040100u);      // a.lo | b.lo << 16
-        w[2 * k + 1] = __builtin_amdgcn_perm(bv[k], av[k], 0x07060302u);  // a.hi | b.hi << 16
-    }
+    using L = __attribute__((address_space(3))) s4;
+    const s4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((L *)row0);
+    const s4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((L *)row1);
+    return __builtin_bit_cast(bf8v, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
-__global__ __launch_bounds__(256) void k_conv_wgrad(ConvIn src, const bf *__restrict__ gout,
-                                                    float *__restrict__ gw, float *__restrict__ gb, Dims d,
-                                                    int nbx, int nby, int nbz)
+// 16 bytes per lane from element `offset` of base into lds + 16 lane; zeros
+// where the offset is kOutside.  kFar: byte offsets may exceed 32 bits.
+constexpr uint32_t kRange = 0xffffff00u, kOutside = 0xffffffffu;
+template <bool kFar>
+__device__ __forceinline__ void load_to_lds(const bf *base, bf *lds, int lane, uint32_t offset)
 {
-    __shared__ __attribute__((aligned(16))) bf gT[16 * WB_GROW];
-    __shared__ __attribute__((aligned(16))) bf iT[16 * WB_PLANE];
+    using L = __attribute__((address_space(3))) void;
+    if constexpr (kFar) {
+        if (offset == kOutside)
+            *reinterpret_cast<uint4 *>(lds + lane * 8) = make_uint4(0, 0, 0, 0);
+        else
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(base + offset),
+                                             (L *)lds, 16, 0, 0);
+    } else {
+        const auto r = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf *>(base), short(0), int(kRange), 0x00020000);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (L *)lds, 16, offset == kOutside ? kOutside : 2 * offset, 0, 0,
+                                                 0);
+    }
+}
+// Wait for this wave's loads to LDS (vmcnt 0).
+__device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0f70); }
+
+template <bool kFar>
+__global__ __launch_bounds__(64 * WB_WAVES) __attribute__((amdgpu_waves_per_eu(3))) void
+k_conv_wgrad(ConvIn src, const bf *__restrict__ gout, float *__restrict__ gw, float *__restrict__ gb, Dims d,
+             int nbx, int nby, int nbz)
+{
+    __shared__ __attribute__((aligned(16))) struct {
+        bf in[WB_ILOADS * 64 * 8];
+        bf go[WB_V * 16];
+        bf more[WB_TEAMS * (27 * 256 + 16) * 2 - WB_ILOADS * 64 * 8 - WB_V * 16];  // for the sums
+    } lds;
     const int Ci = d.Ci, Co = d.Co;
     const int CIT = Ci / 16;
     const int ct = blockIdx.y / CIT, it = blockIdx.y % CIT;
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int col = lane & 15, kq = lane >> 4;
-    const bool bias_wave = wv == 3 && gb != nullptr && it == 0;
-    const bool g3 = wv == 0;               // wave 0 also runs group 8
+    const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
+    const int team = wave / 3, dx = wave % 3;            // dx: x offset + 1
+    const int lane = threadIdx.x & 63;
     const int nbricks = d.B * nbx * nby * nbz;
-    const int cs = Ci - src.cu;            // channel stride of src.in
     const bool up = it * 16 < src.cu;      // this block's input channels come from src.low
-    const int cin = it * 16 - src.cu;      // channel offset in src.in (when !up)
+    const bf *const in = up ? src.low : src.in;
+    const int cs = up ? src.cu : Ci - src.cu;            // channel stride of `in`
+    const int cin = up ? it * 16 : it * 16 - src.cu;     // channel offset in it
 
-    // Operand addresses of this lane at row pair 0: the gout operand (row
-    // kq >> 1, voxels 8 (kq & 1) ..) and, per group, the first of the two
-    // input reads (halo voxel 8 (kq & 1), i.e. x = 8 (kq & 1) - 1).  Row pair
-    // q adds (q / 2) 6 + 2 (q % 2) halo rows to every input address.
-    const bf *ap = gT + col * WB_GROW + kq * 8;
-    const bf *bb[3];
-#pragma unroll
-    for (int gs = 0; gs < 3; ++gs) {
-        const int G = wv + 4 * gs < 9 ? wv + 4 * gs : 8;
-        const int dy = G % 3 - 1, dz = G / 3 - 1;
-        const int hrow = (1 + dz) * (WB_Y + 2) + (kq >> 1) + 1 + dy;
-        bb[gs] = iT + col * WB_PLANE + hrow * WB_RW + (kq & 1) * 8;
-    }
-    f4 acc[3][3], accb = f4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int gs = 0; gs < 3; ++gs)
-#pragma unroll
-        for (int x = 0; x < 3; ++x)
-            acc[gs][x] = f4{0.f, 0.f, 0.f, 0.f};
-    const bf8v ones = __builtin_bit_cast(bf8v, make_uint4(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u));
-
-    // Staging tasks.  gout: thread t packs voxels 2p, 2p + 1 (p = t & 127) of
-    // channel half t >> 7.  Input: task k = (x pair a = k % 9, halo row
-    // r = (k / 9) % 36, channel half k / 324) loads voxels x0 + 2a - 1 and
-    // x0 + 2a of its row and writes halo positions 2a, 2a + 1.  The next
-    // brick's loads are issued before this brick's MFMAs and written to LDS
-    // afterwards.  Element offsets from the brick's first voxel: the gout
-    // pair of this thread, and voxel x0 + 2a - 1 of each input task (+ Ci for
-    // the second voxel).
+    // This lane's pieces: the block's waves w run wave loads j = w + 12 k; piece i = 64 j +
+    // lane is half i % 2 of voxel i / 2 of the halo (or gout) tile.  Byte offsets
+    // from the voxel before the brick's first one in x, y and z (input) and from
+    // the brick's first voxel (gout).
     const BrickGrid grid(nbx, nby, nbz);
-    int goff, ioff[WB_ITERS];
-    {
-        const int v = 2 * (threadIdx.x & 127);
-        goff = (((v >> 6) * d.H + ((v >> 4) & 3)) * d.W + (v & 15)) * Co + ct * 16 + (threadIdx.x >> 7) * 8;
+    auto halo_of = [&](int k, int &hx, int &hy, int &hz) {
+        const int hv = ((wave + WB_WAVES * k) * 64 + lane) >> 1, hrow = hv / WB_HX;
+        hx = hv % WB_HX - 1, hy = hrow % WB_HY - 1, hz = hrow / WB_HY - 1;
+    };
+    const int sh = up ? 1 : 0;  // brick corners are even: (x0 + hx) >> 1 = x0 / 2 + (hx >> 1)
+    const int Hi = d.H >> sh, Wi = d.W >> sh, Di = d.D >> sh;
+    uint32_t ioff[WB_IITERS], goff[WB_GITERS];
+#pragma unroll
+    for (int k = 0; k < WB_IITERS; ++k) {
+        int hx, hy, hz;
+        halo_of(k, hx, hy, hz);
+        ioff[k] = uint32_t((((hz >> sh) + 1) * Hi + (hy >> sh) + 1) * Wi + (hx >> sh) + 1) * uint32_t(cs) +
+                  uint32_t(cin + (lane & 1) * 8);
+        if (hz > WB_Z)
+            ioff[k] = kOutside;  // the last wave load's tail
     }
 #pragma unroll
-    for (int k = 0; k < WB_ITERS; ++k) {
-        const int task = threadIdx.x + 256 * k;
-        const int a = task % WB_XP, r = (task / WB_XP) % WB_HROWS, h = task / (WB_XP * WB_HROWS);
-        const int hy = r % (WB_Y + 2), hz = r / (WB_Y + 2);
-        ioff[k] = (((hz - 1) * d.H + (hy - 1)) * d.W + (2 * a - 1)) * cs + cin + h * 8;
+    for (int k = 0; k < WB_GITERS; ++k) {
+        const int v = ((wave + WB_WAVES * k) * 64 + lane) >> 1;
+        goff[k] = uint32_t(((v >> 7) * d.H + ((v >> 4) & 7)) * d.W + (v & 15)) * uint32_t(Co) +
+                  uint32_t(ct * 16 + (lane & 1) * 8);
     }
-    uint4 gl[2], il[WB_ITERS][2];
     auto load_brick = [&](int br) {
         int b, x0, y0, z0;
         grid.at(br, WB_X, WB_Y, WB_Z, b, x0, y0, z0);
-        const int vb = ((b * d.D + z0) * d.H + y0) * d.W + x0;
-        if (!up && x0 >= 1 && x0 + WB_X < d.W && y0 >= 1 && y0 + WB_Y < d.H && z0 >= 1 && z0 + WB_Z < d.D) {
-            // the whole halo is inside the volume
-            gl[0] = *reinterpret_cast<const uint4 *>(gout + vb * Co + goff);
-            gl[1] = *reinterpret_cast<const uint4 *>(gout + vb * Co + goff + Co);
+        const bf *const ib =
+            in + (((long long)(b * Di + (z0 >> sh) - 1) * Hi + (y0 >> sh) - 1) * Wi + (x0 >> sh) - 1) * cs;
+        const bf *const gr = gout + (((long long)(b * d.D + z0) * d.H + y0) * d.W + x0) * Co;
+        const bool inner = x0 >= 1 && x0 + WB_X < d.W && y0 >= 1 && y0 + WB_Y < d.H && z0 >= 1 && z0 + WB_Z < d.D;
 #pragma unroll
-            for (int k = 0; k < WB_ITERS; ++k)
-                if (threadIdx.x + 256 * k < WB_ITASKS)
-#pragma unroll
-                    for (int m = 0; m < 2; ++m)
-                        il[k][m] = *reinterpret_cast<const uint4 *>(src.in + vb * cs + ioff[k] + m * cs);
-            return;
-        }
-        {
-            const int p = threadIdx.x & 127, h = threadIdx.x >> 7;
-            const int v = 2 * p;
-            const int x = x0 + (v & 15), y = y0 + ((v >> 4) & 3), z = z0 + (v >> 6);
-#pragma unroll
-            for (int m = 0; m < 2; ++m) {
-                gl[m] = make_uint4(0, 0, 0, 0);
-                if (x + m < d.W && y < d.H && z < d.D) {
-                    const int q = ((b * d.D + z) * d.H + y) * d.W + x + m;
-                    gl[m] = *reinterpret_cast<const uint4 *>(gout + q * Co + ct * 16 + h * 8);
-                }
+        for (int k = 0; k < WB_IITERS; ++k) {
+            uint32_t o = ioff[k];
+            if (!inner) {
+                int hx, hy, hz;
+                halo_of(k, hx, hy, hz);
+                if (uint32_t(x0 + hx) >= uint32_t(d.W) || uint32_t(y0 + hy) >= uint32_t(d.H) ||
+                    uint32_t(z0 + hz) >= uint32_t(d.D))
+                    o = kOutside;
             }
+            if (wave + WB_WAVES * k < WB_ILOADS)
+                load_to_lds<kFar>(ib, lds.in + (wave + WB_WAVES * k) * 512, lane, o);
         }
 #pragma unroll
-        for (int k = 0; k < WB_ITERS; ++k) {
-            const int task = threadIdx.x + 256 * k;
-            const int a = task % WB_XP, r = (task / WB_XP) % WB_HROWS, h = task / (WB_XP * WB_HROWS);
-            const int y = y0 + r % (WB_Y + 2) - 1, z = z0 + r / (WB_Y + 2) - 1;
-            const bool row_ok = task < WB_ITASKS && y >= 0 && y < d.H && z >= 0 && z < d.D;
-            const int q0 = ((b * d.D + z) * d.H + y) * d.W;
-            const int l0 = ((b * (d.D >> 1) + (z >> 1)) * (d.H >> 1) + (y >> 1)) * (d.W >> 1);
-#pragma unroll
-            for (int m = 0; m < 2; ++m) {
-                const int x = x0 + 2 * a - 1 + m;
-                il[k][m] = make_uint4(0, 0, 0, 0);
-                if (row_ok && x >= 0 && x < d.W)
-                    il[k][m] = up ? *reinterpret_cast<const uint4 *>(src.low + (l0 + (x >> 1)) * src.cu +
-                                                                     it * 16 + h * 8)
-                                  : *reinterpret_cast<const uint4 *>(src.in + (q0 + x) * cs + cin + h * 8);
+        for (int k = 0; k < WB_GITERS; ++k) {
+            uint32_t o = goff[k];
+            if (!inner) {
+                const int v = ((wave + WB_WAVES * k) * 64 + lane) >> 1;
+                if (x0 + (v & 15) >= d.W || y0 + ((v >> 4) & 7) >= d.H || z0 + (v >> 7) >= d.D)
+                    o = kOutside;
             }
-        }
-    };
-    auto store_brick = [&]() {
-        {
-            const int p = threadIdx.x & 127, h = threadIdx.x >> 7;
-            uint32_t w[8];
-            pair_words(gl[0], gl[1], w);
-#pragma unroll
-            for (int c = 0; c < 8; ++c)
-                reinterpret_cast<uint32_t *>(gT + (h * 8 + c) * WB_GROW)[p] = w[c];
-        }
-#pragma unroll
-        for (int k = 0; k < WB_ITERS; ++k) {
-            const int task = threadIdx.x + 256 * k;
-            if (task >= WB_ITASKS)
-                continue;
-            const int a = task % WB_XP, r = (task / WB_XP) % WB_HROWS, h = task / (WB_XP * WB_HROWS);
-            uint32_t w[8];
-            pair_words(il[k][0], il[k][1], w);
-#pragma unroll
-            for (int c = 0; c < 8; ++c)
-                reinterpret_cast<uint32_t *>(iT + (h * 8 + c) * WB_PLANE + r * WB_RW)[a] = w[c];
+            if (wave + WB_WAVES * k < WB_GLOADS)
+                load_to_lds<kFar>(gr, lds.go + (wave + WB_WAVES * k) * 512, lane, o);
         }
     };
 
+    f4 acc[9], accb = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < 9; ++t)
+        acc[t] = f4{0.f, 0.f, 0.f, 0.f};
+    const bf8v ones = __builtin_bit_cast(bf8v, make_uint4(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u));
+    const bool bias_wave = dx == 0 && gb != nullptr && it == 0;
+    const int qy = team % (WB_Y / WB_QY) * WB_QY, qz = team / (WB_Y / WB_QY) * WB_QZ;  // the team's quarter
+    const bf *const ip = lds.in + ((qz * WB_HY + qy) * WB_HX + dx) * 16 + lane * 4;
+    const bf *const gp = lds.go + (qz * WB_Y + qy) * WB_X * 16 + lane * 4;
+
     const BrickWalk bw = brick_walk(nbricks);
-    if (bw.count > 0)
-        load_brick(bw.first);
     for (int n = 0; n < bw.count; ++n) {
         __syncthreads();  // the previous brick's reads are done
-        store_brick();
+        load_brick(bw.first + n * bw.stride);
+        wait_loads();
         __syncthreads();
-        if (n + 1 < bw.count)
-            load_brick(bw.first + (n + 1) * bw.stride);
-        // row pairs (2q, 2q + 1): pair q + 1's operands are read before pair
-        // q's products, in two register sets; the scheduling barriers keep
-        // the compiler from moving the reads back next to their MFMAs
-        bf8v av[2];
-        uint4 lo[2][3], hi[2][3];
-        auto read_pair = [&](int q, int k) {
-            const int roff = ((q / 2) * (WB_Y + 2) + 2 * (q % 2)) * WB_RW;
-            av[k] = *reinterpret_cast<const bf8v *>(ap + q * 32);
+        bf8v a[2 * WB_QZ];  // rows (z, 2p), (z, 2p + 1) of gout: a[2 z + p]
 #pragma unroll
-            for (int gs = 0; gs < 3; ++gs)
-                if (gs < 2 || g3) {
-                    lo[k][gs] = *reinterpret_cast<const uint4 *>(bb[gs] + roff);
-                    hi[k][gs] = *reinterpret_cast<const uint4 *>(bb[gs] + roff + 8);
+        for (int Z = 0; Z < WB_QZ + 2; ++Z) {
+            if (Z < WB_QZ)
+#pragma unroll
+                for (int p = 0; p < 2; ++p) {
+                    const bf *const row = gp + (Z * WB_Y + 2 * p) * WB_X * 16;
+                    a[2 * Z + p] = read_rows(row, row + WB_X * 16);
+                    if (bias_wave)
+                        accb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[2 * Z + p], ones, accb, 0, 0, 0);
                 }
-        };
-        read_pair(0, 0);
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            if (q + 1 < 8)
-                read_pair(q + 1, (q + 1) & 1);
-            __builtin_amdgcn_sched_barrier(0);
-            const int k = q & 1;
+            for (int Y = 0; Y + 1 < WB_QY + 2; ++Y) {
+                const bf *const row = ip + (Z * WB_HY + Y) * WB_HX * 16;
+                const bf8v v = read_rows(row, row + WB_HX * 16);
 #pragma unroll
-            for (int gs = 0; gs < 3; ++gs)
-                if (gs < 2 || g3) {
-                    const uint4 l = lo[k][gs], h = hi[k][gs];
-                    // halo elements 1-8 (dx = 0) and 2-9 (dx = +1) of the 16 read
-                    const uint4 s0 = make_uint4(__builtin_amdgcn_perm(l.y, l.x, 0x05040302u),
-                                                __builtin_amdgcn_perm(l.z, l.y, 0x05040302u),
-                                                __builtin_amdgcn_perm(l.w, l.z, 0x05040302u),
-                                                __builtin_amdgcn_perm(h.x, l.w, 0x05040302u));
-                    const uint4 s1 = make_uint4(l.y, l.z, l.w, h.x);
-                    acc[gs][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[k], __builtin_bit_cast(bf8v, l),
-                                                                         acc[gs][0], 0, 0, 0);
-                    acc[gs][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[k], __builtin_bit_cast(bf8v, s0),
-                                                                         acc[gs][1], 0, 0, 0);
-                    acc[gs][2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[k], __builtin_bit_cast(bf8v, s1),
-                                                                         acc[gs][2], 0, 0, 0);
-                }
-            if (bias_wave)
-                accb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[k], ones, accb, 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);
+                for (int z = 0; z < WB_QZ; ++z)
+#pragma unroll
+                    for (int p = 0; p < 2; ++p) {
+                        const int kz = Z - z, ky = Y - 2 * p;  // dz + 1, dy + 1
+                        if (kz >= 0 && kz < 3 && ky >= 0 && ky < 3)
+                            acc[kz * 3 + ky] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                a[2 * z + p], v, acc[kz * 3 + ky], 0, 0, 0);
+                    }
+            }
         }
     }
+    // The teams' sums in LDS, each [tap][co][ci] and then the bias; every thread
+    // adds its share of their total to the global gradient, blocks starting at
+    // different places (from the same one they queue at the same addresses).
+    constexpr int NSUM = 27 * 256 + 16;
+    static_assert(sizeof(lds) >= WB_TEAMS * NSUM * sizeof(float), "room for the sums");
+    float *const red = reinterpret_cast<float *>(&lds);
+    const int col = lane & 15, kq = lane >> 4;
+    __syncthreads();
 #pragma unroll
-    for (int gs = 0; gs < 3; ++gs) {
-        const int G = wv + 4 * gs;
-        if (G >= 9)
-            continue;
+    for (int t = 0; t < 9; ++t)
 #pragma unroll
-        for (int x = 0; x < 3; ++x)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int co = ct * 16 + kq * 4 + r, ci = it * 16 + col;
-                atomicAdd(&gw[(co * 27 + 3 * G + x) * Ci + ci], acc[gs][x][r]);
-            }
-    }
-    if (bias_wave && col == 0)  // D[co][*] = sum_k gout[k][co]
+        for (int r = 0; r < 4; ++r)  // D[4 kq + r][col] = sum of co 4 kq + r, ci col
+            red[team * NSUM + (3 * t + dx) * 256 + (kq * 4 + r) * 16 + col] = acc[t][r];
+    if (dx == 0 && col == 0)
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-            atomicAdd(&gb[ct * 16 + kq * 4 + r], accb[r]);
+            red[team * NSUM + 27 * 256 + kq * 4 + r] = accb[r];
+    __syncthreads();
+    auto total = [&](int e) {
+        float v = red[e];
+        for (int q = 1; q < WB_TEAMS; ++q)
+            v += red[q * NSUM + e];
+        return v;
+    };
+    const int rot = int(blockIdx.x) * 7 % 108 * 64;
+    for (int k = threadIdx.x; k < 27 * 256; k += 64 * WB_WAVES) {
+        int e = k + rot;
+        if (e >= 27 * 256)
+            e -= 27 * 256;
+        const int tap = e >> 8, co = ct * 16 + ((e >> 4) & 15), ci = it * 16 + (e & 15);
+        atomicAdd(&gw[(co * 27 + tap) * Ci + ci], total(e));
+    }
+    if (gb != nullptr && it == 0 && threadIdx.x < 16)
+        atomicAdd(&gb[ct * 16 + threadIdx.x], total(27 * 256 + threadIdx.x));
 }
 
 // ------------------------------------------------------------ elementwise
@@ -1644,27 +1614,23 @@ lbmx_status conv_wgrad(ConvIn src, const void *gout, float *gw, float *gb, int32
     const int nbx = (W + WB_X - 1) / WB_X, nby = (H + WB_Y - 1) / WB_Y, nbz = (D + WB_Z - 1) / WB_Z;
     const long long nbricks = (long long)B * nbx * nby * nbz;
     const int pairs = (Co / 16) * (Ci / 16);
-    // one wave of resident blocks over all channel pairs (two per CU, the
-    // register limit); each block sums at least WG_MIN_BRICKS bricks in
-    // registers before its atomic adds (on small grids the atomics of many
-    // short blocks onto the same addresses cost more than the parallelism
-    // gains)
-    static const int per_cu = [] {
-        int nb = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_conv_wgrad, 256, 0) != hipSuccess)
-            nb = 1;
-        return nb < 1 ? 1 : nb;
-    }();
+    // one block per CU (its LDS and registers) over all channel pairs: every
+    // block adds its sums to the same gradient elements, which costs about 6 us
+    // for 256 blocks, so a second round of blocks would cost more than it hides
     int dev = 0, cus = 256;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
         cus = 256;
-    long long gx = ((long long)per_cu * cus + pairs - 1) / pairs;
-    gx = std::min(gx, (nbricks + WG_MIN_BRICKS - 1) / WG_MIN_BRICKS);
+    long long gx = std::min((cus + pairs - 1LL) / pairs, nbricks);
     if (gx >= 8) gx -= gx % 8;  // x extent a multiple of 8: XCD-aware brick order
-    if (gx < 1) gx = 1;
-    hipLaunchKernelGGL(k_conv_wgrad, dim3(unsigned(gx), unsigned(pairs)), dim3(256), 0, S(stream), src,
-                       reinterpret_cast<const bf *>(gout), gw, gb, d, nbx, nby, nbz);
+    // byte offsets within a brick's halo planes, from the voxel before its first
+    const long long span = 2LL * (WB_HZ + 1) * (H + 1) * (W + 2) * (Ci > Co ? Ci : Co);
+    const dim3 blocks{unsigned(gx), unsigned(pairs)}, threads{64 * WB_WAVES};
+    const bf *const g = reinterpret_cast<const bf *>(gout);
+    if (span < (long long)kRange)
+        hipLaunchKernelGGL(k_conv_wgrad<false>, blocks, threads, 0, S(stream), src, g, gw, gb, d, nbx, nby, nbz);
+    else
+        hipLaunchKernelGGL(k_conv_wgrad<true>, blocks, threads, 0, S(stream), src, g, gw, gb, d, nbx, nby, nbz);
     HIP_TRY(hipGetLastError());
     return LBMX_OK;
 }
