@@ -79,36 +79,44 @@ __device__ __forceinline__ long long nvox_of(const Dims &d)
 // A block owns NCO output channel tiles of 16 (blockIdx.y selects the group)
 // and walks bricks of 16 x 4 x 4 voxels in the XCD-aware order of
 // brick_walk.  Per round of 16 input channels it stages in LDS, channel-last:
-//   xs: the brick's input plus a one-voxel halo (18 x 6 x 6 voxels), so the
-//       MFMA operand "8 consecutive input channels of the voxel at this tap"
-//       is one aligned 16-byte read for any tap;
-//   ws: the weights of the block's output channels for all 27 taps, plus a
-//       28th tap of zeros.
-// A row (16 channels, 32 bytes) holds its two 8-channel halves swapped when
-// bit 2 of its x (halo x for xs, output channel for ws) is set: the 8 lanes
-// of a 16-byte LDS read phase then cover all banks.  The products run on
-// v_mfma_f32_16x16x32_bf16 (gfx950; lane layout checked on the device): its
-// K = 32 covers two taps of the round's 16 channels (lanes 0-31 tap 2p,
-// lanes 32-63 tap 2p + 1, p < 14).  The 28th tap has zero weights and reads
-// its input operand from a zeroed LDS block, so non-finite inputs cannot
-// leak into it.  Wave w computes the brick's rows 4w .. 4w+3 (16 voxels
-// each): every weight operand serves 4 rows and every input operand the NCO
-// channel tiles.  Each lane's 14 input-operand addresses are computed once
-// per launch and the taps are unrolled, so the inner loop is LDS reads and
-// MFMAs only (a row step is an immediate offset).  Each lane ends with 4
-// consecutive output channels of one voxel and stores them together.
-// A round's global loads are all issued before any is written to LDS (a
-// fixed count per thread, held in registers), and the next round's (of the
-// same or the next brick) are issued before this round's MFMAs, so their
-// latency overlaps the taps.
+//   x: the brick's input plus a one-voxel halo (18 x 6 x 6 voxels, or 18 x 6 x
+//      10), so the MFMA operand "8 consecutive input channels of the voxel at
+//      this tap" is one aligned 16-byte read for any tap;
+//   w: the weights of the block's output channels for all 27 taps, plus a
+//      28th tap of zeros.
+// Both come from memory straight into LDS (buffer loads to LDS; voxels outside
+// the volume are out of the buffer's range and arrive as zeros).  A row (16
+// channels, 32 bytes) holds its two 8-channel halves swapped when bit 2 of its x
+// (halo x for x, output channel for w) is set, by each lane fetching the half that
+// belongs at its place: the 8 lanes of a 16-byte LDS read phase then cover all
+// banks.  The products run on v_mfma_f32_16x16x32_bf16 (gfx950; lane layout
+// checked on the device): its K = 32 covers two taps of the round's 16 channels
+// (lanes 0-31 tap 2p, lanes 32-63 tap 2p + 1, p < 14).  The 28th tap has zero
+// weights and reads its input operand from a zeroed LDS block, so non-finite
+// inputs cannot leak into it.  A wave computes 4 rows of 16 voxels (8 in two
+// planes): a weight operand serves all of them, and an input operand the NCO
+// channel tiles and every (row, tap pair) that it lies at (TapPairs), which
+// leaves 50 (39) of 56 input reads per 4 rows.  Each lane ends with 4 consecutive
+// output channels of one voxel and stores them together.
+// Per round: wait for the tiles, products, request the next round's tiles into
+// the same place, and finish and store a brick's results while they travel: the
+// wait counts off the stores, which are one instruction per row and tile for
+// every wave, excluded lanes by their offset.  The other blocks of the CU (4 with
+// one channel tile) fill the waits.
+// Bound by LDS reads (15 of 29 us at 64^3 16 -> 16 before they were shared) and,
+// with the SiLU beside z, by the stores (18 us alone).  Batch 4, us, tiles through
+// registers -> here: 64^3 16 -> 16 35 -> 26.5, 48 -> 16 72 -> 53, 32^3 96 -> 32 32 ->
+// 28.5, 16^3 64 -> 64 12.2 -> 10.8, 8^3 96 -> 96 13.4 -> 10.4; data gradients 64^3 16 ->
+// 16 38 -> 30, 16 -> 48 74 -> 47, 32^3 32 -> 96 39 -> 28.  Two buffers and two blocks per
+// CU instead: 34.
 typedef __bf16 bf8v __attribute__((ext_vector_type(8)));
-constexpr int FC_X = 16, FC_Y = 4, FC_Z = 4;        // brick
-constexpr int FC_HX = FC_X + 2, FC_HY = FC_Y + 2, FC_HZ = FC_Z + 2;
-constexpr int FC_HVOX = FC_HX * FC_HY * FC_HZ;      // 648 halo voxels
+constexpr int FC_X = 16, FC_Y = 4;                  // brick: 16 x 4 x 4 RZ voxels
+constexpr int FC_HX = FC_X + 2, FC_HY = FC_Y + 2;
+constexpr int FC_ROW = FC_HX * 16;                  // elements of a halo row
 constexpr int FC_THREADS = 256;                     // block size (the launcher's)
-constexpr int FC_XITEMS = FC_HVOX * 2;              // 16-byte pieces of the input tile
-constexpr int FC_XITERS = (FC_XITEMS + FC_THREADS - 1) / FC_THREADS;
-constexpr int FC_ZERO = 3 * FC_HX * 16 + 16;        // zero block: the padding tap's 4 row reads
+constexpr int FC_ZERO = 3 * FC_ROW + 16;            // zero block: the padding tap's 4 row reads
+constexpr int FC_WLOADS(int nco) { return (27 * nco * 32 + 63) / 64; }  // wave loads of a weight tile
+constexpr int FC_WITERS(int nco) { return (FC_WLOADS(nco) + 3) / 4; }   // per wave
 
 // element offset of half `part` of row `row` whose swizzle bit is `sx`
 __device__ __forceinline__ int fc_slot(int row, int part, int sx)
@@ -214,31 +222,135 @@ struct LossEp {
     int npartial;
 };
 
-// Occupancy is register-bound: 3 waves per SIMD for one channel tile (no
-// spills; 4 would spill), 2 for two and for the loss variant.
+// 16 bytes per lane from element `offset` of base into lds + 16 lane; zeros
+// where the offset is kOutside.  kDirect: straight into LDS (wait_loads), for a
+// 16-byte aligned base and byte offsets below kRange.
+constexpr uint32_t kRange = 0xffffff00u, kOutside = 0xffffffffu;
+template <bool kDirect>
+__device__ __forceinline__ void load_to_lds(const bf *base, bf *lds, int lane, uint32_t offset)
+{
+    if constexpr (kDirect) {
+        using L = __attribute__((address_space(3))) void;
+        const auto r = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf *>(base), short(0), int(kRange), 0x00020000);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (L *)lds, 16, offset == kOutside ? kOutside : 2 * offset, 0, 0,
+                                                 0);
+    } else {
+        uint4 v = make_uint4(0, 0, 0, 0);
+        if (offset != kOutside)
+            __builtin_memcpy(&v, base + offset, 16);
+        *reinterpret_cast<uint4 *>(lds + lane * 8) = v;
+    }
+}
+// Wait until no more than n of this wave's memory operations are on their way
+// (vmcnt n): its loads to LDS before the last n.
+template <int n = 0>
+__device__ __forceinline__ void wait_loads()
+{
+    static_assert(n < 64);
+    __builtin_amdgcn_s_waitcnt(0x0f70 | (n & 15) | (n >> 4 << 14));
+}
+
+typedef uint32_t v2u __attribute__((ext_vector_type(2)));
+typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ auto buffer_of(const void *base, int range)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), short(0), range, 0x00020000);
+}
+// A lane's 8 or 16 bytes at a byte offset of base; nothing (zeros) where the
+// offset or the range (0 or kRange) excludes it.  kDirect (an aligned base): one
+// instruction for the whole wave, whichever lanes are excluded.
+template <bool kDirect, class V>
+__device__ __forceinline__ void store_vec(void *base, int range, V v, uint32_t offset)
+{
+    if constexpr (!kDirect) {
+        if (range && offset != kOutside)
+            __builtin_memcpy(static_cast<char *>(base) + offset, &v, sizeof v);
+    } else if constexpr (sizeof(V) == 8) {
+        __builtin_amdgcn_raw_buffer_store_b64(v, buffer_of(base, range), offset, 0, 0);
+    } else {
+        __builtin_amdgcn_raw_buffer_store_b128(v, buffer_of(base, range), offset, 0, 0);
+    }
+}
+template <bool kDirect>
+__device__ __forceinline__ v2u load_vec(const void *base, int range, uint32_t offset)
+{
+    v2u v{0, 0};
+    if constexpr (kDirect)
+        v = __builtin_amdgcn_raw_buffer_load_b64(buffer_of(base, range), offset, 0, 0);
+    else if (range && offset != kOutside)
+        __builtin_memcpy(&v, static_cast<const char *>(base) + offset, sizeof v);
+    return v;
+}
+
+// What the convolution writes (Epilogue and LossEp): FP32, BF16 (with or
+// without split), BF16 and its SiLU, BF16 times SiLU' at gate, or the loss.
+enum FcOut { kF32, kBf16, kAct, kGate, kLoss };
+
+// Occupancy is register-bound: 4 waves per SIMD for one channel tile, 2 for
+// two and for the loss variant.
 //
 // KS > 1 (layers with several rounds on small grids): the block has KS
 // groups of FC_THREADS threads, each with its own LDS tiles; group g takes
 // rounds g, g + KS, ... of the same brick, which shortens the block's
 // serial chain of rounds KS times; at the end of a brick the other groups
 // add their sums into group 0's through LDS, and group 0 stores.
-constexpr int fc_waves(int nco, bool loss, int ks) { return nco == 1 && !loss && ks == 1 ? 3 : 2; }
-template <int NCO, bool LOSS, int KS>
-__global__ __launch_bounds__(FC_THREADS * KS) __attribute__((amdgpu_waves_per_eu(fc_waves(NCO, LOSS, KS)))) void
-k_conv_fwd(ConvIn src, const bf *__restrict__ w, const float *__restrict__ bias, void *__restrict__ out,
-           int out_f32, Dims d, int nbx, int nby, int nbz, Epilogue ep, LossEp ls)
+constexpr int fc_waves(int nco, int rz, FcOut kind, int ks)
 {
-    constexpr int WITEMS = 27 * NCO * 16 * 2;       // 16-byte pieces of the weight tile
-    constexpr int WITERS = (WITEMS + FC_THREADS - 1) / FC_THREADS;
-    __shared__ __attribute__((aligned(16))) bf xsa[KS][FC_HVOX * 16];
-    __shared__ __attribute__((aligned(16))) bf wsa[KS][28 * NCO * 16 * 16];
-    __shared__ __attribute__((aligned(16))) bf zs[FC_ZERO];
-    __shared__ f4 red[KS > 1 ? (KS - 1) * 4 * NCO * FC_THREADS : 1];
-    const int tid = int(threadIdx.x) % FC_THREADS, kg = int(threadIdx.x) / FC_THREADS;
-    bf *const xs = xsa[kg], *const ws = wsa[kg];
+    return nco == 1 && kind != kLoss && ks == 1 ? (rz == 1 ? 4 : 3) : 2;
+}
+template <int NCO, int RZ>
+struct FcTile {
+    static constexpr int Z = 4 * RZ, HZ = Z + 2;                // brick and halo extent in z
+    static constexpr int PIECES = FC_HX * FC_HY * HZ * 2;       // 16-byte pieces of the input tile
+    static constexpr int LOADS = (PIECES + 63) / 64;            // wave loads of 64 pieces
+    static constexpr int ITERS = (LOADS + 3) / 4;               // per wave
+    static constexpr int WROWS = 28 * NCO * 16;
+    bf x[LOADS * 512];               // input halo
+    bf zero[FC_ZERO];
+    bf w[(FC_WLOADS(NCO) * 32 > WROWS ? FC_WLOADS(NCO) * 32 : WROWS) * 16];  // weights, a 28th tap of zeros
+};
+
+// The input operand of tap pair p (taps 2 p and 2 p + 1) for output row (y, z)
+// of a wave is one of three kinds at halo row (y + dy, z + dz), where a row
+// serves every output row and pair that it lies at:
+//   kind 0: x offsets 0, 1;   kind 1: x offsets 1, 2;
+//   kind 2: x offset 2, and 0 of the next row in y;
+// or (pairs 4 and 13, one use each) x offset 2 of the last row of a plane's taps
+// and 0 of the next plane's first (or the zeros).
+struct TapPairs {
+    static constexpr int kind[14] = {0, 2, 1, 0, 3, 1, 0, 2, 1, 0, 2, 1, 0, 4};
+    static constexpr int dz[14] = {0, 0, 0, 0, 0, 1, 1, 1, 1, 2, 2, 2, 2, 0};
+    static constexpr int dy[14] = {0, 0, 1, 2, 0, 0, 1, 1, 2, 0, 0, 1, 2, 0};
+};
+// The first pair that uses kind k at halo row (y, z) of a wave.
+template <int RZ>
+struct FirstUse {
+    int pair[3][RZ + 2][FC_HY] = {};
+    constexpr FirstUse()
+    {
+        for (int p = 13; p >= 0; --p)
+            for (int z = 0; z < RZ; ++z)
+                for (int y = 0; y < 4; ++y)
+                    if (TapPairs::kind[p] < 3)
+                        pair[TapPairs::kind[p]][z + TapPairs::dz[p]][y + TapPairs::dy[p]] = p;
+    }
+};
+
+template <int NCO, int RZ, FcOut kOut, int KS, bool kDirect>
+__global__ __launch_bounds__(FC_THREADS * KS) __attribute__((amdgpu_waves_per_eu(fc_waves(NCO, RZ, kOut, KS)))) void
+k_conv_fwd(ConvIn src, const bf *__restrict__ w, const float *__restrict__ bias, void *__restrict__ out,
+           Dims d, int nbx, int nby, int nbz, Epilogue ep, LossEp ls)
+{
+    using Tile = FcTile<NCO, RZ>;
+    constexpr int kWaves = fc_waves(NCO, RZ, kOut, KS), NR4 = 4 * RZ;  // rows of a wave
+    constexpr bool kAhead = kWaves <= 2;
+    constexpr int NBUF = KS > 1 ? 2 : 1;
+    __shared__ __attribute__((aligned(16))) Tile tiles[KS][NBUF];
+    static_assert(KS == 1 || NR4 * NCO * FC_THREADS * sizeof(f4) <= sizeof(tiles[0][0].x), "room for a group's sums");
+    const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
+    const int tid = int(threadIdx.x) % FC_THREADS, kg = wave / 4;
     const int Ci = d.Ci, Co = d.Co;
-    const int cs = Ci - src.cu;  // channel stride of src.in
-    const int lane = tid & 63, wv = tid >> 6;
+    const int lane = tid & 63, wv = wave % 4;
     const int col = lane & 15, kq = lane >> 4;
     const int h = kq >> 1, part = kq & 1;   // tap parity and channel half of this lane's K slice
     const int co0 = blockIdx.y * NCO * 16;
@@ -246,298 +358,338 @@ k_conv_fwd(ConvIn src, const bf *__restrict__ w, const float *__restrict__ bias,
     const int R = Ci / 16;  // rounds of 16 input channels per brick
     const BrickGrid grid(nbx, nby, nbz);
     auto brick_at = [&](int j, int &bb, int &xx, int &yy, int &zz) {
-        grid.at(j, FC_X, FC_Y, FC_Z, bb, xx, yy, zz);
+        grid.at(j, FC_X, FC_Y, Tile::Z, bb, xx, yy, zz);
     };
 
-    // This thread's input pieces i = tid + k FC_THREADS (halo voxel
-    // i / 2, channel half i % 2): their element offsets from the brick's
-    // first voxel; and its weight pieces' row offsets in w (-1: none).
+    // This lane's pieces: wave wv runs wave loads j = wv + 4 k; piece i = 64 j +
+    // lane fills 16 bytes of LDS row i / 2: the half (i % 2) ^ swizzle bit of that
+    // voxel (weights: of that tap and output channel).  Element offsets from the
+    // voxel before the brick's first one in x, y and z (weights: from w).
     auto halo_of = [&](int k, int &hx, int &hy, int &hz) {
-        const int hv = (tid + k * FC_THREADS) >> 1, hrow = hv / FC_HX;
+        const int hv = ((wv + 4 * k) * 64 + lane) >> 1, hrow = hv / FC_HX;
         hx = hv % FC_HX, hy = hrow % FC_HY, hz = hrow / FC_HY;
     };
-    int rel[FC_XITERS], wrow[WITERS];
+    uint32_t xoff[Tile::ITERS], woff[FC_WITERS(NCO)];
+    auto x_offsets = [&](bool up) {  // up: voxel (x, y, z) reads low at (x/2, y/2, z/2); brick corners are even
+        const int sh = up ? 1 : 0, cs = up ? src.cu : Ci - src.cu;
+        const int Hi = d.H >> sh, Wi = d.W >> sh;
 #pragma unroll
-    for (int k = 0; k < FC_XITERS; ++k) {
-        int hx, hy, hz;
-        halo_of(k, hx, hy, hz);
-        rel[k] = (((hz - 1) * d.H + (hy - 1)) * d.W + (hx - 1)) * cs + (tid & 1) * 8;
-    }
+        for (int k = 0; k < Tile::ITERS; ++k) {
+            int hx, hy, hz;
+            halo_of(k, hx, hy, hz);
+            const int half = (lane & 1) ^ ((hx >> 2) & 1);
+            xoff[k] = uint32_t((((hz - 1) >> sh) + 1) * Hi + ((hy - 1) >> sh) + 1) * Wi + uint32_t(((hx - 1) >> sh) + 1);
+            xoff[k] = xoff[k] * uint32_t(cs) + uint32_t(half * 8);
+        }
+    };
+    bool up_now = src.cu > 0;
+    x_offsets(up_now);
 #pragma unroll
-    for (int k = 0; k < WITERS; ++k) {
-        const int i = tid + k * FC_THREADS;
-        const int row = i >> 1, tap = row / (NCO * 16), co = row % (NCO * 16);
-        wrow[k] = i < WITEMS ? ((co0 + co) * 27 + tap) * Ci + (i & 1) * 8 : -1;
+    for (int k = 0; k < FC_WITERS(NCO); ++k) {
+        const int row = ((wv + 4 * k) * 64 + lane) >> 1, tap = row / (NCO * 16), co = row % (NCO * 16);
+        const int half = (lane & 1) ^ ((co >> 2) & 1);
+        woff[k] = tap < 27 ? uint32_t(((co0 + co) * 27 + tap) * Ci + half * 8) : kOutside;
     }
 
     // With one round per brick (Ci = 16) the weights are the same for every
-    // item: they are loaded and staged with the block's first item only.
+    // item: they are loaded with the first item of each buffer only.
     const bool w_once = R == 1;
-    uint4 xv[FC_XITERS], wt[WITERS];
-    auto load_round = [&](int j, int c0, bool with_w) {
+    auto load_round = [&](int j, int c0, Tile &t, bool with_w) {
         int b, x0, y0, z0;
         brick_at(j, b, x0, y0, z0);
-        const bf *base = src.in + size_t(((b * d.D + z0) * d.H + y0) * d.W + x0) * cs + (c0 - src.cu);
+        const bool up = c0 < src.cu;
+        if (up != up_now) {
+            up_now = up;
+            x_offsets(up);
+        }
+        const int sh = up ? 1 : 0, cs = up ? src.cu : Ci - src.cu;
+        const int Di = d.D >> sh, Hi = d.H >> sh, Wi = d.W >> sh;
+        const bf *const base = (up ? src.low + c0 : src.in + (c0 - src.cu)) +
+                               (((long long)(b * Di + (z0 >> sh) - 1) * Hi + (y0 >> sh) - 1) * Wi + (x0 >> sh) - 1) * cs;
         const bool interior = x0 >= 1 && x0 + FC_X < d.W && y0 >= 1 && y0 + FC_Y < d.H && z0 >= 1 &&
-                              z0 + FC_Z < d.D;
-        if (c0 < src.cu) {  // upsampled channels: voxel (x, y, z) reads low at (x/2, y/2, z/2)
-            const int Dl = d.D >> 1, Hl = d.H >> 1, Wl = d.W >> 1;
+                              z0 + Tile::Z < d.D;
 #pragma unroll
-            for (int k = 0; k < FC_XITERS; ++k) {
-                uint4 v = make_uint4(0, 0, 0, 0);
-                int hx, hy, hz;
-                halo_of(k, hx, hy, hz);
-                const int x = x0 + hx - 1, y = y0 + hy - 1, z = z0 + hz - 1;
-                if (tid + k * FC_THREADS < FC_XITEMS && x >= 0 && x < d.W && y >= 0 &&
-                    y < d.H && z >= 0 && z < d.D) {
-                    const int l = ((b * Dl + (z >> 1)) * Hl + (y >> 1)) * Wl + (x >> 1);
-                    v = *reinterpret_cast<const uint4 *>(src.low + size_t(l) * src.cu + c0 +
-                                                         (tid & 1) * 8);
-                }
-                xv[k] = v;
+        for (int k = 0; k < Tile::ITERS; ++k) {
+            uint32_t o = xoff[k];
+            int hx, hy, hz;
+            halo_of(k, hx, hy, hz);
+            if (!interior) {
+                if (uint32_t(x0 + hx - 1) >= uint32_t(d.W) || uint32_t(y0 + hy - 1) >= uint32_t(d.H) ||
+                    uint32_t(z0 + hz - 1) >= uint32_t(d.D))
+                    o = kOutside;
             }
-        } else if (interior) {  // the whole halo is inside the volume
-#pragma unroll
-            for (int k = 0; k < FC_XITERS; ++k)
-                if (tid + k * FC_THREADS < FC_XITEMS)
-                    xv[k] = *reinterpret_cast<const uint4 *>(base + rel[k]);
-        } else {
-#pragma unroll
-            for (int k = 0; k < FC_XITERS; ++k) {
-                uint4 v = make_uint4(0, 0, 0, 0);
-                int hx, hy, hz;
-                halo_of(k, hx, hy, hz);
-                const int x = x0 + hx - 1, y = y0 + hy - 1, z = z0 + hz - 1;
-                if (tid + k * FC_THREADS < FC_XITEMS && x >= 0 && x < d.W && y >= 0 &&
-                    y < d.H && z >= 0 && z < d.D)
-                    v = *reinterpret_cast<const uint4 *>(base + rel[k]);
-                xv[k] = v;
-            }
+            if ((Tile::LOADS * 64 > Tile::PIECES) && k == Tile::ITERS - 1 && hz >= Tile::HZ)
+                o = kOutside;  // the last wave load's tail
+            if (wv + 4 * k < Tile::LOADS)
+                load_to_lds<kDirect>(base, t.x + (wv + 4 * k) * 512, lane, o);
         }
         if (!with_w)
             return;
 #pragma unroll
-        for (int k = 0; k < WITERS; ++k)  // [tap][co][2 x 8 ch]
-            wt[k] = wrow[k] >= 0 ? *reinterpret_cast<const uint4 *>(w + size_t(wrow[k]) + c0)
-                                 : make_uint4(0, 0, 0, 0);
-    };
-    auto store_round = [&](bool with_w) {
-#pragma unroll
-        for (int k = 0; k < FC_XITERS; ++k) {
-            const int i = tid + k * FC_THREADS;
-            if (i < FC_XITEMS)
-                *reinterpret_cast<uint4 *>(xs + fc_slot(i >> 1, i & 1, (i >> 1) % FC_HX)) = xv[k];
-        }
-        if (!with_w)
-            return;
-#pragma unroll
-        for (int k = 0; k < WITERS; ++k) {
-            const int i = tid + k * FC_THREADS;
-            if (i < WITEMS)
-                *reinterpret_cast<uint4 *>(ws + fc_slot(i >> 1, i & 1, (i >> 1) % 16)) = wt[k];
-        }
+        for (int k = 0; k < FC_WITERS(NCO); ++k)  // [tap][co][2 x 8 ch]
+            if (wv + 4 * k < FC_WLOADS(NCO))
+                load_to_lds<kDirect>(w + c0, t.w + (wv + 4 * k) * 512, lane, woff[k]);
     };
 
     // LDS operand addresses of this lane: the weight rows of tap 2 p + h are
-    // wa + (2 p NCO + j) 256 for channel tile j; the input row of tap 2 p + h
-    // for the wave's first brick row is bp[p] (the others follow at
-    // FC_HX rows each).
-    const bf *wa = ws + fc_slot(h * NCO * 16 + col, part, col);
-    const bf *bp[14];
+    // wa + (2 p NCO + j) 256 for channel tile j; the input operand of each kind
+    // for the wave's first halo row is at[kind] (the others follow at FC_ROW
+    // each, planes at FC_HY FC_ROW).
+    Tile &t0 = tiles[kg][0];
+    const bf *wa = t0.w + fc_slot(h * NCO * 16 + col, part, col);
+    auto x_at = [&](int dx, int hy, int hz) {
+        return t0.x + fc_slot(((wv * RZ + hz) * FC_HY + hy) * FC_HX + col + dx, part, col + dx);
+    };
+    const bf *at[4 + RZ];
+    at[0] = x_at(h, 0, 0);
+    at[1] = x_at(1 + h, 0, 0);
+    at[2] = h ? x_at(0, 1, 0) : x_at(2, 0, 0);
+    at[3] = h ? x_at(0, 0, 1) : x_at(2, 2, 0);
 #pragma unroll
-    for (int pr = 0; pr < 14; ++pr) {
-        const int t = 2 * pr + h;
-        const int dx = t % 3 - 1, dy = (t / 3) % 3 - 1, dz = t / 9 - 1;
-        const int hx = col + 1 + dx;
-        const int hv = ((wv + 1 + dz) * FC_HY + (1 + dy)) * FC_HX + hx;
-        bp[pr] = t < 27 ? xs + fc_slot(hv, part, hx) : zs;
-    }
+    for (int rz = 0; rz < RZ; ++rz)
+        at[4 + rz] = h ? t0.zero : x_at(2, 2, rz + 2);
 
-    f4 acc[4][NCO];
+    f4 acc[NR4][NCO];
 #pragma unroll
-    for (int rr = 0; rr < 4; ++rr)
+    for (int rr = 0; rr < NR4; ++rr)
 #pragma unroll
         for (int j = 0; j < NCO; ++j)
             acc[rr][j] = f4{0.f, 0.f, 0.f, 0.f};
-    double sq = 0.0;  // LOSS: this lane's sum of squared errors
+    double sq = 0.0;  // kLoss: this lane's sum of squared errors
+    f4 bj[NCO];       // without a bias -0, which leaves every sum as it is
+#pragma unroll
+    for (int j = 0; j < NCO; ++j)
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            bj[j][k] = bias ? bias[co0 + j * 16 + kq * 4 + k] : -0.f;
 
-    for (int i = tid; i < NCO * 16 * 16 / 8; i += FC_THREADS)
-        reinterpret_cast<uint4 *>(ws + 27 * NCO * 16 * 16)[i] = make_uint4(0, 0, 0, 0);
-    for (int i = tid; i < FC_ZERO / 8; i += FC_THREADS)
-        reinterpret_cast<uint4 *>(zs)[i] = make_uint4(0, 0, 0, 0);
+    for (int q = 0; q < NBUF; ++q) {
+        if (FC_WLOADS(NCO) * 512 <= 27 * NCO * 256)  // else the last wave load writes zeros there
+            for (int i = tid; i < NCO * 16 * 16 / 8; i += FC_THREADS)
+                reinterpret_cast<uint4 *>(tiles[kg][q].w + 27 * NCO * 16 * 16)[i] = make_uint4(0, 0, 0, 0);
+        else
+            for (int i = tid + FC_WLOADS(NCO) * 64 - 27 * NCO * 32; i < NCO * 16 * 16 / 8; i += FC_THREADS)
+                reinterpret_cast<uint4 *>(tiles[kg][q].w + 27 * NCO * 16 * 16)[i] = make_uint4(0, 0, 0, 0);
+        for (int i = tid; i < FC_ZERO / 8; i += FC_THREADS)
+            reinterpret_cast<uint4 *>(tiles[kg][q].zero)[i] = make_uint4(0, 0, 0, 0);
+    }
     const BrickWalk bw = brick_walk(nbricks);
     const int NR = (R + KS - 1) / KS;  // steps per brick; group kg takes round kg + KS step
     const int nitems = bw.count * NR;  // (brick, step) pairs of this block
     auto round_of = [&](int it) { return kg + KS * (it % NR); };
-    if (nitems > 0 && round_of(0) < R)
-        load_round(bw.first, round_of(0) * 16, true);
-    int b = 0, x0 = 0, y0 = 0, z0 = 0;
+    auto load_item = [&](int it) {
+        if (it < nitems && round_of(it) < R)
+            load_round(bw.first + (it / NR) * bw.stride, round_of(it) * 16, tiles[kg][NBUF > 1 ? it & 1 : 0],
+                       !w_once || it < NBUF);
+    };
+    load_item(0);
+    wait_loads();
     for (int item = 0; item < nitems; ++item) {
         const int step = item % NR, round = round_of(item);
         const bool active = round < R;  // false for a group left without a round (R % KS != 0)
-        if (step == 0)
-            brick_at(bw.first + (item / NR) * bw.stride, b, x0, y0, z0);
-        __syncthreads();  // the previous round's operands are no longer read
-        if (active)
-            store_round(!w_once || item == 0);
-        __syncthreads();
-        if (item + 1 < nitems && round_of(item + 1) < R)
-            load_round(bw.first + ((item + 1) / NR) * bw.stride, round_of(item + 1) * 16, !w_once);
-        // LOSS: this lane's targets (its 4 rows, channels kq 4 ..) are loaded
-        // before the last round's products, so their latency overlaps them
-        float tg[4][4];
-        if constexpr (LOSS) {
-            if (round + 1 == R) {
+        const bool last = step + 1 == NR;
+        int b, x0, y0, z0;
+        brick_at(bw.first + (item / NR) * bw.stride, b, x0, y0, z0);
+        // The wave's rows of this brick: voxel row0(rr) + col; rows outside the volume have an empty range, lanes outside it an
+        // offset out of range.
+        const int z = z0 + wv * RZ;
+        const bool xin = x0 + col < d.W;
+        auto row0 = [&](int rr) {
+            return ((long long)(b * d.D + z + rr / 4) * d.H + (y0 + rr % 4)) * d.W + x0;
+        };
+        auto range = [&](int rr) { return z + rr / 4 < d.D && y0 + rr % 4 < d.H ? int(kRange) : 0; };
+
+        __syncthreads();  // this item's tiles are in LDS
+        // What the epilogue reads is loaded ahead of the products.
+        constexpr bool kReads = kOut == kLoss || kOut == kGate;
+        static_assert(!kReads || RZ == 1, "8 rows leave no registers for them");
+        uint32_t tg[kOut == kLoss ? NR4 : 1][4];
+        v2u zg[kOut == kGate ? NR4 : 1][NCO];
+        if (kReads && last && kg == 0) {
 #pragma unroll
-                for (int rr = 0; rr < 4; ++rr) {
-                    const int g = wv * 4 + rr;
-                    const int x = x0 + col, y = y0 + g % FC_Y, z = z0 + g / FC_Y;
-                    const bool ok = x < d.W && y < d.H && z < d.D;
-                    const size_t p = ok ? size_t(((b * d.D + z) * d.H + y) * d.W + x) : 0;
+            for (int rr = 0; rr < NR4; ++rr) {
+                if constexpr (kOut == kLoss) {
+                    const auto r = buffer_of(ls.target + row0(rr) * ls.K, range(rr));
 #pragma unroll
-                    for (int k = 0; k < 4; ++k)
-                        tg[rr][k] = ok && kq * 4 + k < ls.K ? ls.target[p * ls.K + kq * 4 + k] : 0.f;
-                }
-            }
-        }
-        // 14 tap pairs (27 taps and a zero tap), each a K = 32 product.  At 3
-        // waves per SIMD the register budget holds one operand set; at 2 the
-        // next pair's operands are read from LDS while the current pair's
-        // products run (two register sets, the scheduling barriers keep the
-        // reads ahead of the products).
-        if constexpr (fc_waves(NCO, LOSS, KS) == 3) {
-#pragma unroll
-            for (int pr = 0; pr < 14; ++pr) {
-                if (!active)
-                    break;
-                bf8v a[NCO];
-#pragma unroll
-                for (int jj = 0; jj < NCO; ++jj)
-                    a[jj] = *reinterpret_cast<const bf8v *>(wa + (2 * pr * NCO + jj) * 256);
-#pragma unroll
-                for (int rr = 0; rr < 4; ++rr) {
-                    const bf8v bv = *reinterpret_cast<const bf8v *>(bp[pr] + rr * FC_HX * 16);
-#pragma unroll
-                    for (int jj = 0; jj < NCO; ++jj)
-                        acc[rr][jj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[jj], bv, acc[rr][jj], 0, 0, 0);
-                }
-            }
-        } else if (active) {
-            bf8v a[2][NCO], bv[2][4];
-            auto read_pr = [&](int pr, int k) {
-#pragma unroll
-                for (int jj = 0; jj < NCO; ++jj)
-                    a[k][jj] = *reinterpret_cast<const bf8v *>(wa + (2 * pr * NCO + jj) * 256);
-#pragma unroll
-                for (int rr = 0; rr < 4; ++rr)
-                    bv[k][rr] = *reinterpret_cast<const bf8v *>(bp[pr] + rr * FC_HX * 16);
-            };
-            read_pr(0, 0);
-#pragma unroll
-            for (int pr = 0; pr < 14; ++pr) {
-                if (pr + 1 < 14)
-                    read_pr(pr + 1, (pr + 1) & 1);
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int rr = 0; rr < 4; ++rr)
-#pragma unroll
-                    for (int jj = 0; jj < NCO; ++jj)
-                        acc[rr][jj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[pr & 1][jj], bv[pr & 1][rr],
-                                                                              acc[rr][jj], 0, 0, 0);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        }
-        if (step + 1 < NR)
-            continue;  // more input channels of this brick to accumulate
-        if constexpr (KS > 1) {
-            if (kg > 0)
-#pragma unroll
-                for (int rr = 0; rr < 4; ++rr)
+                    for (int k = 0; k < 4; ++k) {
+                        const int c = co0 + kq * 4 + k;
+                        tg[rr][k] = __builtin_amdgcn_raw_buffer_load_b32(
+                            r, xin && c < ls.K ? uint32_t(col * ls.K + c) * 4 : kOutside, 0, 0);
+                    }
+                } else if constexpr (kOut == kGate) {
 #pragma unroll
                     for (int j = 0; j < NCO; ++j)
-                        red[(((kg - 1) * 4 + rr) * NCO + j) * FC_THREADS + tid] = acc[rr][j];
+                        zg[rr][j] = load_vec<kDirect>(ep.gate + row0(rr) * Co + co0, range(rr),
+                                                      xin ? uint32_t(col * Co + j * 16 + kq * 4) * 2 : kOutside);
+                }
+            }
+        }
+        if (NBUF > 1)
+            load_item(item + 1);
+        const int boff = NBUF > 1 ? (item & 1) * int(sizeof(Tile) / sizeof(bf)) : 0;
+        // 14 tap pairs (27 taps and a zero tap), each a K = 32 product.
+        // Each input operand is read at its first use and kept for the later ones.
+        if (active) {
+            constexpr FirstUse<RZ> first;
+            bf8v wv8[kAhead ? 2 : 1][NCO], v[3][RZ + 2][FC_HY], v1[NR4];
+            auto read_pair = [&](int pr) {
+                const int kd = TapPairs::kind[pr], dz = TapPairs::dz[pr], dy = TapPairs::dy[pr];
+#pragma unroll
+                for (int jj = 0; jj < NCO; ++jj)
+                    wv8[kAhead ? pr & 1 : 0][jj] = *reinterpret_cast<const bf8v *>(wa + boff + (2 * pr * NCO + jj) * 256);
+#pragma unroll
+                for (int rr = 0; rr < NR4; ++rr) {
+                    const int z = rr / 4, y = rr % 4;
+                    if (kd == 3)
+                        v1[rr] = *reinterpret_cast<const bf8v *>(at[3] + boff + (z * FC_HY + y) * FC_ROW);
+                    else if (kd == 4)
+                        v1[rr] = *reinterpret_cast<const bf8v *>(at[4 + z] + boff + y * FC_ROW);
+                    else if (first.pair[kd][z + dz][y + dy] == pr)
+                        v[kd][z + dz][y + dy] =
+                            *reinterpret_cast<const bf8v *>(at[kd] + boff + ((z + dz) * FC_HY + y + dy) * FC_ROW);
+                }
+            };
+            // With two waves per SIMD the next pair's operands are read while the
+            // current pair's products run (the scheduling barriers keep the reads
+            // ahead of the products); more waves cover the reads by themselves.
+            if (kAhead)
+                read_pair(0);
+#pragma unroll
+            for (int pr = 0; pr < 14; ++pr) {
+                const int kd = TapPairs::kind[pr], dz = TapPairs::dz[pr], dy = TapPairs::dy[pr];
+                bf8v bv[NR4];
+                if (!kAhead)
+                    read_pair(pr);
+#pragma unroll
+                for (int rr = 0; rr < NR4; ++rr)
+                    bv[rr] = kd < 3 ? v[kd][rr / 4 + dz][rr % 4 + dy] : v1[rr];
+                if (kAhead) {
+                    if (pr + 1 < 14)
+                        read_pair(pr + 1);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+#pragma unroll
+                for (int rr = 0; rr < NR4; ++rr)
+#pragma unroll
+                    for (int jj = 0; jj < NCO; ++jj)
+                        acc[rr][jj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv8[kAhead ? pr & 1 : 0][jj], bv[rr],
+                                                                              acc[rr][jj], 0, 0, 0);
+                if (kAhead)
+                    __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        if constexpr (NBUF == 1) {
+            // The next item's loads are on their way while this brick's results
+            // are finished and stored, and are waited for but not the stores.
+            if constexpr (kReads)  // the epilogue's operands have arrived: no wait for them after these loads
+#pragma unroll
+                for (int rr = 0; rr < NR4; ++rr) {
+                    if constexpr (kOut == kLoss)
+                        asm volatile("" : "+v"(tg[rr][0]), "+v"(tg[rr][1]), "+v"(tg[rr][2]), "+v"(tg[rr][3]));
+                    else
+                        for (int j = 0; j < NCO; ++j)
+                            asm volatile("" : "+v"(zg[rr][j]));
+                }
+            __syncthreads();  // this item's tiles are no longer read
+            load_item(item + 1);
+        }
+        if (!last) {  // more input channels of this brick to accumulate
+            wait_loads();
+            continue;
+        }
+        if constexpr (KS > 1) {
+            const int cur = item & 1;
+            auto red = [&](int g, int rr, int j) -> f4 & {
+                return reinterpret_cast<f4 *>(tiles[g][cur].x)[(rr * NCO + j) * FC_THREADS + tid];
+            };
+            __syncthreads();  // the round's operands are no longer read
+            if (kg > 0)
+#pragma unroll
+                for (int rr = 0; rr < NR4; ++rr)
+#pragma unroll
+                    for (int j = 0; j < NCO; ++j)
+                        red(kg, rr, j) = acc[rr][j];
             __syncthreads();
             if (kg == 0)
                 for (int g = 1; g < KS; ++g)
 #pragma unroll
-                    for (int rr = 0; rr < 4; ++rr)
+                    for (int rr = 0; rr < NR4; ++rr)
 #pragma unroll
                         for (int j = 0; j < NCO; ++j)
-                            acc[rr][j] += red[(((g - 1) * 4 + rr) * NCO + j) * FC_THREADS + tid];
+                            acc[rr][j] += red(g, rr, j);
         }
-        f4 bj[NCO];
+        asm volatile("" ::: "memory");  // no store moves ahead of the loads
+        if (kg == 0) {
 #pragma unroll
-        for (int j = 0; j < NCO; ++j) {
-            const int cb = co0 + j * 16 + kq * 4;
-            bj[j] = f4{0.f, 0.f, 0.f, 0.f};
-            if (bias)
-                bj[j] = f4{bias[cb], bias[cb + 1], bias[cb + 2], bias[cb + 3]};
-        }
+            for (int rr = 0; rr < NR4; ++rr) {
+                const int rows = range(rr);
+                const long long p = row0(rr);
 #pragma unroll
-        for (int rr = 0; rr < 4; ++rr) {
-        const int g = wv * 4 + rr;
-        const int x = x0 + col, y = y0 + g % FC_Y, z = z0 + g / FC_Y;
-        if (kg > 0 || x >= d.W || y >= d.H || z >= d.D)
-            continue;
-        const size_t p = size_t(((b * d.D + z) * d.H + y) * d.W + x);
+                for (int j = 0; j < NCO; ++j) {
+                    const int cb = j * 16 + kq * 4;  // from co0: this lane's 4 consecutive output channels
+                    const f4 v = acc[rr][j] + bj[j];
+                    if constexpr (kOut == kF32 || kOut == kLoss) {
+                        float *const o = reinterpret_cast<float *>(out);
+                        store_vec<kDirect>(o + p * Co + co0, o ? rows : 0, __builtin_bit_cast(v4u, v),
+                                           xin ? uint32_t(col * Co + cb) * 4 : kOutside);
+                    }
+                    if constexpr (kOut == kLoss) {
+                        float gv[4];
 #pragma unroll
-        for (int j = 0; j < NCO; ++j) {
-            const int cb = co0 + j * 16 + kq * 4;  // 4 consecutive output channels
-            f4 v = acc[rr][j];
-            if (bias)
-                v += bj[j];
-            if constexpr (LOSS) {
-                if (out)
-                    *reinterpret_cast<f4 *>(reinterpret_cast<float *>(out) + p * Co + cb) = v;
-                float gv[4];
+                        for (int k = 0; k < 4; ++k) {
+                            gv[k] = 0.f;
+                            if (xin && rows && co0 + cb + k < ls.K) {
+                                const float e = v[k] - __uint_as_float(tg[rr][k]);
+                                sq += double(e) * e;
+                                gv[k] = 2.f * e * ls.scale;
+                            }
+                        }
+                        store_vec<kDirect>(ls.grad + p * Co + co0, rows,
+                                           v2u{uint32_t(f2bf(gv[0])) | (uint32_t(f2bf(gv[1])) << 16),
+                                               uint32_t(f2bf(gv[2])) | (uint32_t(f2bf(gv[3])) << 16)},
+                                           xin ? uint32_t(col * Co + cb) * 2 : kOutside);
+                    }
+                    if constexpr (kOut == kBf16 || kOut == kAct || kOut == kGate) {
+                        bf o[4] = {f2bf(v[0]), f2bf(v[1]), f2bf(v[2]), f2bf(v[3])};
+                        if constexpr (kOut == kAct) {
+                            const v2u pa{
+                                uint32_t(f2bf(silu_f(bf2f(o[0])))) | (uint32_t(f2bf(silu_f(bf2f(o[1])))) << 16),
+                                uint32_t(f2bf(silu_f(bf2f(o[2])))) | (uint32_t(f2bf(silu_f(bf2f(o[3])))) << 16)};
+                            store_vec<kDirect>(ep.act + p * Co + co0, rows, pa,
+                                               xin ? uint32_t(col * Co + cb) * 2 : kOutside);
+                        }
+                        if constexpr (kOut == kGate) {
+                            const v2u q = zg[rr][j];
+                            const bf zz[4] = {bf(q.x & 0xffffu), bf(q.x >> 16), bf(q.y & 0xffffu), bf(q.y >> 16)};
 #pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    gv[k] = 0.f;
-                    if (cb + k < ls.K) {
-                        const float e = v[k] - tg[rr][k];
-                        sq += double(e) * e;
-                        gv[k] = 2.f * e * ls.scale;
+                            for (int k = 0; k < 4; ++k)
+                                o[k] = f2bf(silu_grad_f(bf2f(o[k]), bf2f(zz[k])));
+                        }
+                        // a channel tile lies on one side of the split
+                        const bool two = ep.split > 0 && co0 + j * 16 >= ep.split;
+                        const int cs = two ? Co - ep.split : ep.split > 0 ? ep.split : Co;
+                        bf *const t = (two ? ep.out2 - ep.split : reinterpret_cast<bf *>(out)) + co0 + j * 16;
+                        store_vec<kDirect>(t + p * cs, rows,
+                                           v2u{uint32_t(o[0]) | (uint32_t(o[1]) << 16),
+                                               uint32_t(o[2]) | (uint32_t(o[3]) << 16)},
+                                           xin ? uint32_t(col * cs + kq * 4) * 2 : kOutside);
                     }
                 }
-                *reinterpret_cast<uint2 *>(ls.grad + p * Co + cb) =
-                    make_uint2(uint32_t(f2bf(gv[0])) | (uint32_t(f2bf(gv[1])) << 16),
-                               uint32_t(f2bf(gv[2])) | (uint32_t(f2bf(gv[3])) << 16));
-                continue;
             }
-            if (out_f32) {
-                *reinterpret_cast<f4 *>(reinterpret_cast<float *>(out) + p * Co + cb) = v;
-                continue;
-            }
-            bf o[4] = {f2bf(v[0]), f2bf(v[1]), f2bf(v[2]), f2bf(v[3])};
-            if (ep.act) {
-                const uint2 pa = make_uint2(
-                    uint32_t(f2bf(silu_f(bf2f(o[0])))) | (uint32_t(f2bf(silu_f(bf2f(o[1])))) << 16),
-                    uint32_t(f2bf(silu_f(bf2f(o[2])))) | (uint32_t(f2bf(silu_f(bf2f(o[3])))) << 16));
-                *reinterpret_cast<uint2 *>(ep.act + p * Co + cb) = pa;
-            }
-            if (ep.gate) {
-                const uint2 zg = *reinterpret_cast<const uint2 *>(ep.gate + p * Co + cb);
-                const bf zz[4] = {bf(zg.x & 0xffffu), bf(zg.x >> 16), bf(zg.y & 0xffffu), bf(zg.y >> 16)};
-#pragma unroll
-                for (int k = 0; k < 4; ++k)
-                    o[k] = f2bf(silu_grad_f(bf2f(o[k]), bf2f(zz[k])));
-            }
-            const uint2 pk = make_uint2(uint32_t(o[0]) | (uint32_t(o[1]) << 16),
-                                        uint32_t(o[2]) | (uint32_t(o[3]) << 16));
-            if (ep.split > 0 && cb >= ep.split)
-                *reinterpret_cast<uint2 *>(ep.out2 + p * (Co - ep.split) + (cb - ep.split)) = pk;
-            else
-                *reinterpret_cast<uint2 *>(reinterpret_cast<bf *>(out) + p * (ep.split > 0 ? ep.split : Co) +
-                                           cb) = pk;
         }
-        }
+        // All but this brick's stores (every lane's, also those out of range).
+        constexpr int kStores = NR4 * NCO * (kOut == kAct || kOut == kLoss ? 2 : 1);
+        if constexpr (NBUF == 1 && kDirect)
+            wait_loads<kStores>();
+        else
+            wait_loads();
 #pragma unroll
-        for (int rr = 0; rr < 4; ++rr)
+        for (int rr = 0; rr < NR4; ++rr)
 #pragma unroll
             for (int j = 0; j < NCO; ++j)
                 acc[rr][j] = f4{0.f, 0.f, 0.f, 0.f};
     }
-    if constexpr (LOSS) {
+    if constexpr (kOut == kLoss) {
         __shared__ double lred[FC_THREADS / 64];
         for (int o = 32; o > 0; o >>= 1)
             sq += __shfl_xor(sq, o);
@@ -642,29 +794,7 @@ __device__ __forceinline__ bf8v read_rows(const bf *row0, const bf *row1)
     return __builtin_bit_cast(bf8v, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
-// 16 bytes per lane from element `offset` of base into lds + 16 lane; zeros
-// where the offset is kOutside.  kFar: byte offsets may exceed 32 bits.
-constexpr uint32_t kRange = 0xffffff00u, kOutside = 0xffffffffu;
-template <bool kFar>
-__device__ __forceinline__ void load_to_lds(const bf *base, bf *lds, int lane, uint32_t offset)
-{
-    using L = __attribute__((address_space(3))) void;
-    if constexpr (kFar) {
-        if (offset == kOutside)
-            *reinterpret_cast<uint4 *>(lds + lane * 8) = make_uint4(0, 0, 0, 0);
-        else
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(base + offset),
-                                             (L *)lds, 16, 0, 0);
-    } else {
-        const auto r = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf *>(base), short(0), int(kRange), 0x00020000);
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (L *)lds, 16, offset == kOutside ? kOutside : 2 * offset, 0, 0,
-                                                 0);
-    }
-}
-// Wait for this wave's loads to LDS (vmcnt 0).
-__device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0f70); }
-
-template <bool kFar>
+template <bool kDirect>
 __global__ __launch_bounds__(64 * WB_WAVES) __attribute__((amdgpu_waves_per_eu(3))) void
 k_conv_wgrad(ConvIn src, const bf *__restrict__ gout, float *__restrict__ gw, float *__restrict__ gb, Dims d,
              int nbx, int nby, int nbz)
@@ -731,7 +861,7 @@ k_conv_wgrad(ConvIn src, const bf *__restrict__ gout, float *__restrict__ gw, fl
                     o = kOutside;
             }
             if (wave + WB_WAVES * k < WB_ILOADS)
-                load_to_lds<kFar>(ib, lds.in + (wave + WB_WAVES * k) * 512, lane, o);
+                load_to_lds<kDirect>(ib, lds.in + (wave + WB_WAVES * k) * 512, lane, o);
         }
 #pragma unroll
         for (int k = 0; k < WB_GITERS; ++k) {
@@ -742,7 +872,7 @@ k_conv_wgrad(ConvIn src, const bf *__restrict__ gout, float *__restrict__ gw, fl
                     o = kOutside;
             }
             if (wave + WB_WAVES * k < WB_GLOADS)
-                load_to_lds<kFar>(gr, lds.go + (wave + WB_WAVES * k) * 512, lane, o);
+                load_to_lds<kDirect>(gr, lds.go + (wave + WB_WAVES * k) * 512, lane, o);
         }
     };
 
@@ -1321,11 +1451,18 @@ lbmx_status check_dims(int B, int D, int H, int W)
     return LBMX_OK;
 }
 
-template <int NCO, bool LOSS = false, int KS = 1>
-void launch_fwd(ConvIn src, const bf *w, const float *bias, void *out, int out_f32, Dims d, hipStream_t s,
-                Epilogue ep, LossEp ls = LossEp{})
+// Whether every pointer is a multiple of 16 bytes (null counts).
+template <class... P>
+bool aligned16(const P *...p)
 {
-    const int nbx = (d.W + FC_X - 1) / FC_X, nby = (d.H + FC_Y - 1) / FC_Y, nbz = (d.D + FC_Z - 1) / FC_Z;
+    return ((reinterpret_cast<uintptr_t>(p) | ... | 0) & 15) == 0;
+}
+
+template <int NCO, int RZ, FcOut kOut, int KS, bool kDirect>
+void launch_fwd_as(ConvIn src, const bf *w, const float *bias, void *out, Dims d, hipStream_t s, Epilogue ep,
+                   LossEp ls = LossEp{})
+{
+    const int nbx = (d.W + FC_X - 1) / FC_X, nby = (d.H + FC_Y - 1) / FC_Y, nbz = (d.D + 4 * RZ - 1) / (4 * RZ);
     const unsigned bricks = unsigned(d.B * nbx * nby * nbz);
     const unsigned groups = unsigned(d.Co / 16 / NCO);
     // One wave of resident blocks, each walking several bricks so that the
@@ -1334,8 +1471,8 @@ void launch_fwd(ConvIn src, const bf *w, const float *bias, void *out, int out_f
     // kept a multiple of 8 for the XCD-aware brick order.
     static const int per_cu = [] {
         int nb = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_conv_fwd<NCO, LOSS, KS>, FC_THREADS * KS,
-                                                         0) != hipSuccess)
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_conv_fwd<NCO, RZ, kOut, KS, kDirect>,
+                                                         FC_THREADS * KS, 0) != hipSuccess)
             nb = 1;
         return nb < 1 ? 1 : nb;
     }();
@@ -1345,12 +1482,23 @@ void launch_fwd(ConvIn src, const bf *w, const float *bias, void *out, int out_f
         cus = 256;
     const unsigned resident = unsigned(per_cu) * unsigned(cus) / groups;
     unsigned grid = std::max(1u, std::min(bricks, resident));
-    if (LOSS)  // one partial sum per block
+    if (kOut == kLoss)  // one partial sum per block
         grid = std::max(1u, std::min(grid, unsigned(ls.npartial) / groups));
     if (grid >= 8)
         grid -= grid % 8;
-    hipLaunchKernelGGL((k_conv_fwd<NCO, LOSS, KS>), dim3(grid, groups), dim3(FC_THREADS * KS), 0, s, src, w,
-                       bias, out, out_f32, d, nbx, nby, nbz, ep, ls);
+    hipLaunchKernelGGL((k_conv_fwd<NCO, RZ, kOut, KS, kDirect>), dim3(grid, groups), dim3(FC_THREADS * KS), 0, s, src, w,
+                       bias, out, d, nbx, nby, nbz, ep, ls);
+}
+
+template <int NCO, int RZ, int KS = 1, bool kDirect = true>
+void launch_fwd(ConvIn src, const bf *w, const float *bias, void *out, int out_f32, Dims d, hipStream_t s,
+                Epilogue ep)
+{
+    const auto run = out_f32   ? launch_fwd_as<NCO, RZ, kF32, KS, kDirect>
+                     : ep.act  ? launch_fwd_as<NCO, RZ, kAct, KS, kDirect>
+                     : ep.gate ? launch_fwd_as<NCO, 1, kGate, KS, kDirect>  // 8 rows leave no registers for the gate
+                               : launch_fwd_as<NCO, RZ, kBf16, KS, kDirect>;
+    run(src, w, bias, out, d, s, ep, LossEp{});
 }
 
 // Rejects planes whose brick-relative element offsets (a few planes of
@@ -1403,19 +1551,37 @@ lbmx_status conv_fwd(ConvIn src, const void *w, const float *bias, void *out, in
     const Dims d{B, D, H, W, Ci, Co};
     const bf *wb = reinterpret_cast<const bf *>(w);
     hipStream_t s = S(stream);
-    // two output channel tiles per block when Co/16 is even (the input tile
-    // is staged once for both), unless that leaves fewer than two blocks per
-    // CU (small grids: more blocks hide more latency)
+    // Two or three output channel tiles per block (the input tile is staged
+    // once for them) where that leaves two blocks per CU (on smaller grids more
+    // blocks hide more latency): batch 4, 16 -> 48 at 64^3 54 us with one, 47 with
+    // three.  Bricks of 8 planes with one tile from four blocks per CU on and as
+    // far as 32-bit offsets over their halo go: 16 -> 16 at 64^3 29.1 -> 26.8 us,
+    // 48 -> 16 59 -> 52, but at 32^3 10.8 -> 11.8, and with a gate, whose loads no
+    // register is free for during the products, 29.7 -> 31.3 (with two tiles the
+    // registers spill: no gain).  Two groups per block that split the rounds when
+    // one tile per block leaves at most one block per CU.  Operands that are not
+    // 16-byte aligned take the smallest tile with the same split.
     const long long bricks =
-        (long long)B * ((W + FC_X - 1) / FC_X) * ((H + FC_Y - 1) / FC_Y) * ((D + FC_Z - 1) / FC_Z);
-    // and two groups per block splitting the rounds when even one tile per
-    // block leaves at most one block per CU
-    if ((Co / 16) % 2 == 0 && bricks * (Co / 32) >= 512)
-        launch_fwd<2>(src, wb, bias, out, out_f32, d, s, ep);
-    else if (Ci >= 32 && bricks * (Co / 16) <= 256)
-        launch_fwd<1, false, 2>(src, wb, bias, out, out_f32, d, s, ep);
+        (long long)B * ((W + FC_X - 1) / FC_X) * ((H + FC_Y - 1) / FC_Y) * ((D + 3) / 4);
+    const int tiles = Co / 16;
+    const bool far = 2LL * (4 * 2 + 3) * (H + 1) * (W + 2) * Ci >= (long long)kRange;
+    const bool two = tiles % 2 == 0 && bricks * (tiles / 2) >= 512;
+    const bool split = !two && Ci >= 32 && bricks * tiles <= 256;
+    if (!aligned16(src.in, src.low, wb, reinterpret_cast<bf *>(out), ep.act, ep.gate, ep.out2)) {
+        if (split)
+            launch_fwd<1, 1, 2, false>(src, wb, bias, out, out_f32, d, s, ep);
+        else
+            launch_fwd<1, 1, 1, false>(src, wb, bias, out, out_f32, d, s, ep);
+    } else if (two)
+        launch_fwd<2, 1>(src, wb, bias, out, out_f32, d, s, ep);
+    else if (tiles % 3 == 0 && bricks * (tiles / 3) >= 512)
+        launch_fwd<3, 1>(src, wb, bias, out, out_f32, d, s, ep);
+    else if (split)
+        launch_fwd<1, 1, 2>(src, wb, bias, out, out_f32, d, s, ep);
+    else if (!far && bricks * tiles >= 1024)
+        launch_fwd<1, 2>(src, wb, bias, out, out_f32, d, s, ep);
     else
-        launch_fwd<1>(src, wb, bias, out, out_f32, d, s, ep);
+        launch_fwd<1, 1>(src, wb, bias, out, out_f32, d, s, ep);
     HIP_TRY(hipGetLastError());
     return LBMX_OK;
 }
@@ -1464,8 +1630,11 @@ lbmx_status lbmx_nn_conv3d_mse(const void *in, const void *w, const float *bias,
     if ((st = check_plane(H, W, Ci, "conv3d_mse")) != LBMX_OK)
         return st;
     LossEp ls{target, K, 1.0f / float(double(nvox) * K), reinterpret_cast<bf *>(grad), partial, npartial};
-    launch_fwd<1, true>(ConvIn{reinterpret_cast<const bf *>(in), nullptr, 0}, reinterpret_cast<const bf *>(w),
-                        bias, pred, 1, Dims{B, D, H, W, Ci, Co}, S(stream), Epilogue{}, ls);
+    const ConvIn src{reinterpret_cast<const bf *>(in), nullptr, 0};
+    const bf *const wb = reinterpret_cast<const bf *>(w);
+    const auto run = aligned16(src.in, wb, pred, ls.grad) ? launch_fwd_as<1, 1, kLoss, 1, true>
+                                                          : launch_fwd_as<1, 1, kLoss, 1, false>;
+    run(src, wb, bias, pred, Dims{B, D, H, W, Ci, Co}, S(stream), Epilogue{}, ls);
     HIP_TRY(hipGetLastError());
     return LBMX_OK;
 }
@@ -1627,10 +1796,10 @@ lbmx_status conv_wgrad(ConvIn src, const void *gout, float *gw, float *gb, int32
     const long long span = 2LL * (WB_HZ + 1) * (H + 1) * (W + 2) * (Ci > Co ? Ci : Co);
     const dim3 blocks{unsigned(gx), unsigned(pairs)}, threads{64 * WB_WAVES};
     const bf *const g = reinterpret_cast<const bf *>(gout);
-    if (span < (long long)kRange)
-        hipLaunchKernelGGL(k_conv_wgrad<false>, blocks, threads, 0, S(stream), src, g, gw, gb, d, nbx, nby, nbz);
-    else
+    if (span < (long long)kRange && aligned16(src.in, src.low, g))
         hipLaunchKernelGGL(k_conv_wgrad<true>, blocks, threads, 0, S(stream), src, g, gw, gb, d, nbx, nby, nbz);
+    else
+        hipLaunchKernelGGL(k_conv_wgrad<false>, blocks, threads, 0, S(stream), src, g, gw, gb, d, nbx, nby, nbz);
     HIP_TRY(hipGetLastError());
     return LBMX_OK;
 }

@@ -85,3 +85,99 @@ def test_weight_gradient_planes_beyond_32_bit_offsets():
     assert np.all(err <= 2e-5 * bound + 1e-6), err.max()
     gsum = g.double().sum((0, 1, 2, 3)).cpu().numpy()
     assert np.all(np.abs(gb.cpu().numpy() - gsum) <= 2e-5 * g.double().abs().sum((0, 1, 2, 3)).cpu().numpy() + 1e-6)
+
+
+def forward(x, w, b, kind, gate=None, split=0):
+    """Outputs of the forward convolution: FP32, BF16, with its SiLU, times SiLU' at gate, or split."""
+    import torch
+    from paper_1511_04633_amd import unet
+    B, D, H, W, ci = x.shape
+    co = w.shape[0]
+    new = lambda c, t=torch.bfloat16: torch.full((B, D, H, W, c), 7.0, dtype=t, device="cuda")
+    out = new(split or co, torch.float32 if kind == "f32" else torch.bfloat16)
+    act = new(co) if kind == "act" else None
+    out2 = new(co - split) if split else None
+    p = unet.P
+    if kind == "f32":
+        unet.call("lbmx_nn_conv3d_fwd", p(x), p(w), p(b), p(out), 1, B, D, H, W, ci, co, unet.stream_ptr())
+    else:
+        unet.call("lbmx_nn_conv3d_fwd_ep", p(x), p(w), p(b), p(out), p(act), p(gate), p(out2), split, B, D, H, W,
+                  ci, co, unet.stream_ptr())
+    torch.cuda.synchronize()
+    return [t for t in (out, act, out2) if t is not None]
+
+
+# voxel counts on both sides of every tile choice: two and three channel tiles, bricks of
+# 8 planes (whole, one plane and one row more, x and y remainders), several rounds of channels
+@pytest.mark.parametrize("shape,ci,co", [
+    ((1, 64, 32, 64), 16, 32), ((1, 61, 33, 65), 48, 32), ((1, 64, 32, 64), 32, 48), ((2, 33, 31, 66), 16, 48),
+    ((1, 64, 64, 64), 16, 16), ((1, 65, 61, 67), 48, 16), ((4, 57, 36, 33), 32, 16), ((1, 72, 64, 49), 16, 80)])
+def test_forward_tile_choices(shape, ci, co):
+    print(f"case: forward tiles {shape} {ci}->{co}", flush=True)
+    x, w, b = rnd(shape + (ci,), 31), rnd((co, 27, ci), 32), np.random.default_rng(33).standard_normal(co)
+    tx, tw = to_bf(x), to_bf(w)
+    import torch
+    tb = torch.tensor(b.astype(np.float32)).cuda()
+    r = np.random.default_rng(34)
+    edge = [[0, 0, 0, 0], [shape[0] - 1, *(n - 1 for n in shape[1:])]]
+    pts = np.concatenate([edge, np.stack([r.integers(0, n, 4000) for n in shape], 1)])
+    z8 = pts[r.integers(0, len(pts), 500)]
+    z8[:, 1] = (z8[:, 1] // 8 * 8 + 7 * r.integers(0, 2, 500)).clip(0, shape[1] - 1)  # first and last planes of bricks
+    pts = np.concatenate([pts, z8])
+    b32 = b.astype(np.float32).astype(np.float64)
+    ref = N.conv3d_at(x, w, b32, pts)
+    bound = 2e-5 * N.conv3d_at(np.abs(x), np.abs(w), np.abs(b32), pts) + 1e-6
+    at = tuple(torch.tensor(pts.T).cuda())
+    f32, = forward(tx, tw, tb, "f32")
+    assert np.all(np.abs(f32[at].double().cpu().numpy() - ref) <= bound)
+    # the other outputs are roundings of the same sums
+    z, a = forward(tx, tw, tb, "act")
+    assert torch.equal(z, f32.to(torch.bfloat16))
+    assert torch.equal(forward(tx, tw, tb, "plain")[0], z)
+    s = torch.nn.functional.silu(z.float())
+    assert torch.all((a.float() - s).abs() <= 2 ** -8 * s.abs() + 1e-6)
+    gate = to_bf(rnd(shape + (co,), 35))
+    q = gate.double()
+    sg = torch.sigmoid(q)
+    want = z.double() * sg * (1 + q * (1 - sg))
+    got = forward(tx, tw, tb, "gate", gate)[0].double()
+    assert torch.all((got - want).abs() <= 2 ** -8 * want.abs() + 1e-5 * z.double().abs() + 1e-6)
+    if co > 16:
+        lo, hi = forward(tx, tw, tb, "split", split=16)
+        assert torch.equal(torch.cat([lo, hi], -1), z)
+
+
+@pytest.mark.parametrize("shape,ci,co", [((1, 9, 10, 17), 32, 16), ((1, 24, 20, 40), 16, 32)])
+def test_operands_off_16_bytes_give_the_same(shape, ci, co):
+    """Views that start 2 bytes (FP32 output: 4) off a 16-byte boundary."""
+    import torch
+    from paper_1511_04633_amd import unet
+    print(f"case: misaligned {shape} {ci}->{co}", flush=True)
+
+    def off(t):
+        flat = torch.empty(t.numel() + 1, dtype=t.dtype, device="cuda")
+        flat[1:] = t.flatten()
+        return flat[1:].view(t.shape)
+
+    x, w = to_bf(rnd(shape + (ci,), 41)), to_bf(rnd((co, 27, ci), 42))
+    b = to_bf(rnd((co,), 43)).float()
+    gate = to_bf(rnd(shape + (co,), 44))
+    for kind, g in (("f32", None), ("act", None), ("gate", gate), ("plain", None)):
+        for p, q in zip(forward(x, w, b, kind, g), forward(off(x), off(w), b, kind, None if g is None else off(g))):
+            assert torch.equal(p, q), kind
+    gw, gb = wgrad(x, gate)
+    for o in (wgrad(off(x), gate), wgrad(x, off(gate))):
+        assert torch.allclose(o[0], gw, rtol=1e-4, atol=1e-2) and torch.allclose(o[1], gb, rtol=1e-4, atol=1e-2)
+    K = 3
+    tgt = torch.randn(shape + (K,), device="cuda")
+    res = []
+    for f in (lambda t: t, off):
+        pred, grad = f(torch.zeros(shape + (co,), device="cuda")), f(torch.zeros_like(gate))
+        part = torch.zeros(4096, dtype=torch.float64, device="cuda")
+        xx, ww = f(x), f(w)
+        unet.call("lbmx_nn_conv3d_mse", unet.P(xx), unet.P(ww), unet.P(b), unet.P(tgt), K, unet.P(grad),
+                  unet.P(part), 4096, unet.P(pred), *shape, ci, co, unet.stream_ptr())
+        torch.cuda.synchronize()
+        res.append((pred.clone(), grad.clone(), part.sum().item()))
+    assert torch.equal(res[0][0], res[1][0]) and torch.equal(res[0][1], res[1][1])
+    assert abs(res[0][2] - res[1][2]) <= 1e-12 * res[0][2]
