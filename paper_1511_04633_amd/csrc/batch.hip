@@ -59,6 +59,7 @@ struct lbmx_batch {
     int gsteps = 0;
     uint32_t gtiles = 0;
     int cus = 256;
+    Staging staging;
 };
 
 namespace {
@@ -626,7 +627,7 @@ lbmx_status lbmx_batch_read_macro(lbmx_batch *b, int32_t k, double *rho, double 
     lbmx_status s = check(b, k);
     if (s != LBMX_OK)
         return s;
-    return LBMX_DISPATCH(b->storage, macro_to_host, view_of(b, k), rho, ux, uy, uz, theta);
+    return LBMX_DISPATCH(b->storage, macro_to_host, view_of(b, k), b->staging, rho, ux, uy, uz, theta);
 }
 
 lbmx_status lbmx_batch_resample(lbmx_batch *b, int32_t k, int32_t out_n, float *host_uvwt)
@@ -638,20 +639,21 @@ lbmx_status lbmx_batch_resample(lbmx_batch *b, int32_t k, int32_t out_n, float *
         return fail(LBMX_EINVAL, "need host_uvwt != NULL and 1 <= out_n <= 1024");
     const int n = b->p[k].n;
     const size_t cells = size_t(n) * n * n, mc = size_t(out_n) * out_n * out_n;
-    DevBuf fields, outb;
-    HIP_TRY(hipMalloc(&fields.p, 4 * cells * sizeof(double)));
-    HIP_TRY(hipMalloc(&outb.p, 4 * mc * sizeof(float)));
-    double *fd = reinterpret_cast<double *>(fields.p);
-    s = LBMX_DISPATCH(b->storage, launch_macro, view_of(b, k), nullptr, fd, fd + cells, fd + 2 * cells,
-                      fd + 3 * cells);
+    // the fields are staged in the spare lattice, and the result behind them if it fits
+    const View v = view_of(b, k);
+    const size_t fields = 4 * cells * sizeof(double), result = 4 * mc * sizeof(float);
+    DevBuf outb;
+    if (v.spare_bytes < fields + result)
+        HIP_TRY(hipMalloc(&outb.p, result));
+    double *fd = reinterpret_cast<double *>(v.spare);
+    float *const od = reinterpret_cast<float *>(outb.p ? outb.p : v.spare + fields);
+    s = LBMX_DISPATCH(b->storage, launch_macro, v, nullptr, fd, fd + cells, fd + 2 * cells, fd + 3 * cells);
     if (s != LBMX_OK)
         return s;
-    hipLaunchKernelGGL(k_resample, dim3(unsigned((mc + 255) / 256)), dim3(256), 0, b->stream, fd, n, 4,
-                       reinterpret_cast<float *>(outb.p), out_n);
+    hipLaunchKernelGGL(k_resample, dim3(unsigned((mc + 255) / 256)), dim3(256), 0, b->stream, fd, n, 4, od, out_n);
     HIP_TRY(hipGetLastError());
-    HIP_TRY(hipMemcpyAsync(host_uvwt, outb.p, 4 * mc * sizeof(float), hipMemcpyDeviceToHost, b->stream));
-    HIP_TRY(hipStreamSynchronize(b->stream));
-    return LBMX_OK;
+    const HostCopy copy{host_uvwt, od, result};
+    return copies_to_host(b->stream, b->staging, &copy, 1);
 }
 
 lbmx_status lbmx_batch_set_launch(lbmx_batch *b, int32_t block, int32_t grid, int32_t graph_steps)

@@ -74,6 +74,7 @@ struct lbmx_cavity {
     // saving and using the cavity as a source return LBMX_ESTATE until an
     // initialisation succeeds.
     bool failed;
+    Staging staging;
 };
 
 namespace {
@@ -449,7 +450,7 @@ lbmx_status lbmx_get_populations(lbmx_cavity *h, double *f_host, double *g_host)
     lbmx_status s = check_handle(h);
     if (s != LBMX_OK)
         return s;
-    return LBMX_DISPATCH(h->p.storage, pops_to_host, view(h), f_host, g_host);
+    return LBMX_DISPATCH(h->p.storage, pops_to_host, view(h), h->staging, f_host, g_host);
 }
 
 lbmx_status lbmx_save(lbmx_cavity *h, const char *path)
@@ -682,7 +683,7 @@ lbmx_status lbmx_read_macro(lbmx_cavity *h, double *rho, double *ux, double *uy,
     lbmx_status s = check_handle(h);
     if (s != LBMX_OK)
         return s;
-    return LBMX_DISPATCH(h->p.storage, macro_to_host, view(h), rho, ux, uy, uz, theta);
+    return LBMX_DISPATCH(h->p.storage, macro_to_host, view(h), h->staging, rho, ux, uy, uz, theta);
 }
 
 lbmx_status lbmx_nusselt(lbmx_cavity *h, lbmx_nu *out, double *map_host)

@@ -1,0 +1,59 @@
+"""Large results travel to the host in chunks by several threads: each array
+equals the same array read alone, which is copied in one piece."""
+import ctypes
+import threading
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def alone(cav, k):
+    """Field k of the five, read without the others."""
+    from paper_1511_04633_amd import lbmx
+    out = np.full(cav.n ** 3, np.nan)
+    ptr = [None] * 5
+    ptr[k] = out.ctypes.data_as(ctypes.POINTER(ctypes.c_double))
+    assert lbmx.load().lbmx_read_macro(cav._h, *ptr) == 0
+    return out.reshape((cav.n,) * 3)
+
+
+def started(n, storage, seed):
+    from paper_1511_04633_amd import lbmx
+    cav = lbmx.Cavity(n=n, wall_type=1, ra=1e5, storage=storage)
+    cav.init_rest(np.random.default_rng(seed).uniform(-0.5, 0.5, n ** 3))
+    cav.step(3)
+    return cav
+
+
+# below and above the size from which threads copy; chunks that end inside an array
+@pytest.mark.parametrize("n,storage", [(74, "f32"), (75, "f32"), (76, "f64"), (97, "f16_i16"), (128, "f32")])
+def test_fields_and_populations(n, storage):
+    print(f"case: readback n={n} {storage}", flush=True)
+    cav = started(n, storage, n)
+    for _ in range(2):  # the first read allocates the staging memory
+        for k, a in enumerate(cav.read_macro()):
+            assert np.array_equal(a, alone(cav, k)), k
+    f, g = cav.get_populations()
+    rho = f.reshape(19, n, n, n).sum(0)
+    assert np.allclose(rho, alone(cav, 0), rtol=0, atol=1e-12 * 19)
+    assert np.allclose(g.reshape(7, n, n, n).sum(0), alone(cav, 4), rtol=0, atol=1e-12 * 7)
+
+
+def test_handles_read_from_several_threads():
+    print("case: readback from four threads", flush=True)
+    cavs = [started(75 + k, "f32", k) for k in range(4)]
+    got = [None] * 4
+
+    def read(k):
+        got[k] = cavs[k].read_macro()
+
+    ts = [threading.Thread(target=read, args=(k,)) for k in range(4)]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join()
+    for k, c in enumerate(cavs):
+        for q in range(5):
+            assert np.array_equal(got[k][q], alone(c, q)), (k, q)
