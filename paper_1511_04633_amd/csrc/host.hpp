@@ -618,11 +618,22 @@ lbmx_status rest_from_host(const View &v, const double *theta0_host)
     return LBMX_OK;
 }
 
+// State from sampled fields (SourceFields, SourceTwoFields), staged at the
+// nodes in the spare lattice.
+template <class St, class Src>
+lbmx_status unstream_sampled(const View &v, const Src &src, bool density)
+{
+    const size_t cells = (size_t)v.n * v.n * v.n;
+    double *nodes = reinterpret_cast<double *>(v.spare);
+    hipLaunchKernelGGL(k_sample<Src>, plane_grid(v.n), dim3(256), 0, v.stream, nodes, v.n, cells, src);
+    return launch_unstream<St>(v, SourceNodes{nodes, cells, density});
+}
+
 template <class St, class E>
 lbmx_status unstream_fields(const View &v, const E *u, const E *w2, const E *w, const E *th,
                             int src_n, double vscale, const E *rho)
 {
-    return launch_unstream<St>(v, SourceFields<E>{u, w2, w, th, src_n, v.n, E(vscale), rho});
+    return unstream_sampled<St>(v, SourceFields<E>{u, w2, w, th, src_n, v.n, E(vscale), rho}, rho != nullptr);
 }
 
 // Device buffer released at scope exit (after the work using it completed:
@@ -697,7 +708,7 @@ inline lbmx_status init_from_state(const View &dst, int32_t dst_storage, const V
 template <class St>
 lbmx_status unstream_two_fields(const View &v, const SourceTwoFields &src)
 {
-    return launch_unstream<St>(v, src);
+    return unstream_sampled<St>(v, src, true);
 }
 
 // dst's state at t = 0 from wa (fields of a) + wb (fields of b): each

@@ -546,13 +546,38 @@ struct SourcePops {
     __device__ double g(int i, int c) const { return buf[(size_t)slot[19 + i] * cells + c]; }
 };
 
+// f = f^eq(rho, u) (Eq. 17) and g = w_T theta (1 + 4 e.u), whose moments are
+// n^eq of Eq. (33), from node fields staged as n^3 doubles each: u, v, w, theta
+// and, unless density is false (rho = 1), rho - 1.
+struct SourceNodes {
+    const double *buf;
+    size_t cells;
+    bool density;
+    __device__ double f(int i, int c) const
+    {
+        const double vel[3] = {buf[c], buf[cells + c], buf[2 * cells + c]};
+        const int e[3] = {ex19(i), ey19(i), ez19(i)};
+        double eu = e[0] * vel[0] + e[1] * vel[1] + e[2] * vel[2];
+        double uu = vel[0] * vel[0] + vel[1] * vel[1] + vel[2] * vel[2];
+        if (!density)
+            return w19(i) * (3.0 * eu + 4.5 * eu * eu - 1.5 * uu);
+        const double dr = buf[4 * cells + c];
+        return w19(i) * (dr + (1.0 + dr) * (3.0 * eu + 4.5 * eu * eu - 1.5 * uu));
+    }
+    __device__ double g(int i, int c) const
+    {
+        const double vel[3] = {buf[c], buf[cells + c], buf[2 * cells + c]}, t = buf[3 * cells + c];
+        const int e[3] = {i == 1 ? 1 : (i == 2 ? -1 : 0), i == 3 ? 1 : (i == 4 ? -1 : 0),
+                          i == 5 ? 1 : (i == 6 ? -1 : 0)};
+        return w7(i) * t * (1.0 + 4.0 * (e[0] * vel[0] + e[1] * vel[1] + e[2] * vel[2]));
+    }
+};
+
 // Velocity / temperature (and optionally density) fields sampled
 // trilinearly from a node-centred src_n^3 grid of element type E (FP32
-// fields from a caller or a network, FP64 fields of another cavity):
-// f = f^eq(rho, u) (Eq. 17; rho = 1 without a density field, otherwise
-// 1 + (rho_src - 1) vscale^2) and
-// g = w_T theta (1 + 4 e.u), whose moments are n^eq of Eq. (33).  The
-// sampled velocities are multiplied by vscale (1 keeps them bitwise).
+// fields from a caller or a network, FP64 fields of another cavity).  The
+// sampled velocities are multiplied by vscale (1 keeps them bitwise) and
+// rho - 1 by vscale^2 (hydrostatic and dynamic pressure go with u_c^2).
 template <class E>
 struct SourceFields {
     const E *u, *v, *w, *th;
@@ -592,27 +617,11 @@ struct SourceFields {
         vel[2] = sample(w, x, y, z) * vscale;
         theta = sample(th, x, y, z);
     }
-    __device__ double f(int i, int c) const
+    __device__ bool density() const { return rho != nullptr; }
+    __device__ double excess(int c) const  // rho - 1
     {
-        double vel[3], t;
-        node(c, vel, t);
-        const int e[3] = {ex19(i), ey19(i), ez19(i)};
-        double eu = e[0] * vel[0] + e[1] * vel[1] + e[2] * vel[2];
-        double uu = vel[0] * vel[0] + vel[1] * vel[1] + vel[2] * vel[2];
-        if (!rho)
-            return w19(i) * (3.0 * eu + 4.5 * eu * eu - 1.5 * uu);
-        // rho - 1 scales with u_c^2 (hydrostatic and dynamic pressure), as u with u_c
         const int x = c % n, y = (c / n) % n, z = c / (n * n);
-        const double dr = (double(sample(rho, x, y, z)) - 1.0) * double(vscale) * double(vscale);
-        return w19(i) * (dr + (1.0 + dr) * (3.0 * eu + 4.5 * eu * eu - 1.5 * uu));
-    }
-    __device__ double g(int i, int c) const
-    {
-        double vel[3], t;
-        node(c, vel, t);
-        const int e[3] = {i == 1 ? 1 : (i == 2 ? -1 : 0), i == 3 ? 1 : (i == 4 ? -1 : 0),
-                          i == 5 ? 1 : (i == 6 ? -1 : 0)};
-        return w7(i) * t * (1.0 + 4.0 * (e[0] * vel[0] + e[1] * vel[1] + e[2] * vel[2]));
+        return (double(sample(rho, x, y, z)) - 1.0) * double(vscale) * double(vscale);
     }
 };
 
@@ -620,7 +629,7 @@ struct SourceFields {
 // cavities): u = wa u_a + wb u_b, theta = wa theta_a + wb theta_b and
 // rho - 1 = wa (rho_a - 1) + wb (rho_b - 1), each sampled trilinearly as by
 // SourceFields (velocities scaled by its vscale, density variations by
-// vscale^2); f = f^eq(rho, u) (Eq. 17) and g = w_T theta (1 + 4 e.u).
+// vscale^2).
 struct SourceTwoFields {
     SourceFields<double> a, b;  // with density fields
     double wa, wb;
@@ -633,26 +642,34 @@ struct SourceTwoFields {
             vel[d] = wa * va[d] + wb * vb[d];
         theta = wa * ta + wb * tb;
     }
-    __device__ double f(int i, int c) const
+    __device__ bool density() const { return true; }
+    __device__ double excess(int c) const
     {
-        double vel[3], t;
-        node(c, vel, t);
-        const double eu = ex19(i) * vel[0] + ey19(i) * vel[1] + ez19(i) * vel[2];
-        const double uu = vel[0] * vel[0] + vel[1] * vel[1] + vel[2] * vel[2];
         const int x = c % a.n, y = (c / a.n) % a.n, z = c / (a.n * a.n);
-        const double dr = wa * (a.sample(a.rho, x, y, z) - 1.0) * a.vscale * a.vscale +
-                          wb * (b.sample(b.rho, x, y, z) - 1.0) * b.vscale * b.vscale;
-        return w19(i) * (dr + (1.0 + dr) * (3.0 * eu + 4.5 * eu * eu - 1.5 * uu));
-    }
-    __device__ double g(int i, int c) const
-    {
-        double vel[3], t;
-        node(c, vel, t);
-        const int e[3] = {i == 1 ? 1 : (i == 2 ? -1 : 0), i == 3 ? 1 : (i == 4 ? -1 : 0),
-                          i == 5 ? 1 : (i == 6 ? -1 : 0)};
-        return w7(i) * t * (1.0 + 4.0 * (e[0] * vel[0] + e[1] * vel[1] + e[2] * vel[2]));
+        return wa * (a.sample(a.rho, x, y, z) - 1.0) * a.vscale * a.vscale +
+               wb * (b.sample(b.rho, x, y, z) - 1.0) * b.vscale * b.vscale;
     }
 };
+
+// The fields of src at every node of plane blockIdx.y, as SourceNodes reads them.
+// Once per node, where each of the 26 populations would sample its own target
+// node: 192^3 from 96^3 3.43 ms in one pass, 0.77 in two (0.15 here, bound by the
+// FP64 interpolation; 0.54 in k_unstream, by the reads of 26 targets from cache).
+template <typename Src>
+__global__ __launch_bounds__(256) void k_sample(double *__restrict__ out, int n, size_t cells, Src src)
+{
+    const int cp = blockIdx.x * blockDim.x + threadIdx.x;
+    if (cp >= n * n)
+        return;
+    const int c = cp + n * n * int(blockIdx.y);
+    double vel[3], t;
+    src.node(c, vel, t);
+    for (int d = 0; d < 3; ++d)
+        out[d * cells + c] = vel[d];
+    out[3 * cells + c] = t;
+    if (src.density())
+        out[4 * cells + c] = src.excess(c);
+}
 
 // "Unstream": write the post-collision lattice P whose pull reproduces S.
 // For population i at node y: if y + e_i is inside, P_i(y) = S_i(y + e_i);
