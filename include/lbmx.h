@@ -433,6 +433,20 @@ lbmx_status lbmx_nn_conv3d_fwd_upcat(const void *low, const void *skip, const vo
                                      void *out, void *act, int32_t B, int32_t D, int32_t H, int32_t W,
                                      int32_t Cu, int32_t Cs, int32_t Co, void *stream);
 
+/* The whole network in one call, for inference: input construction
+ * (lbmx_nn_make_input), `count` encoder levels of two SiLU layers with
+ * levels[l] channels and 2x2x2 pooling between them, the decoder levels, each
+ * reading [upsampled | skip] in place, and the head: pred FP32 [B][m^3][16].
+ * w and b are host arrays of 4 count - 1 device pointers in forward order (w
+ * BF16 [Co][27][Ci]).  Pre-activations are not kept; activations lie in ws,
+ * device memory of lbmx_nn_unet_workspace bytes, 16-byte aligned.  The results
+ * are those of the single calls bit for bit.  EINVAL as the single calls. */
+lbmx_status lbmx_nn_unet_workspace(const int32_t *levels, int32_t count, int32_t B, int32_t m,
+                                   size_t *bytes);
+lbmx_status lbmx_nn_unet_forward(const float *cond, const void *const *w, const float *const *b,
+                                 const int32_t *levels, int32_t count, int32_t B, int32_t m, void *ws,
+                                 float *pred, void *stream);
+
 /* cat [B][2D][2H][2W][Ch + Cs] = [nearest x2 upsampling of h [B][D][H][W][Ch]
  * | skip [B][2D][2H][2W][Cs]] in one pass (lbmx_nn_up2 then lbmx_nn_concat).
  * Ch, Cs multiples of 16. */

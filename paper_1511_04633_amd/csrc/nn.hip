@@ -283,8 +283,9 @@ __device__ __forceinline__ v2u load_vec(const void *base, int range, uint32_t of
 }
 
 // What the convolution writes (Epilogue and LossEp): FP32, BF16 (with or
-// without split), BF16 and its SiLU, BF16 times SiLU' at gate, or the loss.
-enum FcOut { kF32, kBf16, kAct, kGate, kLoss };
+// without split), BF16 and its SiLU, its SiLU alone, BF16 times SiLU' at gate, or
+// the loss.
+enum FcOut { kF32, kBf16, kAct, kSilu, kGate, kLoss };
 
 // Occupancy is register-bound: 4 waves per SIMD for one channel tile, 2 for
 // two and for the loss variant.
@@ -649,9 +650,9 @@ k_conv_fwd(ConvIn src, const bf *__restrict__ w, const float *__restrict__ bias,
                                                uint32_t(f2bf(gv[2])) | (uint32_t(f2bf(gv[3])) << 16)},
                                            xin ? uint32_t(col * Co + cb) * 2 : kOutside);
                     }
-                    if constexpr (kOut == kBf16 || kOut == kAct || kOut == kGate) {
+                    if constexpr (kOut == kBf16 || kOut == kAct || kOut == kSilu || kOut == kGate) {
                         bf o[4] = {f2bf(v[0]), f2bf(v[1]), f2bf(v[2]), f2bf(v[3])};
-                        if constexpr (kOut == kAct) {
+                        if constexpr (kOut == kAct || kOut == kSilu) {
                             const v2u pa{
                                 uint32_t(f2bf(silu_f(bf2f(o[0])))) | (uint32_t(f2bf(silu_f(bf2f(o[1])))) << 16),
                                 uint32_t(f2bf(silu_f(bf2f(o[2])))) | (uint32_t(f2bf(silu_f(bf2f(o[3])))) << 16)};
@@ -665,6 +666,8 @@ k_conv_fwd(ConvIn src, const bf *__restrict__ w, const float *__restrict__ bias,
                             for (int k = 0; k < 4; ++k)
                                 o[k] = f2bf(silu_grad_f(bf2f(o[k]), bf2f(zz[k])));
                         }
+                        if constexpr (kOut == kSilu)
+                            continue;
                         // a channel tile lies on one side of the split
                         const bool two = ep.split > 0 && co0 + j * 16 >= ep.split;
                         const int cs = two ? Co - ep.split : ep.split > 0 ? ep.split : Co;
@@ -1495,7 +1498,8 @@ void launch_fwd(ConvIn src, const bf *w, const float *bias, void *out, int out_f
                 Epilogue ep)
 {
     const auto run = out_f32   ? launch_fwd_as<NCO, RZ, kF32, KS, kDirect>
-                     : ep.act  ? launch_fwd_as<NCO, RZ, kAct, KS, kDirect>
+                     : ep.act  ? out ? launch_fwd_as<NCO, RZ, kAct, KS, kDirect>
+                                     : launch_fwd_as<NCO, RZ, kSilu, KS, kDirect>
                      : ep.gate ? launch_fwd_as<NCO, 1, kGate, KS, kDirect>  // 8 rows leave no registers for the gate
                                : launch_fwd_as<NCO, RZ, kBf16, KS, kDirect>;
     run(src, w, bias, out, d, s, ep, LossEp{});
@@ -1523,14 +1527,15 @@ lbmx_status check_upcat(const ConvIn &src, int32_t D, int32_t H, int32_t W, int3
     return LBMX_OK;
 }
 
+// out may be null where act_only allows it: the activation alone is written.
 lbmx_status conv_fwd(ConvIn src, const void *w, const float *bias, void *out, int32_t out_f32,
                      int32_t B, int32_t D, int32_t H, int32_t W, int32_t Ci, int32_t Co, void *stream,
-                     Epilogue ep)
+                     Epilogue ep, bool act_only = false)
 {
     lbmx_status st = check_dims(B, D, H, W);
     if (st != LBMX_OK)
         return st;
-    if (!src.in || !w || !out)
+    if (!src.in || !w || (!out && !(act_only && ep.act)))
         return fail(LBMX_EINVAL, "conv3d: NULL tensor");
     if (Ci < 16 || Ci % 16 || Ci > 1024 || Co < 16 || Co % 16 || Co > 1024)
         return fail(LBMX_EINVAL, "conv3d: need Ci, Co multiples of 16 in [16, 1024]");
@@ -1586,9 +1591,106 @@ lbmx_status conv_fwd(ConvIn src, const void *w, const float *bias, void *out, in
     return LBMX_OK;
 }
 
+// The U-Net's inference: every launch in order, activations one after another
+// in the workspace (base null: only its size is counted).
+struct UnetPlan {
+    const int32_t *levels;
+    int count, B, m;
+    void *stream;
+    char *base;
+    size_t used = 0;
+
+    bf *take(int r, int c)
+    {
+        char *const p = base ? base + used : nullptr;
+        used += (size_t(B) * r * r * r * c * sizeof(bf) + 255) / 256 * 256;
+        return reinterpret_cast<bf *>(p);
+    }
+    lbmx_status run(const float *cond, const void *const *w, const float *const *b, float *pred)
+    {
+        int q = 0, r = m;
+        lbmx_status st = LBMX_OK;
+        auto layer = [&](ConvIn src, int ci, int co, lbmx_status *s) {
+            bf *const a = take(r, co);
+            if (base && *s == LBMX_OK)
+                *s = conv_fwd(src, w[q], b[q], nullptr, 0, B, r, r, r, ci, co, stream,
+                              Epilogue{a, nullptr, nullptr, 0}, true);
+            ++q;
+            return a;
+        };
+        bf *h = take(r, 16);
+        if (base)
+            st = lbmx_nn_make_input(cond, h, B, m, stream);
+        int ch = 16;
+        bf *skip[8];
+        for (int l = 0; l < count; ++l) {
+            const int c = levels[l];
+            h = layer(ConvIn{h, nullptr, 0}, ch, c, &st);
+            h = layer(ConvIn{h, nullptr, 0}, c, c, &st);
+            ch = c;
+            if (l + 1 < count) {
+                skip[l] = h;
+                bf *const p = take(r / 2, c);
+                if (base && st == LBMX_OK)
+                    st = lbmx_nn_pool2(h, p, B, r, r, r, c, 0, stream);
+                h = p;
+                r /= 2;
+            }
+        }
+        for (int l = count - 2; l >= 0; --l) {
+            const int c = levels[l];
+            r *= 2;
+            h = layer(ConvIn{skip[l], h, ch}, ch + c, c, &st);
+            h = layer(ConvIn{h, nullptr, 0}, c, c, &st);
+            ch = c;
+        }
+        if (base && st == LBMX_OK)
+            st = lbmx_nn_conv3d_fwd(h, w[q], b[q], pred, 1, B, m, m, m, ch, 16, stream);
+        return st;
+    }
+};
+
+lbmx_status check_unet(const int32_t *levels, int32_t count, int32_t B, int32_t m)
+{
+    if (!levels || count < 1 || count > 8 || B < 1 || m < 1 || m > 4096)
+        return fail(LBMX_EINVAL, "unet: need 1 to 8 levels, B >= 1 and 1 <= m <= 4096");
+    for (int l = 0; l < count; ++l)
+        if (levels[l] < 16 || levels[l] % 16 || levels[l] > 1024)
+            return fail(LBMX_EINVAL, "unet: channels must be multiples of 16 in [16, 1024]");
+    return LBMX_OK;
+}
+
 }  // namespace
 
 extern "C" {
+
+lbmx_status lbmx_nn_unet_workspace(const int32_t *levels, int32_t count, int32_t B, int32_t m, size_t *bytes)
+{
+    lbmx_status st = check_unet(levels, count, B, m);
+    if (st != LBMX_OK)
+        return st;
+    if (!bytes)
+        return fail(LBMX_EINVAL, "unet: NULL argument");
+    UnetPlan plan{levels, count, B, m, nullptr, nullptr};
+    st = plan.run(nullptr, nullptr, nullptr, nullptr);
+    *bytes = plan.used;
+    return st;
+}
+
+lbmx_status lbmx_nn_unet_forward(const float *cond, const void *const *w, const float *const *b,
+                                 const int32_t *levels, int32_t count, int32_t B, int32_t m, void *ws,
+                                 float *pred, void *stream)
+{
+    lbmx_status st = check_unet(levels, count, B, m);
+    if (st != LBMX_OK)
+        return st;
+    if (!cond || !w || !b || !ws || !pred)
+        return fail(LBMX_EINVAL, "unet: NULL argument");
+    for (int k = 0; k < 4 * count - 1; ++k)
+        if (!w[k])
+            return fail(LBMX_EINVAL, "unet: layer %d has no weights", k);
+    return UnetPlan{levels, count, B, m, stream, reinterpret_cast<char *>(ws)}.run(cond, w, b, pred);
+}
 
 lbmx_status lbmx_nn_conv3d_fwd(const void *in, const void *w, const float *bias, void *out,
                                int32_t out_f32, int32_t B, int32_t D, int32_t H, int32_t W,

@@ -69,6 +69,10 @@ def nn():
                                   _vp],
             "lbmx_nn_pool2_bwd_gate": [_vp, _vp, _vp, _vp, _i32, _i32, _i32, _i32, _i32, _vp],
             "lbmx_nn_up2_bwd_gate": [_vp, _vp, _vp, _i32, _i32, _i32, _i32, _i32, _vp],
+            "lbmx_nn_unet_workspace": [ctypes.POINTER(_i32), _i32, _i32, _i32,
+                                       ctypes.POINTER(ctypes.c_size_t)],
+            "lbmx_nn_unet_forward": [_vp, ctypes.POINTER(_vp), ctypes.POINTER(_vp), ctypes.POINTER(_i32),
+                                     _i32, _i32, _i32, _vp, _vp, _vp],
             "lbmx_nn_conv3d_flip_many": [_vp, _vp, _i32, ctypes.POINTER(ctypes.c_int64),
                                          ctypes.POINTER(ctypes.c_int32),
                                          ctypes.POINTER(ctypes.c_int32), _vp],
@@ -251,11 +255,29 @@ class UNet:
 
         s = stream_ptr()
         m = self.m
+        if self.fused and not train and self.record is None:
+            return self._infer(cond, B, s)
         cache, h = self._trunk(cond, B)
         pred = torch.empty((B, m ** 3, 16), dtype=torch.float32, device="cuda")
         call("lbmx_nn_conv3d_fwd", P(h), P(self.head.wb), P(self.head.b), P(pred), 1, B, m, m, m,
              self.head.ci, 16, s)
         self._cache = (cache, h, B) if train else None
+        return pred
+
+    def _infer(self, cond, B, s):
+        """forward() without a cache: every launch from one native call."""
+        import torch
+
+        convs = self.convs()
+        levels = (ctypes.c_int32 * len(self.LEVELS))(*self.LEVELS)
+        ptrs = _vp * len(convs)
+        size = ctypes.c_size_t()
+        call("lbmx_nn_unet_workspace", levels, len(levels), B, self.m, ctypes.byref(size))
+        ws = torch.empty(size.value, dtype=torch.uint8, device="cuda")
+        pred = torch.empty((B, self.m ** 3, 16), dtype=torch.float32, device="cuda")
+        call("lbmx_nn_unet_forward", P(cond), ptrs(*[c.wb.data_ptr() for c in convs]),
+             ptrs(*[c.b.data_ptr() for c in convs]), levels, len(levels), B, self.m, P(ws), P(pred), s)
+        self._cache = None
         return pred
 
     def forward_loss(self, cond, B, target, partial, pred=None, K=NOUT):
@@ -595,8 +617,8 @@ def predict_fields(net, log10_ra, wall_type, u_c=1.0):
     m = net.m
     cond = cond_tensor([log10_ra], [wall_type])
     pred = net.forward(cond, 1)
-    sc = torch.tensor(net.scale.cpu().numpy() * np.array([u_c, u_c, u_c, 1.0], np.float32),
-                      device="cuda")
+    sc = net.scale.clone()
+    sc[:3] *= u_c
     out = torch.empty((NOUT, m ** 3), dtype=torch.float32, device="cuda")
     call("lbmx_nn_layout", P(pred), P(out), 1, m ** 3, NOUT, 16, 0, P(sc), stream_ptr())
     torch.cuda.current_stream().synchronize()

@@ -788,3 +788,34 @@ def test_unet_training_reduces_loss():
     hist = unet.train(net, fields, np.array([3.5, 4.0, 5.0, 5.5]), np.array([1, 2, 3, 1]),
                       epochs=40, batch=2, lr=1e-3, augment=False)["loss"]
     assert hist[-1] < 0.2 * hist[0], hist
+
+
+@pytest.mark.parametrize("m,B", [(8, 1), (16, 3), (24, 2), (40, 1), (64, 1), (64, 2)])
+def test_inference_equals_training_forward(m, B):
+    """forward() without a cache (one native call, activations only) gives the
+    predictions of the training forward pass bit for bit, on every stream."""
+    import torch
+    from paper_1511_04633_amd import unet
+    print(f"case: inference m={m} B={B}", flush=True)
+    net = unet.UNet(seed=5, m=m)
+    for c in net.convs():
+        c.b.copy_(torch.linspace(-0.3, 0.3, c.co))
+    cond = unet.cond_tensor([3.5 + 0.4 * k for k in range(B)], [1 + k % 3 for k in range(B)])
+    ref = net.forward(cond, B, train=True).clone()
+    net._cache = None
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(s):
+        other = net.forward(cond, B)
+    s.synchronize()
+    assert torch.equal(net.forward(cond, B), ref) and torch.equal(other, ref)
+
+
+def test_inference_refuses_odd_levels():
+    """A grid whose pooling meets an odd extent is refused as by the single calls."""
+    from paper_1511_04633_amd import lbmx, unet
+    net = unet.UNet(seed=5, m=20)
+    cond = unet.cond_tensor([5.0], [1])
+    for train in (False, True):
+        with pytest.raises(lbmx.LbmxError):
+            net.forward(cond, 1, train=train)
