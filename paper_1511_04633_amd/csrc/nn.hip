@@ -222,18 +222,18 @@ struct LossEp {
     int npartial;
 };
 
-// 16 bytes per lane from element `offset` of base into lds + 16 lane; zeros
-// where the offset is kOutside.  kDirect: straight into LDS (wait_loads), for a
-// 16-byte aligned base and byte offsets below kRange.
+// 16 bytes per lane from `offset` of base into lds + 16 lane; zeros where the
+// offset is kOutside.  kDirect: straight into LDS (wait_loads), for a 16-byte
+// aligned base; the offset is in units of 1 / load_units elements.
 constexpr uint32_t kRange = 0xffffff00u, kOutside = 0xffffffffu;
+constexpr uint32_t load_units(bool direct) { return direct ? 2 : 1; }  // bytes, which must stay below kRange
 template <bool kDirect>
 __device__ __forceinline__ void load_to_lds(const bf *base, bf *lds, int lane, uint32_t offset)
 {
     if constexpr (kDirect) {
         using L = __attribute__((address_space(3))) void;
         const auto r = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf *>(base), short(0), int(kRange), 0x00020000);
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (L *)lds, 16, offset == kOutside ? kOutside : 2 * offset, 0, 0,
-                                                 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (L *)lds, 16, offset, 0, 0, 0);
     } else {
         uint4 v = make_uint4(0, 0, 0, 0);
         if (offset != kOutside)
@@ -241,6 +241,25 @@ __device__ __forceinline__ void load_to_lds(const bf *base, bf *lds, int lane, u
         *reinterpret_cast<uint4 *>(lds + lane * 8) = v;
     }
 }
+
+// Which positions of a tile lie inside the volume: a position's x, y, z are a
+// byte each with the top bit set (tile_pos), and one subtraction from either end
+// of the valid range keeps the top bits of the bytes in it.  Five instructions
+// per position, where the comparisons of positions found anew by division took
+// about 25, a third of the arithmetic of a round at the volume's faces (62 % of
+// the bricks of 64^3).
+constexpr uint32_t kTops = 0x808080u;
+__device__ __forceinline__ uint32_t tile_pos(int x, int y, int z) { return kTops | uint32_t(x | y << 8 | z << 16); }
+struct TileRange {
+    uint32_t lo, hi;
+    // positions from (lx, ly, lz) to (hx, hy, hz), all non-negative; none if hz < 0
+    __device__ __forceinline__ TileRange(int lx, int ly, int lz, int hx, int hy, int hz)
+        : lo(uint32_t(lx | ly << 8 | (hz < 0 ? 127 : lz) << 16)),
+          hi(2 * kTops + uint32_t(min(hx, 127) | min(hy, 127) << 8 | max(min(hz, 127), 0) << 16))
+    {
+    }
+    __device__ __forceinline__ bool has(uint32_t pos) const { return ((pos - lo) & (hi - pos) & kTops) == kTops; }
+};
 // Wait until no more than n of this wave's memory operations are on their way
 // (vmcnt n): its loads to LDS before the last n.
 template <int n = 0>
@@ -248,6 +267,16 @@ __device__ __forceinline__ void wait_loads()
 {
     static_assert(n < 64);
     __builtin_amdgcn_s_waitcnt(0x0f70 | (n & 15) | (n >> 4 << 14));
+}
+
+// A barrier that orders LDS accesses but leaves loads to LDS on their way, where
+// __syncthreads would wait for them (vmcnt 0).
+__device__ __forceinline__ void lds_barrier()
+{
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt 0: this wave's reads of LDS are done
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
 }
 
 typedef uint32_t v2u __attribute__((ext_vector_type(2)));
@@ -364,32 +393,39 @@ k_conv_fwd(ConvIn src, const bf *__restrict__ w, const float *__restrict__ bias,
 
     // This lane's pieces: wave wv runs wave loads j = wv + 4 k; piece i = 64 j +
     // lane fills 16 bytes of LDS row i / 2: the half (i % 2) ^ swizzle bit of that
-    // voxel (weights: of that tap and output channel).  Element offsets from the
-    // voxel before the brick's first one in x, y and z (weights: from w).
+    // voxel (weights: of that tap and output channel).  Offsets from the voxel
+    // before the brick's first one in x, y and z (weights: from w), and positions
+    // in the halo.
+    constexpr uint32_t kUnits = load_units(kDirect);
+    uint32_t xoff[Tile::ITERS], xpos[Tile::ITERS], woff[FC_WITERS(NCO)];
     auto halo_of = [&](int k, int &hx, int &hy, int &hz) {
         const int hv = ((wv + 4 * k) * 64 + lane) >> 1, hrow = hv / FC_HX;
         hx = hv % FC_HX, hy = hrow % FC_HY, hz = hrow / FC_HY;
     };
-    uint32_t xoff[Tile::ITERS], woff[FC_WITERS(NCO)];
     auto x_offsets = [&](bool up) {  // up: voxel (x, y, z) reads low at (x/2, y/2, z/2); brick corners are even
         const int sh = up ? 1 : 0, cs = up ? src.cu : Ci - src.cu;
         const int Hi = d.H >> sh, Wi = d.W >> sh;
 #pragma unroll
         for (int k = 0; k < Tile::ITERS; ++k) {
-            int hx, hy, hz;
-            halo_of(k, hx, hy, hz);
+            const int hx = xpos[k] & 127, hy = (xpos[k] >> 8) & 127, hz = (xpos[k] >> 16) & 127;
             const int half = (lane & 1) ^ ((hx >> 2) & 1);
             xoff[k] = uint32_t((((hz - 1) >> sh) + 1) * Hi + ((hy - 1) >> sh) + 1) * Wi + uint32_t(((hx - 1) >> sh) + 1);
-            xoff[k] = xoff[k] * uint32_t(cs) + uint32_t(half * 8);
+            xoff[k] = kUnits * (xoff[k] * uint32_t(cs) + uint32_t(half * 8));
         }
     };
+#pragma unroll
+    for (int k = 0; k < Tile::ITERS; ++k) {
+        int hx, hy, hz;
+        halo_of(k, hx, hy, hz);
+        xpos[k] = hz < Tile::HZ ? tile_pos(hx, hy, hz) : 0u;  // the last wave load's tail is never inside
+    }
     bool up_now = src.cu > 0;
     x_offsets(up_now);
 #pragma unroll
     for (int k = 0; k < FC_WITERS(NCO); ++k) {
         const int row = ((wv + 4 * k) * 64 + lane) >> 1, tap = row / (NCO * 16), co = row % (NCO * 16);
         const int half = (lane & 1) ^ ((co >> 2) & 1);
-        woff[k] = tap < 27 ? uint32_t(((co0 + co) * 27 + tap) * Ci + half * 8) : kOutside;
+        woff[k] = tap < 27 ? kUnits * uint32_t(((co0 + co) * 27 + tap) * Ci + half * 8) : kOutside;
     }
 
     // With one round per brick (Ci = 16) the weights are the same for every
@@ -407,23 +443,11 @@ k_conv_fwd(ConvIn src, const bf *__restrict__ w, const float *__restrict__ bias,
         const int Di = d.D >> sh, Hi = d.H >> sh, Wi = d.W >> sh;
         const bf *const base = (up ? src.low + c0 : src.in + (c0 - src.cu)) +
                                (((long long)(b * Di + (z0 >> sh) - 1) * Hi + (y0 >> sh) - 1) * Wi + (x0 >> sh) - 1) * cs;
-        const bool interior = x0 >= 1 && x0 + FC_X < d.W && y0 >= 1 && y0 + FC_Y < d.H && z0 >= 1 &&
-                              z0 + Tile::Z < d.D;
+        const TileRange inside(x0 == 0, y0 == 0, z0 == 0, d.W - x0, d.H - y0, d.D - z0);
 #pragma unroll
-        for (int k = 0; k < Tile::ITERS; ++k) {
-            uint32_t o = xoff[k];
-            int hx, hy, hz;
-            halo_of(k, hx, hy, hz);
-            if (!interior) {
-                if (uint32_t(x0 + hx - 1) >= uint32_t(d.W) || uint32_t(y0 + hy - 1) >= uint32_t(d.H) ||
-                    uint32_t(z0 + hz - 1) >= uint32_t(d.D))
-                    o = kOutside;
-            }
-            if ((Tile::LOADS * 64 > Tile::PIECES) && k == Tile::ITERS - 1 && hz >= Tile::HZ)
-                o = kOutside;  // the last wave load's tail
+        for (int k = 0; k < Tile::ITERS; ++k)
             if (wv + 4 * k < Tile::LOADS)
-                load_to_lds<kDirect>(base, t.x + (wv + 4 * k) * 512, lane, o);
-        }
+                load_to_lds<kDirect>(base, t.x + (wv + 4 * k) * 512, lane, inside.has(xpos[k]) ? xoff[k] : kOutside);
         if (!with_w)
             return;
 #pragma unroll
@@ -751,42 +775,45 @@ __global__ __launch_bounds__(256) void k_conv_flip_many(const bf *__restrict__ w
 
 // gw[co][tap][ci] += sum_p gout[p][co] in[p + off(tap)][ci], gb[co] += sum_p gout[p][co].
 //
-// A block owns one (co tile, ci tile) pair (blockIdx.y) and walks bricks of 16 x
-// 8 x 8 voxels in the order of brick_walk.  Per brick it brings the gout tile
-// (1024 voxels of 16 channels) and the input tile with a one-voxel halo (18 x 10
-// x 10 voxels) from memory straight into LDS, channel-last as they lie in
-// memory (buffer loads to LDS; voxels outside the volume are out of the
-// buffer's range and arrive as zeros).  Four teams of three waves take the
-// brick's 16 x 4 x 4 quarters.  The reduction runs over voxels, so both MFMA operands need several voxels of one channel
-// per lane: ds_read_b64_tr_b16 transposes on the way out of LDS (lane layout
-// checked on the device: 16 voxels of 16 channels, 512 consecutive bytes read
-// at lane * 8, give lane l channel l % 16 of voxels 4 (l / 16) .. + 3).  K = 32
+// A block owns one (co tile, ci tile) pair (blockIdx.y) and a range of the chunks
+// of 16 x 8 x 4 voxels, in the order of columns along z.  Down a column it keeps
+// rings of plane groups in LDS, channel-last as they lie in memory: four groups
+// of four input planes of 18 x 10 voxels (planes 4 k - 1 .. 4 k + 2: chunk c reads
+// group c and the first two planes of c + 1) and three of four gout planes.  While
+// it computes on chunk c, what chunks c + 1 and c + 2 need travels from memory
+// straight into LDS (buffer loads to LDS; voxels outside the volume are
+// out of the buffer's range and arrive as zeros); one barrier per chunk.
+// The reduction runs over voxels, so both MFMA operands need several voxels of one
+// channel per lane: ds_read_b64_tr_b16 transposes on the way out of LDS (lane
+// layout checked on the device: 16 voxels of 16 channels, 512 consecutive bytes
+// read at lane * 8, give lane l channel l % 16 of voxels 4 (l / 16) .. + 3).  K = 32
 // of v_mfma_f32_16x16x32_bf16 is two rows of 16 voxels, one read each, so any
 // tap's operand is two reads at lane * 8 plus a constant, and the inner loop is
 // LDS reads and MFMAs only.
-// Wave dx of a team accumulates the 9 taps of its x offset: it holds the row
-// pairs of gout in registers and reads the 5 row pairs (Y, Y + 1) of each halo
-// plane once; a row pair serves every (dy, dz) it lies at: 72 products for 76
+// Four teams of three waves take two of the chunk's rows in y each; wave dx of a
+// team accumulates the 9 taps of its x offset: it holds the row pairs of gout of
+// the four planes in registers and reads the 3 row pairs (Y, Y + 1) of each of 6
+// input planes once; a row pair serves every dz it lies at: 36 products for 22
 // reads.  Wave 0 also accumulates the bias gradient against ones.  At the end
 // the teams' sums meet in LDS and the block adds them to gw / gb atomically,
 // each block from another place on.
-// Bound by the chain load, wait, products of a brick (one block's 90 KB tile per
-// CU) and by the 256 blocks' atomic adds to the same elements (6 us at 64^3).
-// Batch 4: 64^3 16 -> 16 51.5 us (bricks transposed through registers, two
-// 4-wave blocks per CU) -> 31.1, 48 -> 16 86 -> 53, 32^3 96 -> 32 48.8 -> 34.9,
-// 16^3 64 -> 64 19.3 -> 14.6, 8^3 64 -> 96 11.9 -> 9.3.  Two blocks of half the
-// brick per CU overlap loads and products but add twice the atomics: 42 us.
+// Bound by the block's fixed part (launch, first loads, the teams' sums: 10 us)
+// and the blocks' atomic adds to the same elements (4 us of 28 at 64^3), then by
+// loads and products, which overlap (loads alone 21 us, products alone 24).  Batch
+// 4, bricks transposed through registers -> loaded whole into LDS -> streamed down
+// columns, us: 64^3 16 -> 16 51.5 -> 31 -> 28, 48 -> 16 86 -> 53 -> 52, 32^3 96 -> 32 49
+// -> 35 -> 31, 16^3 160 -> 64 33 -> 30 -> 19, 64 -> 64 19.3 -> 14.6 -> 14.
 // Element indices are 32-bit (the host checks B D H W C < 2^31 and the plane
 // extents).
-constexpr int WB_X = 16, WB_Y = 8, WB_Z = 8, WB_V = WB_X * WB_Y * WB_Z;
-constexpr int WB_HX = WB_X + 2, WB_HY = WB_Y + 2, WB_HZ = WB_Z + 2;
-constexpr int WB_HV = WB_HX * WB_HY * WB_HZ;        // 1800 halo voxels
-constexpr int WB_QY = 4, WB_QZ = 4;                 // a team's part of the brick: 16 x 4 x 4
-constexpr int WB_TEAMS = (WB_Y / WB_QY) * (WB_Z / WB_QZ), WB_WAVES = 3 * WB_TEAMS;
-constexpr int WB_ILOADS = (2 * WB_HV + 63) / 64;    // wave loads of 64 16-byte pieces: input tile
-constexpr int WB_GLOADS = 2 * WB_V / 64;            // and gout tile
+constexpr int WB_X = 16, WB_Y = 8, WB_Z = 4, WB_V = WB_X * WB_Y * WB_Z;
+constexpr int WB_HX = WB_X + 2, WB_HY = WB_Y + 2;
+constexpr int WB_HV = WB_HX * WB_HY * WB_Z;         // 720 voxels of an input group
+constexpr int WB_TEAMS = WB_Y / 2, WB_WAVES = 3 * WB_TEAMS;
+constexpr int WB_ILOADS = 24;                       // wave loads of 64 16-byte pieces: input group (2 per wave)
+constexpr int WB_GLOADS = 2 * WB_V / 64;            // and gout group
 constexpr int WB_IITERS = (WB_ILOADS + WB_WAVES - 1) / WB_WAVES;  // per wave
 constexpr int WB_GITERS = (WB_GLOADS + WB_WAVES - 1) / WB_WAVES;
+static_assert(WB_ILOADS * 64 >= 2 * WB_HV && WB_ILOADS == WB_IITERS * WB_WAVES, "as many for every wave");
 
 // The operand of two rows of 16 voxels: this lane's channel, 4 voxels of each.
 __device__ __forceinline__ bf8v read_rows(const bf *row0, const bf *row1)
@@ -802,10 +829,10 @@ __global__ __launch_bounds__(64 * WB_WAVES) __attribute__((amdgpu_waves_per_eu(3
 k_conv_wgrad(ConvIn src, const bf *__restrict__ gout, float *__restrict__ gw, float *__restrict__ gb, Dims d,
              int nbx, int nby, int nbz)
 {
-    __shared__ __attribute__((aligned(16))) struct {
-        bf in[WB_ILOADS * 64 * 8];
-        bf go[WB_V * 16];
-        bf more[WB_TEAMS * (27 * 256 + 16) * 2 - WB_ILOADS * 64 * 8 - WB_V * 16];  // for the sums
+    constexpr int NSUM = 27 * 256 + 16;
+    __shared__ __attribute__((aligned(16))) union {
+        bf ring[4 * WB_ILOADS * 512 + 3 * WB_GLOADS * 512];
+        float sums[WB_TEAMS * NSUM];
     } lds;
     const int Ci = d.Ci, Co = d.Co;
     const int CIT = Ci / 16;
@@ -813,70 +840,55 @@ k_conv_wgrad(ConvIn src, const bf *__restrict__ gout, float *__restrict__ gw, fl
     const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
     const int team = wave / 3, dx = wave % 3;            // dx: x offset + 1
     const int lane = threadIdx.x & 63;
-    const int nbricks = d.B * nbx * nby * nbz;
     const bool up = it * 16 < src.cu;      // this block's input channels come from src.low
     const bf *const in = up ? src.low : src.in;
     const int cs = up ? src.cu : Ci - src.cu;            // channel stride of `in`
     const int cin = up ? it * 16 : it * 16 - src.cu;     // channel offset in it
 
-    // This lane's pieces: the block's waves w run wave loads j = w + 12 k; piece i = 64 j +
-    // lane is half i % 2 of voxel i / 2 of the halo (or gout) tile.  Byte offsets
-    // from the voxel before the brick's first one in x, y and z (input) and from
-    // the brick's first voxel (gout).
-    const BrickGrid grid(nbx, nby, nbz);
-    auto halo_of = [&](int k, int &hx, int &hy, int &hz) {
-        const int hv = ((wave + WB_WAVES * k) * 64 + lane) >> 1, hrow = hv / WB_HX;
-        hx = hv % WB_HX - 1, hy = hrow % WB_HY - 1, hz = hrow / WB_HY - 1;
-    };
-    const int sh = up ? 1 : 0;  // brick corners are even: (x0 + hx) >> 1 = x0 / 2 + (hx >> 1)
+    // This lane's pieces: wave w runs wave loads j = w + 12 k; piece i = 64 j + lane
+    // is half i % 2 of voxel i / 2 of the group.  Offsets from the voxel before the
+    // chunk's first one in x, y and z (input) and from its first voxel (gout), and
+    // positions in the group.
+    constexpr uint32_t kUnits = load_units(kDirect);
+    const BrickGrid grid(nbx, nby, 1);
+    const int sh = up ? 1 : 0;  // corners are even: (x0 + hx) >> 1 = x0 / 2 + (hx >> 1)
     const int Hi = d.H >> sh, Wi = d.W >> sh, Di = d.D >> sh;
-    uint32_t ioff[WB_IITERS], goff[WB_GITERS];
+    uint32_t ioff[WB_IITERS], ipos[WB_IITERS], goff[WB_GITERS], gpos[WB_GITERS];
 #pragma unroll
     for (int k = 0; k < WB_IITERS; ++k) {
-        int hx, hy, hz;
-        halo_of(k, hx, hy, hz);
-        ioff[k] = uint32_t((((hz >> sh) + 1) * Hi + (hy >> sh) + 1) * Wi + (hx >> sh) + 1) * uint32_t(cs) +
-                  uint32_t(cin + (lane & 1) * 8);
-        if (hz > WB_Z)
-            ioff[k] = kOutside;  // the last wave load's tail
+        const int hv = ((wave + WB_WAVES * k) * 64 + lane) >> 1, hrow = hv / WB_HX;
+        const int hx = hv % WB_HX, hy = hrow % WB_HY, hz = hrow / WB_HY;
+        ioff[k] = kUnits * (uint32_t((((hz - 1) >> sh) + 1) * Hi + ((hy - 1) >> sh) + 1) * Wi + ((hx - 1) >> sh) + 1) *
+                      uint32_t(cs) +
+                  kUnits * uint32_t(cin + (lane & 1) * 8);
+        ipos[k] = hz < WB_Z ? tile_pos(hx, hy, hz) : 0u;  // the last wave load's tail is never inside
     }
 #pragma unroll
     for (int k = 0; k < WB_GITERS; ++k) {
         const int v = ((wave + WB_WAVES * k) * 64 + lane) >> 1;
-        goff[k] = uint32_t(((v >> 7) * d.H + ((v >> 4) & 7)) * d.W + (v & 15)) * uint32_t(Co) +
-                  uint32_t(ct * 16 + (lane & 1) * 8);
+        goff[k] = kUnits * (uint32_t(((v >> 7) * d.H + ((v >> 4) & 7)) * d.W + (v & 15)) * uint32_t(Co) +
+                            uint32_t(ct * 16 + (lane & 1) * 8));
+        gpos[k] = tile_pos(v & 15, (v >> 4) & 7, v >> 7);
     }
-    auto load_brick = [&](int br) {
-        int b, x0, y0, z0;
-        grid.at(br, WB_X, WB_Y, WB_Z, b, x0, y0, z0);
-        const bf *const ib =
-            in + (((long long)(b * Di + (z0 >> sh) - 1) * Hi + (y0 >> sh) - 1) * Wi + (x0 >> sh) - 1) * cs;
-        const bf *const gr = gout + (((long long)(b * d.D + z0) * d.H + y0) * d.W + x0) * Co;
-        const bool inner = x0 >= 1 && x0 + WB_X < d.W && y0 >= 1 && y0 + WB_Y < d.H && z0 >= 1 && z0 + WB_Z < d.D;
+    int b = 0, x0 = 0, y0 = 0;  // the column
+    auto load_input = [&](int k4, bf *to) {  // planes k4 - 1 .. k4 + 2
+        const bf *const base =
+            in + (((long long)(b * Di + (k4 >> sh) - 1) * Hi + (y0 >> sh) - 1) * Wi + (x0 >> sh) - 1) * cs;
+        const TileRange inside(x0 == 0, y0 == 0, k4 == 0, d.W - x0, d.H - y0, d.D - k4);
 #pragma unroll
-        for (int k = 0; k < WB_IITERS; ++k) {
-            uint32_t o = ioff[k];
-            if (!inner) {
-                int hx, hy, hz;
-                halo_of(k, hx, hy, hz);
-                if (uint32_t(x0 + hx) >= uint32_t(d.W) || uint32_t(y0 + hy) >= uint32_t(d.H) ||
-                    uint32_t(z0 + hz) >= uint32_t(d.D))
-                    o = kOutside;
-            }
+        for (int k = 0; k < WB_IITERS; ++k)
             if (wave + WB_WAVES * k < WB_ILOADS)
-                load_to_lds<kDirect>(ib, lds.in + (wave + WB_WAVES * k) * 512, lane, o);
-        }
+                load_to_lds<kDirect>(base, to + (wave + WB_WAVES * k) * 512, lane,
+                                     inside.has(ipos[k]) ? ioff[k] : kOutside);
+    };
+    auto load_gout = [&](int z0, bf *to) {
+        const bf *const base = gout + (((long long)(b * d.D + z0) * d.H + y0) * d.W + x0) * Co;
+        const TileRange inside(0, 0, 0, d.W - 1 - x0, d.H - 1 - y0, d.D - 1 - z0);
 #pragma unroll
-        for (int k = 0; k < WB_GITERS; ++k) {
-            uint32_t o = goff[k];
-            if (!inner) {
-                const int v = ((wave + WB_WAVES * k) * 64 + lane) >> 1;
-                if (x0 + (v & 15) >= d.W || y0 + ((v >> 4) & 7) >= d.H || z0 + (v >> 7) >= d.D)
-                    o = kOutside;
-            }
+        for (int k = 0; k < WB_GITERS; ++k)
             if (wave + WB_WAVES * k < WB_GLOADS)
-                load_to_lds<kDirect>(gr, lds.go + (wave + WB_WAVES * k) * 512, lane, o);
-        }
+                load_to_lds<kDirect>(base, to + (wave + WB_WAVES * k) * 512, lane,
+                                     inside.has(gpos[k]) ? goff[k] : kOutside);
     };
 
     f4 acc[9], accb = f4{0.f, 0.f, 0.f, 0.f};
@@ -885,49 +897,78 @@ k_conv_wgrad(ConvIn src, const bf *__restrict__ gout, float *__restrict__ gw, fl
         acc[t] = f4{0.f, 0.f, 0.f, 0.f};
     const bf8v ones = __builtin_bit_cast(bf8v, make_uint4(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u));
     const bool bias_wave = dx == 0 && gb != nullptr && it == 0;
-    const int qy = team % (WB_Y / WB_QY) * WB_QY, qz = team / (WB_Y / WB_QY) * WB_QZ;  // the team's quarter
-    const bf *const ip = lds.in + ((qz * WB_HY + qy) * WB_HX + dx) * 16 + lane * 4;
-    const bf *const gp = lds.go + (qz * WB_Y + qy) * WB_X * 16 + lane * 4;
+    const int ip = (2 * team * WB_HX + dx) * 16 + lane * 4, gp = 2 * team * WB_X * 16 + lane * 4;
 
-    const BrickWalk bw = brick_walk(nbricks);
-    for (int n = 0; n < bw.count; ++n) {
-        __syncthreads();  // the previous brick's reads are done
-        load_brick(bw.first + n * bw.stride);
-        wait_loads();
-        __syncthreads();
-        bf8v a[2 * WB_QZ];  // rows (z, 2p), (z, 2p + 1) of gout: a[2 z + p]
+    // chunks of this block: a contiguous range; ranges of one XCD are neighbours
+    const int nchunks = d.B * nbx * nby * nbz, G = int(gridDim.x), bx = int(blockIdx.x);
+    const int range = G % 8 == 0 ? bx % 8 * (G / 8) + bx / 8 : bx;
+    const int c0 = int((long long)range * nchunks / G), c1 = int((long long)(range + 1) * nchunks / G);
+    int g0 = 0, q = 0;  // ring places of the chunk's input group and gout group
+    auto in_at = [&](int k) { return ((g0 + k) & 3) * (WB_ILOADS * 512); };
+    auto go_at = [&](int k) { return 4 * WB_ILOADS * 512 + (q + k < 3 ? q + k : q + k - 3) * (WB_GLOADS * 512); };
+    // One chunk.  What arrives and what is read are different places of the ring
+    // between two barriers, which restrict tells the compiler: without it, it
+    // waits for everything on its way before the first transposing read.
+    auto chunk = [&](bf *__restrict__ arrive, const bf *__restrict__ ring, int c) {
+        const int colm = c / nbz, cz = c - colm * nbz, z0 = cz * WB_Z;
+        const int rest = min(c1 - c, nbz - cz);  // chunks left of the range in this column
+        auto load_set = [&](int k) {  // what chunk c + k needs and c + k - 1 does not
+            load_input(z0 + (k + 1) * WB_Z, arrive + in_at(k + 1));
+            load_gout(z0 + k * WB_Z, arrive + go_at(k));
+        };
+        if (c == c0 || cz == 0) {  // a new column
+            int zero;
+            grid.at(colm, WB_X, WB_Y, 1, b, x0, y0, zero);
+            lds_barrier();  // the previous chunk's reads are done
+            load_input(z0, arrive + in_at(0));
+            load_set(0);
+            if (rest > 1)
+                load_set(1);
+        }
+        if (kDirect && rest > 1) {  // all but the next chunk's
+            if (wave < WB_GLOADS - WB_WAVES)
+                wait_loads<WB_IITERS + 2>();
+            else
+                wait_loads<WB_IITERS + 1>();
+        } else {
+            wait_loads();
+        }
+        lds_barrier();
+        if (rest > 2)
+            load_set(2);
+        const bf *const gq = ring + go_at(0) + gp, *const in0 = ring + in_at(0) + ip, *const in1 = ring + in_at(1) + ip;
+        bf8v a[WB_Z];  // the team's two rows of gout plane z
 #pragma unroll
-        for (int Z = 0; Z < WB_QZ + 2; ++Z) {
-            if (Z < WB_QZ)
+        for (int Z = 0; Z < WB_Z + 2; ++Z) {
+            if (Z < WB_Z) {
+                const bf *const row = gq + Z * WB_Y * WB_X * 16;
+                a[Z] = read_rows(row, row + WB_X * 16);
+                if (bias_wave)
+                    accb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[Z], ones, accb, 0, 0, 0);
+            }
+            const bf *const plane = (Z < WB_Z ? in0 : in1) + Z % WB_Z * WB_HY * WB_HX * 16;
 #pragma unroll
-                for (int p = 0; p < 2; ++p) {
-                    const bf *const row = gp + (Z * WB_Y + 2 * p) * WB_X * 16;
-                    a[2 * Z + p] = read_rows(row, row + WB_X * 16);
-                    if (bias_wave)
-                        accb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[2 * Z + p], ones, accb, 0, 0, 0);
-                }
-#pragma unroll
-            for (int Y = 0; Y + 1 < WB_QY + 2; ++Y) {
-                const bf *const row = ip + (Z * WB_HY + Y) * WB_HX * 16;
+            for (int Y = 0; Y < 3; ++Y) {  // dy + 1
+                const bf *const row = plane + Y * WB_HX * 16;
                 const bf8v v = read_rows(row, row + WB_HX * 16);
 #pragma unroll
-                for (int z = 0; z < WB_QZ; ++z)
-#pragma unroll
-                    for (int p = 0; p < 2; ++p) {
-                        const int kz = Z - z, ky = Y - 2 * p;  // dz + 1, dy + 1
-                        if (kz >= 0 && kz < 3 && ky >= 0 && ky < 3)
-                            acc[kz * 3 + ky] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                                a[2 * z + p], v, acc[kz * 3 + ky], 0, 0, 0);
-                    }
+                for (int kz = 0; kz < 3; ++kz)  // dz + 1
+                    if (Z - kz >= 0 && Z - kz < WB_Z)
+                        acc[kz * 3 + Y] =
+                            __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[Z - kz], v, acc[kz * 3 + Y], 0, 0, 0);
             }
         }
-    }
+        g0 = (g0 + 1) & 3;
+        q = q == 2 ? 0 : q + 1;
+    };
+    int none = 0;  // not known to the compiler, which would pass a known address by itself and lose restrict
+    asm volatile("" : "+s"(none));
+    for (int c = c0; c < c1; ++c)
+        chunk(lds.ring + none, lds.ring + none, c);
     // The teams' sums in LDS, each [tap][co][ci] and then the bias; every thread
     // adds its share of their total to the global gradient, blocks starting at
     // different places (from the same one they queue at the same addresses).
-    constexpr int NSUM = 27 * 256 + 16;
-    static_assert(sizeof(lds) >= WB_TEAMS * NSUM * sizeof(float), "room for the sums");
-    float *const red = reinterpret_cast<float *>(&lds);
+    float *const red = lds.sums;
     const int col = lane & 15, kq = lane >> 4;
     __syncthreads();
 #pragma unroll
@@ -1883,19 +1924,23 @@ lbmx_status conv_wgrad(ConvIn src, const void *gout, float *gw, float *gb, int32
     if (nv * (Ci > Co ? Ci : Co) >= (1LL << 31))
         return fail(LBMX_EINVAL, "conv3d_wgrad: tensor of %lld voxels too large", nv);
     const int nbx = (W + WB_X - 1) / WB_X, nby = (H + WB_Y - 1) / WB_Y, nbz = (D + WB_Z - 1) / WB_Z;
-    const long long nbricks = (long long)B * nbx * nby * nbz;
+    const long long nchunks = (long long)B * nbx * nby * nbz;
     const int pairs = (Co / 16) * (Ci / 16);
-    // one block per CU (its LDS and registers) over all channel pairs: every
-    // block adds its sums to the same gradient elements, which costs about 6 us
-    // for 256 blocks, so a second round of blocks would cost more than it hides
     int dev = 0, cus = 256;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
         cus = 256;
-    long long gx = std::min((cus + pairs - 1LL) / pairs, nbricks);
-    if (gx >= 8) gx -= gx % 8;  // x extent a multiple of 8: XCD-aware brick order
-    // byte offsets within a brick's halo planes, from the voxel before its first
-    const long long span = 2LL * (WB_HZ + 1) * (H + 1) * (W + 2) * (Ci > Co ? Ci : Co);
+    // Blocks of one round (a block takes a whole CU, and every block adds its sums
+    // to the same gradient elements) and of two chunks or more,
+    // and where that costs little a multiple of 8 or 2: the blocks of all pairs that
+    // read the same voxels then run on the same XCDs.  Batch 4, 160 -> 64 at 16^3 with
+    // 7 blocks for each of 40 pairs, a second round of blocks, 29.6 us, with 6 19.3;
+    // 32 -> 64 at 16^3 one chunk each 12.1, two 10.4.
+    long long gx = std::min(std::max(1LL, (long long)cus / pairs), (nchunks + 1) / 2);
+    if (gx >= 32) gx -= gx % 8;
+    else if (gx >= 8) gx -= gx % 2;
+    // byte offsets within a group of planes, from the voxel before its first
+    const long long span = 2LL * (WB_Z + 1) * (H + 1) * (W + 2) * (Ci > Co ? Ci : Co);
     const dim3 blocks{unsigned(gx), unsigned(pairs)}, threads{64 * WB_WAVES};
     const bf *const g = reinterpret_cast<const bf *>(gout);
     if (span < (long long)kRange && aligned16(src.in, src.low, g))

@@ -181,3 +181,36 @@ def test_operands_off_16_bytes_give_the_same(shape, ci, co):
         res.append((pred.clone(), grad.clone(), part.sum().item()))
     assert torch.equal(res[0][0], res[1][0]) and torch.equal(res[0][1], res[1][1])
     assert abs(res[0][2] - res[1][2]) <= 1e-12 * res[0][2]
+
+
+# many channel pairs leave few blocks each: long ranges of chunks (the rings wrap several
+# times), ranges that start and end inside a column, several columns per block
+@pytest.mark.parametrize("shape,ci,co", [((1, 30, 9, 17), 256, 256), ((2, 19, 10, 20), 96, 128),
+                                         ((1, 45, 8, 16), 160, 128)])
+def test_weight_gradient_long_ranges(shape, ci, co):
+    print(f"case: wgrad ranges {shape} {ci}->{co}", flush=True)
+    B, D, H, W = shape
+    x, g = rnd((B, D, H, W, ci), 51), rnd((B, D, H, W, co), 52)
+    ref, bound = N.conv3d_wgrad(x, g), N.conv3d_wgrad(np.abs(x), np.abs(g))
+    for a, r, b in zip(wgrad(to_bf(x), to_bf(g)), ref, bound):
+        err = np.abs(a.cpu().numpy() - r)
+        assert np.all(err <= 2e-5 * b + 1e-6), (err.max(), shape)
+
+
+def test_weight_gradient_upsampled_input():
+    """A decoder layer's input read in place, against its concatenation."""
+    import torch
+    from paper_1511_04633_amd import unet
+    B, D, H, W, cu, cs, co = 2, 22, 10, 34, 32, 16, 32
+    print(f"case: wgrad upcat {B}x{D}x{H}x{W} {cu}+{cs}->{co}", flush=True)
+    low, skip, g = rnd((B, D // 2, H // 2, W // 2, cu), 61), rnd((B, D, H, W, cs), 62), rnd((B, D, H, W, co), 63)
+    tl, ts, tg = to_bf(low), to_bf(skip), to_bf(g)
+    gw = torch.zeros((co, 27, cu + cs), device="cuda")
+    gb = torch.zeros(co, device="cuda")
+    unet.call("lbmx_nn_conv3d_wgrad_upcat", unet.P(tl), unet.P(ts), unet.P(tg), unet.P(gw), unet.P(gb), B, D, H, W,
+              cu, cs, co, unet.stream_ptr())
+    torch.cuda.synchronize()
+    x = np.concatenate([N.up2(low), skip], -1)
+    ref, bound = N.conv3d_wgrad(x, g), N.conv3d_wgrad(np.abs(x), np.abs(g))
+    for a, r, b in zip((gw, gb), ref, bound):
+        assert np.all(np.abs(a.cpu().numpy() - r) <= 2e-5 * b + 1e-6)
