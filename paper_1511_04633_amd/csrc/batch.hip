@@ -144,29 +144,34 @@ unsigned grid_blocks(const lbmx_batch *b)
     return unsigned(b->grid);
 }
 
+template <class St, int kForce, int kPolicy>
+void launch_batch_step(lbmx_batch *b)
+{
+    using T = typename St::T;
+    hipLaunchKernelGGL((k_step_batch<St, kForce, kPolicy>), dim3(grid_blocks(b)), dim3(b->block), 0, b->stream,
+                       reinterpret_cast<const BatchCav<T> *>(b->d_cavs), b->d_tiles, b->ntiles, b->parity,
+                       b->d_t + (size_t)b->parity * b->count, b->d_t + (size_t)(b->parity ^ 1) * b->count);
+}
+
 template <class St>
 lbmx_status launch_direct(lbmx_batch *b, int64_t nsteps)
 {
-    using T = typename St::T;
-    const auto *cavs = reinterpret_cast<const BatchCav<T> *>(b->d_cavs);
+    size_t bytes = 0;
+    for (int k = 0; k < b->count; ++k)
+        bytes += b->L[k].lattice;
+    const bool near = near_lattice(bytes, b->storage);
     for (int64_t s = 0; s < nsteps; ++s) {
-        const uint32_t *t_in = b->d_t + (size_t)b->parity * b->count;
-        uint32_t *t_out = b->d_t + (size_t)(b->parity ^ 1) * b->count;
         switch (b->force_model) {
         case LBMX_FORCE_EQ15_RHO:
-            hipLaunchKernelGGL((k_step_batch<St, LBMX_FORCE_EQ15_RHO>), dim3(grid_blocks(b)),
-                               dim3(b->block), 0, b->stream, cavs, b->d_tiles, b->ntiles, b->parity,
-                               t_in, t_out);
+            near ? launch_batch_step<St, LBMX_FORCE_EQ15_RHO, kNear>(b)
+                 : launch_batch_step<St, LBMX_FORCE_EQ15_RHO, kFar>(b);
             break;
         case LBMX_FORCE_GUO:
-            hipLaunchKernelGGL((k_step_batch<St, LBMX_FORCE_GUO>), dim3(grid_blocks(b)),
-                               dim3(b->block), 0, b->stream, cavs, b->d_tiles, b->ntiles, b->parity,
-                               t_in, t_out);
+            near ? launch_batch_step<St, LBMX_FORCE_GUO, kNear>(b) : launch_batch_step<St, LBMX_FORCE_GUO, kFar>(b);
             break;
         default:
-            hipLaunchKernelGGL((k_step_batch<St, LBMX_FORCE_EQ15>), dim3(grid_blocks(b)),
-                               dim3(b->block), 0, b->stream, cavs, b->d_tiles, b->ntiles, b->parity,
-                               t_in, t_out);
+            near ? launch_batch_step<St, LBMX_FORCE_EQ15, kNear>(b)
+                 : launch_batch_step<St, LBMX_FORCE_EQ15, kFar>(b);
         }
         b->parity ^= 1;
     }

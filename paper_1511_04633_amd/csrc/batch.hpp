@@ -38,7 +38,7 @@ struct Tile {
 // tile writes step + 1 to t_out[k], which the next launch (parity 1 - p)
 // reads.  No launch writes what it reads, so a captured graph replays with
 // advancing steps.
-template <class St, int kForce>
+template <class St, int kForce, int kPolicy>
 __global__ __launch_bounds__(1024) void k_step_batch(const BatchCav<typename St::T> *__restrict__ cavs,
                                                      const Tile *__restrict__ tiles, uint32_t ntiles,
                                                      int parity, const uint32_t *__restrict__ t_in,
@@ -66,7 +66,7 @@ __global__ __launch_bounds__(1024) void k_step_batch(const BatchCav<typename St:
         T f[19], g[7];
         pull<St, true>(cv->lat[parity], geo, s, y, f, g);
         collide<T, kForce>(f, g, cv->rates);
-        put<St>(cv->lat[parity ^ 1], s, c, step, geo, f, g);
+        put<St, kPolicy>(cv->lat[parity ^ 1], s, c, step, geo, f, g);
     }
 }
 

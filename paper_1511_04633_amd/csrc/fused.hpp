@@ -44,7 +44,7 @@ __device__ __forceinline__ int xcd_item()
 // One tile of tx x ty x tz nodes per block; step A runs on the tile and its
 // halo (clipped at the walls) with one thread per node, at most NT of them.
 // Bound by launch and memory latency: 16^3 FP32 3.65 us per step with k_step,
-// 2.52 us here; 32^3 4.25 -> 3.0 us.
+// 2.65 us here; 32^3 4.25 -> 3.2 us.
 template <class St, int kForce, int NT>
 __global__ __launch_bounds__(NT) void
 k_step2_tile(const char *__restrict__ src, char *__restrict__ dst, Geometry<typename St::T> geo,
@@ -104,8 +104,8 @@ k_step2_tile(const char *__restrict__ src, char *__restrict__ dst, Geometry<type
     collide<T, kForce>(f, g, rates);
     s.vF += uint32_t(cz) * plane;
     s.vG += uint32_t(cz) * plane;
-    put<St>(dst + size_t(plane) * z0, s,
-            uint32_t(x) + uint32_t(n) * (uint32_t(y) + uint32_t(n) * uint32_t(z)), geo.step + 1u, geo, f, g);
+    put<St, kNear>(dst + size_t(plane) * z0, s,
+                   uint32_t(x) + uint32_t(n) * (uint32_t(y) + uint32_t(n) * uint32_t(z)), geo.step + 1u, geo, f, g);
 }
 
 // ------------------------------------------------------------- large grids
@@ -129,7 +129,7 @@ k_step2_tile(const char *__restrict__ src, char *__restrict__ dst, Geometry<type
 // Bound by HBM and by the memory phases that the barriers keep apart from the
 // arithmetic (vector unit busy about half of the time; 256^3 FP32 reads 1.89 GB
 // for 1.74 GB of lattice).  256^3: FP32 581 -> 382 us per step, FP64 1179 ->
-// 910 us; 128^3 FP32 74 -> 64 us.  64 x 13 tiles rather than 32 x 28 or
+// 773 us; 128^3 FP32 74 -> 63 us.  64 x 13 tiles rather than 32 x 28 or
 // 32 x 13: the rows' end columns cost a memory line each (FP32 256^3 with an
 // earlier alignment: 405, 477 and 430 us); loading the next plane before step A
 // instead spills registers.
@@ -255,9 +255,9 @@ __device__ __forceinline__ void march2(const char *__restrict__ src, char *__res
         }
         pin(raw.f, raw.g);  // the loads have landed: the stores below are waited for by nothing
         if (z > z0 && inB)
-            put<St>(dst + plane * (z - 1), sB,
-                    uint32_t(x0 + bx) + uint32_t(n) * (uint32_t(y0 + by) + uint32_t(n) * uint32_t(z - 1)),
-                    geo.step + 1u, geo, f2, g2);
+            put<St, kFar>(dst + plane * (z - 1), sB,
+                          uint32_t(x0 + bx) + uint32_t(n) * (uint32_t(y0 + by) + uint32_t(n) * uint32_t(z - 1)),
+                          geo.step + 1u, geo, f2, g2);
     }
 }
 
@@ -299,11 +299,12 @@ struct Step2Plan {
 // filled round of blocks counting as a full one: a turn of the 64 x 13 tile
 // took 8.6 to 9.9 us over 96^3 .. 320^3, of two 32 x 13 blocks on one CU 9.6 to
 // 10.5 us (FP64, one block: 9.0 to 11.2 us); where rows do not start on 64-byte
-// boundaries 10.0 to 11.6, 10.8 to 17.8 and 10.9 to 14.3 us.  k_step, at the
-// memory rate it reaches, where that is shorter (FP32: 96^3 33.3 us against
-// 32.7, 136^3 90 against 101; 144^3 106 against 100, 192^3 242 against 183).
+// boundaries 10.0 to 11.6, 10.8 to 17.8 and 10.9 to 14.3 us.  k_step, at the rate
+// it reaches from memory or, `near`, from the memory-side cache, where that is
+// shorter (FP32: 96^3 28.8 us against 32.7, 112^3 50.1 against 49.4; 144^3 106
+// against 100, 192^3 242 against 182; FP64: 88^3 50 against 44).
 template <typename T>
-inline Step2Plan plan_step2(int n, int cus)
+inline Step2Plan plan_step2(int n, int cus, bool near)
 {
     constexpr bool f64 = sizeof(T) == 8;
     auto up = [](int a, int b) { return (a + b - 1) / b; };
@@ -315,7 +316,8 @@ inline Step2Plan plan_step2(int n, int cus)
         return make(Step2Plan::kTile, n, 2, 2);
     if (!f64 && n <= 40)
         return make(Step2Plan::kTile, up(n, 2), 3, 2);
-    const double single = 2.0 + double(n) * n * n * (f64 ? 416.0 / 5.65e6 : 208.0 / 5.95e6);
+    const double rate = f64 ? (near ? 7.0e6 : 5.65e6) : (near ? 6.6e6 : 5.95e6);  // bytes per us
+    const double single = 2.0 + 52.0 * sizeof(T) * double(n) * n * n / rate;
     Step2Plan best = make(Step2Plan::kSingle, 1, 1, 1);
     double best_us = 0.98 * single;
     const bool aligned = n % (f64 ? 8 : 16) == 0;

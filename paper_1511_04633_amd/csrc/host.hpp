@@ -309,6 +309,18 @@ Geometry<typename St::T> geometry(const View &v)
 // blocks of 256.
 inline dim3 plane_grid(int n) { return dim3((unsigned(n) * unsigned(n) + 255) / 256, unsigned(n)); }
 
+// Whether steps write lattices of so many bytes with kNear: where the lattice and
+// most of the other fit the memory-side cache (measured, kNear / kFar us per step:
+// FP32 108^3, 131 MB, 41.8 / 46.7, 120^3 65.0 / 63.8; f16 / i16 128^3, 109 MB, 36 /
+// 39, 144^3 61 / 57), but not FP32 ones that lie in the L2s with the other (48^3, 11.5
+// MB: 6.6 / 6.15; 44^3 4.9 / 5.5, 54^3 7.6 / 8.1).
+inline bool near_lattice(size_t bytes, int32_t storage)
+{
+    if (storage == LBMX_F32 && bytes > (size_t(10) << 20) && bytes < (size_t(14) << 20))
+        return false;
+    return bytes <= (size_t(132) << 20);
+}
+
 constexpr uint32_t kAllPops = (1u << 26) - 1;
 
 template <class St, typename Src>

@@ -260,37 +260,45 @@ __device__ __forceinline__ Buffer make_buffer(const char *base)
 {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(base), short(0), int(0xffffffffu), 0x00020000);
 }
-constexpr int kNonTemporal = 2;  // the nt bit of a buffer instruction
+// Cache policies of the stores.  kNear writes through the XCD's L2 (sc1), so that
+// a kernel's end finds little to write back, and keeps the line in the 256 MB
+// memory-side cache, where the next step reads it if one lattice and most of the
+// other fit.  kFar streams past it (nt; with sc1 for 8- and 2-byte populations,
+// which measured 1 to 8 % faster, 4-byte ones did not).  us per step, nt stores and
+// (FP64) nt loads -> kNear: FP32 64^3 11.8 -> 9.5, 96^3 33.3 -> 28.8, 104^3 41.4 ->
+// 37.4; FP64 50^3 11.6 -> 9.15, 80^3 39 -> 32; f16 / i16 64^3 7.3 -> 6.9, 96^3 20.3 ->
+// 18.3, 128^3 40 -> 36.  Plain stores, written back at the kernel's end: FP32 64^3
+// 9.5, 48^3 6.9 (kNear 6.6), f16 / i16 64^3 8.1.
+constexpr int kNear = 16, kFar = 18;
+template <typename S, int kPolicy>
+constexpr int store_bits() { return kPolicy == kFar && sizeof(typename Codec<S>::Raw) == 4 ? 2 : kPolicy; }
 
 // Loads return the storage bits (Codec<S>::Raw); Codec<S>::dec converts.
-// 8-byte populations (FP64 storage) are read non-temporally (measured 2.5 %
-// faster at 256^3); narrower ones are not (slower: a wavefront's x-shifted
-// reads share cache lines with its neighbours').
+// They are temporal: a wavefront's x-shifted reads share cache lines with its
+// neighbours'.
 template <typename S>
 __device__ __forceinline__ typename Codec<S>::Raw ld(Buffer b, uint32_t lane, uint32_t uniform)
 {
     using R = typename Codec<S>::Raw;
     if constexpr (sizeof(R) == 8) {
         typedef uint32_t u2 __attribute__((ext_vector_type(2)));
-        return __builtin_bit_cast(R, u2(__builtin_amdgcn_raw_buffer_load_b64(b, lane, uniform, kNonTemporal)));
+        return __builtin_bit_cast(R, u2(__builtin_amdgcn_raw_buffer_load_b64(b, lane, uniform, 0)));
     } else if constexpr (sizeof(R) == 4)
         return __builtin_bit_cast(R, __builtin_amdgcn_raw_buffer_load_b32(b, lane, uniform, 0));
     else
         return __builtin_bit_cast(R, __builtin_amdgcn_raw_buffer_load_b16(b, lane, uniform, 0));
 }
-// Stores are non-temporal: the written lattice is read back only in the next
-// step, long after it has left the caches.
-template <typename S>
+template <typename S, int kPolicy>
 __device__ __forceinline__ void st(Buffer b, uint32_t lane, uint32_t uniform, typename Codec<S>::Raw v)
 {
     using R = typename Codec<S>::Raw;
     if constexpr (sizeof(R) == 8) {
         typedef uint32_t u2 __attribute__((ext_vector_type(2)));
-        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, v), b, lane, uniform, kNonTemporal);
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, v), b, lane, uniform, store_bits<S, kPolicy>());
     } else if constexpr (sizeof(R) == 4)
-        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), b, lane, uniform, kNonTemporal);
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), b, lane, uniform, store_bits<S, kPolicy>());
     else
-        __builtin_amdgcn_raw_buffer_store_b16(v, b, lane, uniform, kNonTemporal);
+        __builtin_amdgcn_raw_buffer_store_b16(v, b, lane, uniform, store_bits<S, kPolicy>());
 }
 
 // Bytes of a segment of n^2 elements: whole 128-byte lines, so that a
@@ -450,7 +458,7 @@ __device__ __forceinline__ void pull(const char *__restrict__ base, const Geomet
 
 // Write the 26 populations of node number `node` at `s` (post-collision values
 // of step `step`).
-template <class St>
+template <class St, int kPolicy>
 __device__ __forceinline__ void put(char *__restrict__ base, const Site &s, uint32_t node, uint32_t step,
                                     const Geometry<typename St::T> &geo, const typename St::T f[19],
                                     const typename St::T g[7])
@@ -463,17 +471,17 @@ __device__ __forceinline__ void put(char *__restrict__ base, const Site &s, uint
     const Buffer buf = make_buffer(base);
 #pragma unroll
     for (int i = 0; i < 19; ++i)
-        st<SF>(buf, s.vF, i * pl.segF, Codec<SF>::enc(f[i], T(inv_w19(i))));
+        st<SF, kPolicy>(buf, s.vF, i * pl.segF, Codec<SF>::enc(f[i], T(inv_w19(i))));
     if constexpr (std::is_same<SG, Fix16>::value) {
         const RoundBits rb(node, step);
 #pragma unroll
         for (int i = 0; i < 7; ++i)
-            st<SG>(buf, s.vG, pl.offG + i * pl.segG,
+            st<SG, kPolicy>(buf, s.vG, pl.offG + i * pl.segG,
                    Codec<SG>::enc_r(g[i], T(inv_w7(i)) * geo.inv_escale, rb.u16(i)));
     } else {
 #pragma unroll
         for (int i = 0; i < 7; ++i)
-            st<SG>(buf, s.vG, pl.offG + i * pl.segG, Codec<SG>::enc(g[i], T(inv_w7(i))));
+            st<SG, kPolicy>(buf, s.vG, pl.offG + i * pl.segG, Codec<SG>::enc(g[i], T(inv_w7(i))));
     }
 }
 
@@ -496,7 +504,7 @@ __device__ __forceinline__ uint32_t div_small(uint32_t c, uint32_t n, float inv_
 // n (rows of 300 nodes in blocks of 256 would leave 41 % of the lanes idle);
 // otherwise a block covers (bx, by) nodes over (x, y).  kForce is the force
 // model (LBMX_FORCE_*).
-template <class St, int kForce, bool kFlat>
+template <class St, int kForce, bool kFlat, int kPolicy>
 __global__ __launch_bounds__(1024) void k_step(const char *__restrict__ src, char *__restrict__ dst,
                                                Geometry<typename St::T> geo,
                                                Rates<typename St::T> rates, float inv_n)
@@ -516,7 +524,7 @@ __global__ __launch_bounds__(1024) void k_step(const char *__restrict__ src, cha
     T f[19], g[7];
     pull<St, false>(src + plane, geo, s, y, f, g);
     collide<T, kForce>(f, g, rates);
-    put<St>(dst + plane, s, uint32_t(x) + uint32_t(geo.n) * (uint32_t(y) + uint32_t(geo.n) * z), geo.step,
+    put<St, kPolicy>(dst + plane, s, uint32_t(x) + uint32_t(geo.n) * (uint32_t(y) + uint32_t(geo.n) * z), geo.step,
             geo, f, g);
 }
 
@@ -699,7 +707,7 @@ __global__ __launch_bounds__(256) void k_unstream(char *__restrict__ dst,
         const int tx = x + ex19(i), ty = y + ey19(i), tz = z + ez19(i);
         const bool in = tx >= 0 && tx < n && ty >= 0 && ty < n && tz >= 0 && tz < n;
         double v = in ? srcS.f(i, tx + n * (ty + n * tz)) : srcS.f(opp19(i), c);
-        st<SF>(plane, uint32_t(cp) * pl.bF, i * pl.segF, Codec<SF>::enc(T(v), T(inv_w19(i))));
+        st<SF, kFar>(plane, uint32_t(cp) * pl.bF, i * pl.segF, Codec<SF>::enc(T(v), T(inv_w19(i))));
     }
     const double th_lin = double(geo.theta_hot) +
                           double(geo.theta_cold - geo.theta_hot) * (y + 0.5) / n;
@@ -724,7 +732,7 @@ __global__ __launch_bounds__(256) void k_unstream(char *__restrict__ dst,
             v = dir ? 2.0 * w7(go[i]) * tw - s_in : s_in;
         }
         const T inv_w = St::kScaledG ? T(inv_w7(i)) * geo.inv_escale : T(inv_w7(i));
-        st<SG>(plane, uint32_t(cp) * pl.bG, pl.offG + i * pl.segG, Codec<SG>::enc(T(v), inv_w));
+        st<SG, kFar>(plane, uint32_t(cp) * pl.bG, pl.offG + i * pl.segG, Codec<SG>::enc(T(v), inv_w));
     }
 }
 

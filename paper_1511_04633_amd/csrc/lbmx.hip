@@ -112,7 +112,7 @@ int64_t launch_step_pairs(lbmx_cavity *h, int64_t nsteps, Geometry<typename St::
                           const Rates<typename St::T> &rates)
 {
     using T = typename St::T;
-    const Step2Plan p = plan_step2<T>(h->p.n, h->cus);
+    const Step2Plan p = plan_step2<T>(h->p.n, h->cus, near_lattice(h->L.lattice, h->p.storage));
     if (p.kind == Step2Plan::kSingle)
         return 0;
     auto run = [&](auto kernel, int threads, auto... args) {
@@ -154,15 +154,14 @@ void launch_step_kernels(lbmx_cavity *h, int64_t nsteps)
     const dim3 block = flat ? dim3(kFlatBlock) : dim3(h->bx, h->by);
     const dim3 grid = flat ? dim3((n * n + kFlatBlock - 1) / kFlatBlock, 1, n)
                            : dim3((n + h->bx - 1) / h->bx, (n + h->by - 1) / h->by, n);
+    const bool near = near_lattice(h->L.lattice, h->p.storage);
+    const auto kernel = flat ? (near ? k_step<St, kForce, true, kNear> : k_step<St, kForce, true, kFar>)
+                             : (near ? k_step<St, kForce, false, kNear> : k_step<St, kForce, false, kFar>);
     Geometry<T> g = geo;
     for (int64_t s = 0; s < nsteps; ++s) {
         g.step = uint32_t(h->t);
-        if (flat)
-            hipLaunchKernelGGL((k_step<St, kForce, true>), grid, block, 0, h->stream, lattice(h, h->cur),
-                               lattice(h, 1 - h->cur), g, rates, inv_n);
-        else
-            hipLaunchKernelGGL((k_step<St, kForce, false>), grid, block, 0, h->stream, lattice(h, h->cur),
-                               lattice(h, 1 - h->cur), g, rates, inv_n);
+        hipLaunchKernelGGL(kernel, grid, block, 0, h->stream, lattice(h, h->cur), lattice(h, 1 - h->cur), g, rates,
+                           inv_n);
         h->cur = 1 - h->cur;
         h->t += 1;
     }

@@ -65,3 +65,20 @@ def test_variants_equal_single_steps(force_model, aniso):
         print(f"case: two steps, force {force_model} aniso {aniso} n={n}", flush=True)
         a, b = both(4, n=n, wall_type=2, ra=1e4, storage="f32", force_model=force_model, aniso=aniso)
         assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1]), n
+
+
+# both sides of the lattice sizes at which the steps' store policy changes
+@pytest.mark.parametrize("n,storage", [(45, "f32"), (48, "f32"), (51, "f32"), (108, "f32"), (112, "f32"),
+                                       (86, "f64"), (88, "f64"), (135, "f16_i16"), (140, "f16_i16")])
+def test_store_policies_give_the_same_steps(n, storage):
+    """The state after several steps equals the batch's (another kernel) bit for bit."""
+    print(f"case: store policy n={n} {storage}", flush=True)
+    th = inputs.theta_noise(n, 3, 0.3)
+    cav = L.Cavity(n=n, wall_type=1, ra=1e5, storage=storage)
+    cav.init_rest(th)
+    b = L.Batch([dict(n=n, wall_type=1, ra=1e5)], storage=storage)
+    b.init_rest(0, th)
+    cav.step(5)
+    b.step(5)
+    for p, q in zip(cav.read_macro(), b.read_macro(0)):
+        assert np.array_equal(p, q)
