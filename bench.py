@@ -177,9 +177,9 @@ def storage_sweep(n: int, wall_type: int, ra: float, steps: int = 500, warmup: i
         ev_ms = cav.step_timed(steps)
         torch.cuda.synchronize()
         wall = time.perf_counter() - t0
-        bpc = lbmx.bytes_per_cell(st)
+        bpc = lbmx.bytes_per_cell(st) // cav.steps_per_pass()  # per step
         kernel_s = ev_ms / 1e3 / steps
-        out.append({"storage": st, "bytes_per_cell": bpc,
+        out.append({"storage": st, "bytes_per_cell": bpc, "steps_per_pass": cav.steps_per_pass(),
                     "mlups": round(n ** 3 * steps / wall / 1e6, 1),
                     "kernel_us": round(kernel_s * 1e6, 2),
                     "frac": round(n ** 3 * bpc / kernel_s / 1e9 / HBM_PEAK_GBS, 4)})
@@ -368,7 +368,9 @@ def main():
         int(n ** 3 * lbmx.bytes_per_cell(args.storage)) // 2)
     cells = n ** 3
     mlups = cells * args.steps / wall / 1e6
-    bpc = lbmx.bytes_per_cell(args.storage)
+    # the bytes a step cannot do without: two lattices per pass, over its steps
+    spp = cav.steps_per_pass()
+    bpc = lbmx.bytes_per_cell(args.storage) // spp
     kernel_s = ev_ms / 1e3 / args.steps
     achieved = cells * bpc / kernel_s / 1e9
     tr = None if variant else counter_traffic(args.storage, n)
@@ -397,7 +399,7 @@ def main():
                      "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                      "traffic": None if tr is None else tr["traffic_bytes"],
                      "traffic_over_algorithmic": None if tr is None else tr["traffic_over_algorithmic"],
-                     "algorithmic_bytes": cells * bpc, "bytes_per_cell": bpc,
+                     "algorithmic_bytes": cells * bpc, "bytes_per_cell": bpc, "steps_per_pass": spp,
                      "kernel_us": round(kernel_s * 1e6, 2),
                      "copy_achieved": None if copy_gbs is None else round(copy_gbs, 1)},
         "nu3d_after": nu["nu3d"],

@@ -31,7 +31,9 @@
  *     its workspace.  Between steps the second lattice is spare, and the
  *     transfers and readbacks stage their data in it, so no call on a
  *     cavity after lbmx_create allocates device memory (lbmx_save and
- *     lbmx_load use a pinned host buffer of up to 64 MB).
+ *     lbmx_load use a pinned host buffer of up to 64 MB; reads of 16 MB and
+ *     more go through up to 32 MB of pinned host memory, kept until the
+ *     handle is destroyed, and up to 8 threads for the call's duration).
  *   - Failed cavities: a cavity fails when a Nu evaluation finds non-finite
  *     values (LBMX_EUNSTABLE: the run diverged) or when a device call fails
  *     while its state is being changed.  Until an initialisation succeeds
@@ -201,8 +203,8 @@ lbmx_status lbmx_get_populations(lbmx_cavity *h, double *f_host, double *g_host)
  * it was (a successful load also clears a failed state).  The file is
  * a 376-byte header (magic "LBMXCKPT", version 1, sizeof(lbmx_params), the
  * parameters, t, lattice bytes, nodes per slab; host byte order) followed by
- * the lattice; it is tied to this library's lattice layout and is not meant
- * to be portable across versions.  Both calls synchronise the stream.
+ * the lattice as slabs of consecutive nodes (whatever the layout in memory);
+ * it is not meant to be portable across versions.  Both calls synchronise the stream.
  * Errors: EIO when the file cannot be opened, written or read in full;
  * EINVAL when it is not a checkpoint, has another version, size, layout or
  * parameter set (checked before the cavity's state is touched). */
@@ -300,9 +302,16 @@ lbmx_status lbmx_run_to_steady(lbmx_cavity *h, double tol, int64_t every, int64_
  * results (each thread finds its node and walls from its own indices);
  * shapes whose rows span whole wavefronts (bx a multiple of 64, or bx = n)
  * keep every load and store coalesced and run fastest.  EINVAL otherwise.
- * 0, 0 restores the default (bx = min(n, 256), by = min(n, max(1, 256 / bx))). */
+ * 0, 0 restores the default, which takes two steps per pass over the lattice
+ * (FP32 and FP64, except under Guo's forcing) where that is faster, and which
+ * lbmx_get_launch reports as bx = min(n, 256), by = min(n, max(1, 256 / bx)); an
+ * explicit shape takes one step per launch.  Results do not depend on it. */
 lbmx_status lbmx_set_launch(lbmx_cavity *h, int32_t bx, int32_t by);
 lbmx_status lbmx_get_launch(const lbmx_cavity *h, int32_t *bx, int32_t *by);
+
+/* Time steps that a step launch takes per read and write of the lattice: 2 or 1
+ * (the bytes a step moves are 2 lattices over this number). */
+lbmx_status lbmx_get_steps_per_pass(const lbmx_cavity *h, int32_t *steps);
 
 /* ------------------------------------------------------------------ batch
  * Many cavities (uneven n, Ra, wall type; one storage format) advanced
@@ -365,8 +374,8 @@ lbmx_status lbmx_batch_read_macro(lbmx_batch *b, int32_t k, double *rho, double 
 /* u, v, w (lattice units) and theta of cavity k resampled trilinearly onto
  * an out_n^3 node-centred grid of the same cube (clamped at the outermost
  * node centres): host_uvwt holds 4 out_n^3 floats, field-major, x fastest.
- * Allocates and frees device buffers of 32 n_k^3 + 16 out_n^3 bytes (a
- * dataset-export call, not part of the stepping). */
+ * Staged in cavity k's spare lattice; a result that does not fit there (16
+ * out_n^3 bytes) gets a device buffer for the call. */
 lbmx_status lbmx_batch_resample(lbmx_batch *b, int32_t k, int32_t out_n, float *host_uvwt);
 
 /* Launch shape: `block` threads (= nodes per tile, multiple of 64, <= 1024),

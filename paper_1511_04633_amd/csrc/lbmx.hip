@@ -779,6 +779,23 @@ lbmx_status lbmx_get_launch(const lbmx_cavity *h, int32_t *bx, int32_t *by)
     return LBMX_OK;
 }
 
+lbmx_status lbmx_get_steps_per_pass(const lbmx_cavity *h, int32_t *steps)
+{
+    lbmx_status s = check_handle(h);
+    if (s != LBMX_OK)
+        return s;
+    if (!steps)
+        return fail(LBMX_EINVAL, "NULL output");
+    const bool near = near_lattice(h->L.lattice, h->p.storage);
+    const bool able = h->bx == 0 && h->p.force_model != LBMX_FORCE_GUO;
+    const bool two = able && ((h->p.storage == LBMX_F32 &&
+                               plan_step2<float>(h->p.n, h->cus, near).kind != Step2Plan::kSingle) ||
+                              (h->p.storage == LBMX_F64 &&
+                               plan_step2<double>(h->p.n, h->cus, near).kind != Step2Plan::kSingle));
+    *steps = two ? 2 : 1;
+    return LBMX_OK;
+}
+
 lbmx_status lbmx_nusselt_noalloc(lbmx_cavity *h, lbmx_nu *out, double *map_host)
 {
     lbmx_status s = check_handle(h);

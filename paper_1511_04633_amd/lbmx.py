@@ -30,7 +30,7 @@ SYMBOLS = [
     "lbmx_init_from_cavities", "lbmx_step", "lbmx_step_timed", "lbmx_time",
     "lbmx_read_macro", "lbmx_nusselt", "lbmx_nusselt_noalloc", "lbmx_run_to_steady",
     "lbmx_set_launch",
-    "lbmx_get_launch", "lbmx_strerror", "lbmx_last_error",
+    "lbmx_get_launch", "lbmx_get_steps_per_pass", "lbmx_strerror", "lbmx_last_error",
     "lbmx_batch_create", "lbmx_batch_destroy", "lbmx_batch_init_rest", "lbmx_batch_init_from",
     "lbmx_batch_step",
     "lbmx_batch_run_to_steady", "lbmx_batch_info", "lbmx_batch_nusselt",
@@ -121,6 +121,7 @@ def load() -> ctypes.CDLL:
         "lbmx_run_to_steady": [_vp, ctypes.c_double, i64, i64, ctypes.POINTER(lbmx_nu)],
         "lbmx_set_launch": [_vp, i32, i32],
         "lbmx_get_launch": [_vp, ctypes.POINTER(i32), ctypes.POINTER(i32)],
+        "lbmx_get_steps_per_pass": [_vp, ctypes.POINTER(i32)],
         "lbmx_batch_create": [P, i32, _vp, ctypes.POINTER(_vp)],
         "lbmx_batch_init_rest": [_vp, i32, _dp],
         "lbmx_batch_init_from": [_vp, i32, _vp, i32],
@@ -322,6 +323,12 @@ class Cavity:
         bx, by = ctypes.c_int32(), ctypes.c_int32()
         _check(load().lbmx_get_launch(self._h, ctypes.byref(bx), ctypes.byref(by)))
         return int(bx.value), int(by.value)
+
+    def steps_per_pass(self) -> int:
+        """Time steps per read and write of the lattice: 2 or 1."""
+        k = ctypes.c_int32()
+        _check(load().lbmx_get_steps_per_pass(self._h, ctypes.byref(k)))
+        return int(k.value)
 
     # ---- observables --------------------------------------------------------
     def read_macro(self):

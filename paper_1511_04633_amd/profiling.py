@@ -5,7 +5,8 @@ per dispatch) are scaled by what the same counters read for the runtime's
 plain copy kernel (``__amd_rocclr_copyBuffer``, which bench.py's copy probe
 launches on a buffer of known size): on MI355X FETCH_SIZE reads half the
 copied bytes and WRITE_SIZE all of them.  The result is tied to a hash of
-the kernel sources; bench.py reports it only while that hash matches.
+the kernel sources; bench.py reports it only while that hash matches.  Bytes
+are per time step: half a launch's for the kernels that take two.
 
 Usage: python -m paper_1511_04633_amd.profiling FETCH_CSV WRITE_CSV STORAGE N
 prints the JSON entry for profiles/traffic.json.
@@ -20,7 +21,7 @@ import statistics
 import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
-KERNEL_SOURCES = ["csrc/collide.hpp", "csrc/kernels.hpp", "csrc/lbmx.hip"]
+KERNEL_SOURCES = ["csrc/collide.hpp", "csrc/fused.hpp", "csrc/kernels.hpp", "csrc/lbmx.hip"]
 # element bytes of the (flow, energy) populations per storage format
 BYTES = {"f64": (8, 8), "f32": (4, 4), "f16": (2, 2), "bf16": (2, 2), "f16_f32": (2, 4),
          "bf16_f32": (2, 4), "f16_i16": (2, 2)}
@@ -54,10 +55,11 @@ def traffic_entry(fetch_csv, write_csv, storage, n):
     cw = [v for v in write["__amd_rocclr_copyBuffer"] if v > 0.5 * copy_kib]
     s_fetch = copy_kib / statistics.median(cf)
     s_write = copy_kib / statistics.median(cw)
-    step = [k for k in fetch if "k_step" in k][0]
-    f_kib = statistics.median(fetch[step]) * s_fetch
-    w_kib = statistics.median(write[step]) * s_write
-    algo = 2 * lattice_bytes(storage, n)
+    step = max((k for k in fetch if "k_step" in k), key=lambda k: len(fetch[k]))
+    per_pass = 2 if "k_step2" in step else 1  # bytes per time step
+    f_kib = statistics.median(fetch[step]) * s_fetch / per_pass
+    w_kib = statistics.median(write[step]) * s_write / per_pass
+    algo = 2 * lattice_bytes(storage, n) // per_pass
     return {"storage": storage, "n": n, "kernel": step,
             "fetch_kib_raw": statistics.median(fetch[step]),
             "write_kib_raw": statistics.median(write[step]),
