@@ -1511,8 +1511,10 @@ void launch_fwd_as(ConvIn src, const bf *w, const float *bias, void *out, Dims d
     const unsigned groups = unsigned(d.Co / 16 / NCO);
     // One wave of resident blocks, each walking several bricks so that the
     // next brick's loads overlap the current one's products (measured 2-3 %
-    // faster than one brick per block on the 64^3 layers); the x extent is
-    // kept a multiple of 8 for the XCD-aware brick order.
+    // faster than one brick per block on the 64^3 layers); their number is
+    // kept a multiple of 8 for the XCD-aware brick order.  With fewer bricks than
+    // that, one each (8 blocks for 12 bricks, a batch of 3 at 8^3: 96 -> 96 16.0
+    // us, 12 blocks 9.7).
     static const int per_cu = [] {
         int nb = 0;
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_conv_fwd<NCO, RZ, kOut, KS, kDirect>,
@@ -1528,7 +1530,7 @@ void launch_fwd_as(ConvIn src, const bf *w, const float *bias, void *out, Dims d
     unsigned grid = std::max(1u, std::min(bricks, resident));
     if (kOut == kLoss)  // one partial sum per block
         grid = std::max(1u, std::min(grid, unsigned(ls.npartial) / groups));
-    if (grid >= 8)
+    if (grid < bricks && grid >= 8)
         grid -= grid % 8;
     hipLaunchKernelGGL((k_conv_fwd<NCO, RZ, kOut, KS, kDirect>), dim3(grid, groups), dim3(FC_THREADS * KS), 0, s, src, w,
                        bias, out, d, nbx, nby, nbz, ep, ls);
@@ -1600,9 +1602,9 @@ lbmx_status conv_fwd(ConvIn src, const void *w, const float *bias, void *out, in
     // Two or three output channel tiles per block (the input tile is staged
     // once for them) where that leaves two blocks per CU (on smaller grids more
     // blocks hide more latency): batch 4, 16 -> 48 at 64^3 54 us with one, 47 with
-    // three.  Bricks of 8 planes with one tile from four blocks per CU on and as
+    // three.  Bricks of 8 planes with one tile from eight blocks per CU on and as
     // far as 32-bit offsets over their halo go: 16 -> 16 at 64^3 29.1 -> 26.8 us,
-    // 48 -> 16 59 -> 52, but at 32^3 10.8 -> 11.8, and with a gate, whose loads no
+    // 48 -> 16 59 -> 52, but at batch 1 17.6 -> 19.9, and with a gate, whose loads no
     // register is free for during the products, 29.7 -> 31.3 (with two tiles the
     // registers spill: no gain).  Two groups per block that split the rounds when
     // one tile per block leaves at most one block per CU.  Operands that are not
@@ -1624,7 +1626,7 @@ lbmx_status conv_fwd(ConvIn src, const void *w, const float *bias, void *out, in
         launch_fwd<3, 1>(src, wb, bias, out, out_f32, d, s, ep);
     else if (split)
         launch_fwd<1, 1, 2>(src, wb, bias, out, out_f32, d, s, ep);
-    else if (!far && bricks * tiles >= 1024)
+    else if (!far && bricks * tiles >= 2048)
         launch_fwd<1, 2>(src, wb, bias, out, out_f32, d, s, ep);
     else
         launch_fwd<1, 1>(src, wb, bias, out, out_f32, d, s, ep);

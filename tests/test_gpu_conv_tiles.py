@@ -111,7 +111,8 @@ def forward(x, w, b, kind, gate=None, split=0):
 # 8 planes (whole, one plane and one row more, x and y remainders), several rounds of channels
 @pytest.mark.parametrize("shape,ci,co", [
     ((1, 64, 32, 64), 16, 32), ((1, 61, 33, 65), 48, 32), ((1, 64, 32, 64), 32, 48), ((2, 33, 31, 66), 16, 48),
-    ((1, 64, 64, 64), 16, 16), ((1, 65, 61, 67), 48, 16), ((4, 57, 36, 33), 32, 16), ((1, 72, 64, 49), 16, 80)])
+    ((1, 64, 64, 64), 16, 16), ((1, 65, 61, 67), 48, 16), ((4, 57, 36, 33), 32, 16), ((1, 72, 64, 49), 16, 80),
+    ((2, 69, 61, 67), 16, 16), ((1, 33, 30, 66), 48, 80), ((3, 8, 8, 8), 32, 32)])
 def test_forward_tile_choices(shape, ci, co):
     print(f"case: forward tiles {shape} {ci}->{co}", flush=True)
     x, w, b = rnd(shape + (ci,), 31), rnd((co, 27, ci), 32), np.random.default_rng(33).standard_normal(co)
