@@ -413,6 +413,7 @@ struct HostCopy {
 // MB) 1.9 -> 1.25 ms, 128^3 7.3 -> 2.5, 192^3 27.7 -> 7.4, 256^3 64 -> 17.4, the
 // first read of a handle, which allocates the staging (at most 32 MB), 3 ms more.
 // Below, the threads cost more than they save: 64^3 (10 MB) 0.60 -> 0.80 ms.
+// hipStreamPerThread names another stream in every thread: this one copies alone.
 inline lbmx_status copies_to_host(hipStream_t stream, Staging &staging, const HostCopy *list, int count)
 try {
     constexpr size_t kLeast = 16u << 20, kChunk = 2u << 20;
@@ -424,7 +425,7 @@ try {
     const int cpus = sched_getaffinity(0, sizeof set, &set) == 0 ? CPU_COUNT(&set) : 1;
     const int threads = std::min(kThreads, cpus);
     const size_t chunk = std::min(kChunk, std::max<size_t>(256u << 10, total / (4 * size_t(threads)) >> 12 << 12));
-    if (total < kLeast || threads < 2 || !staging.reserve(2 * threads * chunk)) {
+    if (total < kLeast || threads < 2 || stream == hipStreamPerThread || !staging.reserve(2 * threads * chunk)) {
         for (int i = 0; i < count; ++i)
             HIP_TRY(hipMemcpyAsync(list[i].dst, list[i].src, list[i].bytes, hipMemcpyDeviceToHost, stream));
         HIP_TRY(hipStreamSynchronize(stream));

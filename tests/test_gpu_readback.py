@@ -57,3 +57,24 @@ def test_handles_read_from_several_threads():
     for k, c in enumerate(cavs):
         for q in range(5):
             assert np.array_equal(got[k][q], alone(c, q)), (k, q)
+
+
+def test_large_reads_on_a_per_thread_stream():
+    """hipStreamPerThread (handle 2) is another stream in every thread."""
+    from types import SimpleNamespace
+
+    from paper_1511_04633_amd import lbmx
+    n = 80
+    print(f"case: readback on a per-thread stream n={n}", flush=True)
+    th = np.random.default_rng(1).uniform(-0.5, 0.5, n ** 3)
+    got = []
+    for stream in (None, SimpleNamespace(cuda_stream=2)):
+        cav = lbmx.Cavity(n=n, wall_type=1, ra=1e5, storage="f32", stream=stream)
+        cav.init_rest(th)
+        for _ in range(3):
+            cav.step(50)
+            fields = cav.read_macro()
+        got.append(fields + cav.get_populations())
+        cav.close()
+    for a, b in zip(*got):
+        assert np.array_equal(a, b)
