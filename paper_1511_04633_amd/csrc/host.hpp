@@ -437,8 +437,10 @@ try {
         for (size_t o = 0; o < list[i].bytes; o += chunk)
             chunks.push_back({static_cast<char *>(list[i].dst) + o, static_cast<const char *>(list[i].src) + o,
                               std::min(chunk, list[i].bytes - o)});
-    int dev = 0;
-    HIP_TRY(hipGetDevice(&dev));
+    // the workers' events belong to the stream's device, which need not be the caller's
+    int dev = 0, callers = 0;
+    HIP_TRY(hipGetDevice(&callers));
+    HIP_TRY(hipStreamGetDevice(stream, &dev));
     std::atomic<int> first_error{hipSuccess};
     auto run = [&](int w) {
         auto ok = [&](hipError_t e) {
@@ -482,6 +484,7 @@ try {
         run(w);
     for (std::thread &t : pool)
         t.join();
+    (void)hipSetDevice(callers);
     HIP_TRY(hipStreamSynchronize(stream));  // nothing is on its way to the staging memory
     HIP_TRY(hipError_t(first_error.load()));
     return LBMX_OK;

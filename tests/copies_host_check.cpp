@@ -1,6 +1,7 @@
 // copies_to_host (csrc/host.hpp) on the CPU, against a model of the HIP calls it
 // makes: streams are queues whose work runs when somebody waits for them, and
-// hipStreamPerThread is another queue in every thread.  usage: <exe> <case>
+// hipStreamPerThread is another queue in every thread, and an event can be recorded
+// only on streams of the device on which it was created.  usage: <exe> <case>
 #include "../paper_1511_04633_amd/csrc/host.hpp"
 
 #include <cstdarg>
@@ -38,7 +39,10 @@ void run(Queue &q, size_t upto)  // with the lock held
         ++q.done;
     }
 }
+thread_local int device = 0;
+std::map<hipStream_t, int> device_of;  // 0 for a stream not in it
 struct Event {
+    int device;
     Queue *q = nullptr;
     size_t at = 0;
 };
@@ -60,13 +64,15 @@ hipError_t hipStreamSynchronize(hipStream_t s)
 }
 hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned)
 {
-    *e = reinterpret_cast<hipEvent_t>(new Event);
+    *e = reinterpret_cast<hipEvent_t>(new Event{device});
     return hipSuccess;
 }
 hipError_t hipEventRecord(hipEvent_t e, hipStream_t s)
 {
     std::lock_guard<std::mutex> g(lock);
     Event *ev = reinterpret_cast<Event *>(e);
+    if (ev->device != device_of[s])
+        return hipErrorInvalidHandle;
     ev->q = &queue_of(s);
     ev->at = ev->q->pushed;
     return hipSuccess;
@@ -84,10 +90,20 @@ hipError_t hipEventDestroy(hipEvent_t e)
     delete reinterpret_cast<Event *>(e);
     return hipSuccess;
 }
-hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipSetDevice(int d)
+{
+    device = d;
+    return hipSuccess;
+}
 hipError_t hipGetDevice(int *d)
 {
-    *d = 0;
+    *d = device;
+    return hipSuccess;
+}
+hipError_t hipStreamGetDevice(hipStream_t s, hipDevice_t *d)
+{
+    std::lock_guard<std::mutex> g(lock);
+    *d = device_of[s];
     return hipSuccess;
 }
 hipError_t hipHostMalloc(void **p, size_t n, unsigned)
@@ -153,5 +169,9 @@ int main(int argc, char **argv)
         return copies(own, large);
     if (c == "per_thread_stream")
         return copies(hipStreamPerThread, large) + copies(hipStreamPerThread, small);
+    if (c == "other_device") {  // the handle's stream on device 1, the caller on device 0
+        device_of[own] = 1;
+        return copies(own, large) + (device == 0 ? 0 : 4);
+    }
     return 3;
 }
