@@ -414,6 +414,8 @@ struct HostCopy {
 // first read of a handle, which allocates the staging (at most 32 MB), 3 ms more.
 // Below, the threads cost more than they save: 64^3 (10 MB) 0.60 -> 0.80 ms.
 // hipStreamPerThread names another stream in every thread: this one copies alone.
+// Memory that HIP knows (pinned by the caller) needs no staging: into it the device
+// writes at the bus's rate, five fields of 96^3 0.70 ms, through the chunks 1.25.
 inline lbmx_status copies_to_host(hipStream_t stream, Staging &staging, const HostCopy *list, int count)
 try {
     constexpr size_t kLeast = 16u << 20, kChunk = 2u << 20;
@@ -421,23 +423,35 @@ try {
     size_t total = 0;
     for (int i = 0; i < count; ++i)
         total += list[i].bytes;
+    bool known[26] = {};  // destinations that HIP knows
+    if (total >= kLeast)
+        for (int i = 0; i < count; ++i) {
+            hipPointerAttribute_t at;
+            known[i] = hipPointerGetAttributes(&at, list[i].dst) == hipSuccess && at.type != hipMemoryTypeUnregistered;
+            if (known[i])
+                total -= list[i].bytes;
+            else
+                (void)hipGetLastError();
+        }
     cpu_set_t set;
     const int cpus = sched_getaffinity(0, sizeof set, &set) == 0 ? CPU_COUNT(&set) : 1;
     const int threads = std::min(kThreads, cpus);
     const size_t chunk = std::min(kChunk, std::max<size_t>(256u << 10, total / (4 * size_t(threads)) >> 12 << 12));
-    if (total < kLeast || threads < 2 || stream == hipStreamPerThread || !staging.reserve(2 * threads * chunk)) {
-        for (int i = 0; i < count; ++i)
+    const bool direct = total < kLeast || threads < 2 || stream == hipStreamPerThread ||
+                        !staging.reserve(2 * threads * chunk);
+    for (int i = 0; i < count; ++i)
+        if (direct || known[i])
             HIP_TRY(hipMemcpyAsync(list[i].dst, list[i].src, list[i].bytes, hipMemcpyDeviceToHost, stream));
+    if (direct) {
         HIP_TRY(hipStreamSynchronize(stream));
         return LBMX_OK;
     }
     std::vector<HostCopy> chunks;
     chunks.reserve(total / chunk + count);
     for (int i = 0; i < count; ++i)
-        for (size_t o = 0; o < list[i].bytes; o += chunk)
+        for (size_t o = 0; !known[i] && o < list[i].bytes; o += chunk)
             chunks.push_back({static_cast<char *>(list[i].dst) + o, static_cast<const char *>(list[i].src) + o,
                               std::min(chunk, list[i].bytes - o)});
-    // the workers' events belong to the stream's device, which need not be the caller's
     int dev = 0, callers = 0;
     HIP_TRY(hipGetDevice(&callers));
     HIP_TRY(hipStreamGetDevice(stream, &dev));

@@ -40,6 +40,8 @@ void run(Queue &q, size_t upto)  // with the lock held
     }
 }
 thread_local int device = 0;
+std::map<const void *, size_t> pinned;  // by the caller: begin, bytes
+size_t staged = 0;                      // bytes of pinned memory that the code allocated
 std::map<hipStream_t, int> device_of;  // 0 for a stream not in it
 struct Event {
     int device;
@@ -109,12 +111,22 @@ hipError_t hipStreamGetDevice(hipStream_t s, hipDevice_t *d)
 hipError_t hipHostMalloc(void **p, size_t n, unsigned)
 {
     *p = std::malloc(n);
+    staged += n;
     return hipSuccess;
 }
 hipError_t hipHostFree(void *p)
 {
     std::free(p);
     return hipSuccess;
+}
+hipError_t hipPointerGetAttributes(hipPointerAttribute_t *a, const void *p)
+{
+    for (const auto &r : pinned)
+        if (p >= r.first && p < static_cast<const char *>(r.first) + r.second) {
+            a->type = hipMemoryTypeHost;
+            return hipSuccess;
+        }
+    return hipErrorInvalidValue;
 }
 hipError_t hipGetLastError() { return hipSuccess; }
 const char *hipGetErrorString(hipError_t) { return "error"; }
@@ -135,14 +147,17 @@ lbmx_status fail(lbmx_status s, const char *fmt, ...)
 
 using namespace lbmx::host;
 
-// Arrays of doubles that work enqueued on `s` fills, copied to the host: exit
-// status 0 where each arrives whole and as it was filled.
-static int copies(hipStream_t s, const std::vector<size_t> &sizes)
+// Arrays of doubles that work enqueued on `s` fills, copied to the host (the first
+// `pins` of them into memory that the caller has pinned): exit status 0 where each
+// arrives whole and as it was filled.
+static int copies(hipStream_t s, const std::vector<size_t> &sizes, size_t pins = 0)
 {
     std::vector<std::vector<double>> dev, host;
     for (size_t n : sizes) {
         dev.emplace_back(n, -1.0);
         host.emplace_back(n, -2.0);
+        if (host.size() <= pins)
+            pinned[host.back().data()] = n * sizeof(double);
     }
     push(s, [&] {
         for (size_t k = 0; k < dev.size(); ++k)
@@ -169,6 +184,10 @@ int main(int argc, char **argv)
         return copies(own, large);
     if (c == "per_thread_stream")
         return copies(hipStreamPerThread, large) + copies(hipStreamPerThread, small);
+    if (c == "pinned")  // nothing is staged
+        return copies(own, large, large.size()) + (staged == 0 ? 0 : 4);
+    if (c == "partly_pinned")
+        return copies(own, {900001, 2500003, 700001}, 1) + (staged > 0 ? 0 : 4);
     if (c == "other_device") {  // the handle's stream on device 1, the caller on device 0
         device_of[own] = 1;
         return copies(own, large) + (device == 0 ? 0 : 4);
