@@ -658,7 +658,11 @@ lbmx_status lbmx_batch_resample(lbmx_batch *b, int32_t k, int32_t out_n, float *
     hipLaunchKernelGGL(k_resample, dim3(unsigned((mc + 255) / 256)), dim3(256), 0, b->stream, fd, n, 4, od, out_n);
     HIP_TRY(hipGetLastError());
     const HostCopy copy{host_uvwt, od, result};
-    return copies_to_host(b->stream, b->staging, &copy, 1);
+    s = copies_to_host(b->stream, b->staging, &copy, 1);
+    if (s != LBMX_OK)
+        return s;
+    HIP_TRY(hipStreamSynchronize(b->stream));
+    return LBMX_OK;
 }
 
 lbmx_status lbmx_batch_set_launch(lbmx_batch *b, int32_t block, int32_t grid, int32_t graph_steps)

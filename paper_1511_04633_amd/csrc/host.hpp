@@ -403,8 +403,8 @@ struct HostCopy {
     size_t bytes;
 };
 
-// The device-to-host copies of `list`, after the work enqueued on `stream`.
-// Synchronises the stream.
+// The device-to-host copies of `list`, after the work enqueued on `stream`; they
+// have arrived once the caller has synchronised it.
 //
 // From 16 MB on, threads take chunks in turn: each has two pinned chunks, one on
 // its way from the device while it copies the other out.  A copy straight into
@@ -433,19 +433,17 @@ try {
             else
                 (void)hipGetLastError();
         }
+    int threads = 1;
     cpu_set_t set;
-    const int cpus = sched_getaffinity(0, sizeof set, &set) == 0 ? CPU_COUNT(&set) : 1;
-    const int threads = std::min(kThreads, cpus);
+    if (total >= kLeast && stream != hipStreamPerThread && sched_getaffinity(0, sizeof set, &set) == 0)
+        threads = std::min(kThreads, CPU_COUNT(&set));
     const size_t chunk = std::min(kChunk, std::max<size_t>(256u << 10, total / (4 * size_t(threads)) >> 12 << 12));
-    const bool direct = total < kLeast || threads < 2 || stream == hipStreamPerThread ||
-                        !staging.reserve(2 * threads * chunk);
+    const bool direct = threads < 2 || !staging.reserve(2 * threads * chunk);
     for (int i = 0; i < count; ++i)
         if (direct || known[i])
             HIP_TRY(hipMemcpyAsync(list[i].dst, list[i].src, list[i].bytes, hipMemcpyDeviceToHost, stream));
-    if (direct) {
-        HIP_TRY(hipStreamSynchronize(stream));
+    if (direct)
         return LBMX_OK;
-    }
     std::vector<HostCopy> chunks;
     chunks.reserve(total / chunk + count);
     for (int i = 0; i < count; ++i)
@@ -499,10 +497,12 @@ try {
     for (std::thread &t : pool)
         t.join();
     (void)hipSetDevice(callers);
-    HIP_TRY(hipStreamSynchronize(stream));  // nothing is on its way to the staging memory
+    if (first_error.load() != hipSuccess)
+        (void)hipStreamSynchronize(stream);  // nothing is on its way to the staging memory
     HIP_TRY(hipError_t(first_error.load()));
     return LBMX_OK;
 } catch (const std::bad_alloc &) {
+    (void)hipStreamSynchronize(stream);
     return fail(LBMX_ENOMEM, "host allocation failed");
 }
 
@@ -542,6 +542,7 @@ lbmx_status pops_to_host(const View &v, Staging &staging, double *f, double *g)
         if (s != LBMX_OK)
             return s;
     }
+    HIP_TRY(hipStreamSynchronize(v.stream));
     return LBMX_OK;
 }
 
@@ -605,7 +606,11 @@ lbmx_status macro_to_host(const View &v, Staging &staging, double *r, double *u,
     for (int k = 0; k < 5; ++k)
         if (host[k])
             list[count++] = {host[k], dev[k], cells * sizeof(double)};
-    return copies_to_host(v.stream, staging, list, count);
+    s = copies_to_host(v.stream, staging, list, count);
+    if (s != LBMX_OK)
+        return s;
+    HIP_TRY(hipStreamSynchronize(v.stream));
+    return LBMX_OK;
 }
 
 // Nusselt reduction; `scratch` holds 4 n + 4 doubles, the result {Nu_3D,

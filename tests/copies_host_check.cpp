@@ -42,6 +42,7 @@ void run(Queue &q, size_t upto)  // with the lock held
 thread_local int device = 0;
 std::map<const void *, size_t> pinned;  // by the caller: begin, bytes
 size_t staged = 0;                      // bytes of pinned memory that the code allocated
+size_t waits = 0;                       // for a stream
 std::map<hipStream_t, int> device_of;  // 0 for a stream not in it
 struct Event {
     int device;
@@ -62,6 +63,7 @@ hipError_t hipStreamSynchronize(hipStream_t s)
     std::lock_guard<std::mutex> g(lock);
     Queue &q = queue_of(s);
     run(q, q.pushed);
+    ++waits;
     return hipSuccess;
 }
 hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned)
@@ -168,7 +170,7 @@ static int copies(hipStream_t s, const std::vector<size_t> &sizes, size_t pins =
     for (size_t k = 0; k < dev.size(); ++k)
         list.push_back({host[k].data(), dev[k].data(), dev[k].size() * sizeof(double)});
     Staging staging;
-    if (copies_to_host(s, staging, list.data(), int(list.size())) != LBMX_OK)
+    if (copies_to_host(s, staging, list.data(), int(list.size())) != LBMX_OK || hipStreamSynchronize(s) != hipSuccess)
         return 2;
     return host == dev && host[0][0] == 0.0 ? 0 : 1;
 }
@@ -178,8 +180,8 @@ int main(int argc, char **argv)
     const std::string c = argc > 1 ? argv[1] : "";
     const hipStream_t own = reinterpret_cast<hipStream_t>(0x1000);
     const std::vector<size_t> small = {1000, 3}, large = {1000003, 700001, 1, 900001};
-    if (c == "small")
-        return copies(own, small);
+    if (c == "small")  // waits for nothing: several passes of them follow each other
+        return copies(own, small) + (waits == 1 ? 0 : 4);
     if (c == "large")
         return copies(own, large);
     if (c == "per_thread_stream")
