@@ -253,7 +253,10 @@ lbmx_status lbmx_init_from_cavities(lbmx_cavity *dst, lbmx_cavity *a, double wa,
                                     double wb);
 
 /* Advance nsteps >= 0 time steps (fused streaming + double-MRT collision,
- * Eqs. 14 and 29, wall conditions of Eqs. 6-10).  Asynchronous. */
+ * Eqs. 14 and 29, wall conditions of Eqs. 6-10).  Asynchronous; enqueues
+ * kernels only, so it can be captured into a graph: a capture of an even number
+ * of steps ends in the lattice where it began and can be replayed (t counts the
+ * captured call, not the replays). */
 lbmx_status lbmx_step(lbmx_cavity *h, int64_t nsteps);
 
 /* As lbmx_step, and also report the elapsed device time of the nsteps

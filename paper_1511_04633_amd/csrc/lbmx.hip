@@ -74,6 +74,7 @@ struct lbmx_cavity {
     // saving and using the cavity as a source return LBMX_ESTATE until an
     // initialisation succeeds.
     bool failed;
+    bool captured;  // steps were enqueued on a stream under capture
     Staging staging;
 };
 
@@ -101,6 +102,19 @@ void default_launch(int n, int *bx, int *by)
     if (b < 1) b = 1;
     if (b > n) b = n;
     *by = b;
+}
+
+// Whether every step has to change the lattice, by itself or two pairs at a time: a
+// graph captured from an even number of steps is replayed on the lattice where it
+// ended, also when steps run between its replays.  True from the first steps on that
+// are enqueued under capture.
+bool keeps_lattice(lbmx_cavity *h)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(h->stream, &st) != hipSuccess)
+        (void)hipGetLastError();
+    h->captured = h->captured || st == hipStreamCaptureStatusActive;
+    return h->captured;
 }
 
 // Pairs of steps by the kernels that take two steps per pass (fused.hpp), for
@@ -147,7 +161,7 @@ void launch_step_kernels(lbmx_cavity *h, int64_t nsteps)
     if constexpr (kForce != LBMX_FORCE_GUO && (std::is_same<St, Store<float, float>>::value ||
                                                std::is_same<St, Store<double, double>>::value)) {
         if (h->bx == 0 && nsteps >= 2)
-            nsteps -= launch_step_pairs<St, kForce>(h, nsteps, geo, rates);
+            nsteps -= launch_step_pairs<St, kForce>(h, keeps_lattice(h) ? nsteps / 4 * 4 : nsteps, geo, rates);
     }
     const float inv_n = 1.0f / float(n);
     const bool flat = h->bx == 0;  // the default launch
@@ -359,6 +373,7 @@ lbmx_status lbmx_create(const lbmx_params *p, void *dev_workspace, size_t ws_byt
     h->cur = 0;
     h->t = 0;
     h->failed = false;
+    h->captured = false;
     h->bx = h->by = 0;
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess ||

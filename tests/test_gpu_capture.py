@@ -1,0 +1,71 @@
+"""Steps captured into a graph: a graph of an even number of steps ends in the
+lattice it starts from, so that every replay takes the state that many steps on,
+whatever else is stepped between the replays."""
+import numpy as np
+import pytest
+
+from paper_1511_04633_amd import inputs
+from paper_1511_04633_amd import lbmx as L
+
+pytestmark = pytest.mark.gpu
+
+
+# sizes whose default launch takes two steps per pass (tiles, marching columns) and one
+@pytest.mark.parametrize("n,storage", [(16, "f32"), (16, "f64"), (112, "f32"), (64, "f32"), (24, "f16")])
+@pytest.mark.parametrize("steps", [2, 4, 6])
+def test_replays_advance_the_state(n, storage, steps):
+    import torch
+    print(f"case: capture of {steps} steps n={n} {storage}", flush=True)
+    s = torch.cuda.Stream()
+    kw = dict(n=n, wall_type=2, ra=1e5, storage=storage)
+    th = inputs.theta_noise(n, 7, 0.3)
+    with torch.cuda.stream(s):
+        cav, ref = L.Cavity(stream=s, **kw), L.Cavity(stream=s, **kw)
+    cav.init_rest(th)
+    ref.init_rest(th)
+    cav.step(3)  # loads the kernels before the capture
+    cav.init_rest(th)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=s):
+        cav.step(steps)
+    # the capture enqueued nothing: the first replay takes the first steps
+    for replay in range(4):
+        with torch.cuda.stream(s):
+            graph.replay()
+        ref.step(steps)
+        for a, b in zip(cav.read_macro(), ref.read_macro()):
+            assert np.array_equal(a, b), replay
+        if replay % 2:  # steps outside the graph
+            cav.step(2)
+            ref.step(2)
+    cav.close()
+    ref.close()
+
+
+def test_odd_captures_alternate_between_the_lattices():
+    """Two graphs of three steps captured one after the other take turns."""
+    import torch
+    n = 16
+    print("case: two captures of three steps", flush=True)
+    s = torch.cuda.Stream()
+    th = inputs.theta_noise(n, 7, 0.3)
+    with torch.cuda.stream(s):
+        cav, ref = (L.Cavity(n=n, wall_type=1, ra=1e5, storage="f32", stream=s) for _ in range(2))
+    cav.step(3)
+    cav.init_rest(th)
+    ref.init_rest(th)
+    graphs = []
+    for _ in range(2):
+        graphs.append(torch.cuda.CUDAGraph())
+        with torch.cuda.graph(graphs[-1], stream=s):
+            cav.step(3)
+    for _ in range(3):
+        with torch.cuda.stream(s):
+            for g in graphs:
+                g.replay()
+        ref.step(6)
+        for a, b in zip(cav.read_macro(), ref.read_macro()):
+            assert np.array_equal(a, b)
+    cav.close()
+    ref.close()
