@@ -503,11 +503,14 @@ __device__ __forceinline__ uint32_t div_small(uint32_t c, uint32_t n, float inv_
 // nodes in storage order, so that every wavefront but the last is full for any
 // n (rows of 300 nodes in blocks of 256 would leave 41 % of the lanes idle);
 // otherwise a block covers (bx, by) nodes over (x, y).  kForce is the force
-// model (LBMX_FORCE_*).
-template <class St, int kForce, bool kFlat, int kPolicy>
-__global__ __launch_bounds__(1024) void k_step(const char *__restrict__ src, char *__restrict__ dst,
-                                               Geometry<typename St::T> geo,
-                                               Rates<typename St::T> rates, float inv_n)
+// model (LBMX_FORCE_*).  kThreads bounds the block: within the 128 registers that
+// 1024 threads leave each, FP64 under Guo's forcing spills 36 (48^3 15.0 us against
+// 8.8 us with blocks of 256, 256^3 1724 against 1230); the others fit.
+constexpr int kFlatBlock = 256;
+template <class St, int kForce, bool kFlat, int kPolicy, int kThreads>
+__global__ __launch_bounds__(kThreads) void k_step(const char *__restrict__ src, char *__restrict__ dst,
+                                                   Geometry<typename St::T> geo,
+                                                   Rates<typename St::T> rates, float inv_n)
 {
     using T = typename St::T;
     int x = blockIdx.x * blockDim.x + threadIdx.x;

@@ -89,10 +89,9 @@ View view(lbmx_cavity *h)
     return make_view(lattice(h, h->cur), lattice(h, 1 - h->cur), h->L.lattice, h->p, h->d, h->stream);
 }
 
-// Threads per block of the default launch (blocks over a plane's nodes in
-// storage order).  At 256^3 FP32 this is the 256 x 1 block, which measured 1 %
-// faster than 256 x 2 and 5 % faster than 128 x 2.
-constexpr int kFlatBlock = 256;
+// The default launch's blocks of kFlatBlock nodes in storage order are 256 x 1 blocks
+// at 256^3, which measured 1 % faster there (FP32) than 256 x 2 and 5 % faster than
+// 128 x 2.
 
 // The rows-by-columns shape reported for the default launch.
 void default_launch(int n, int *bx, int *by)
@@ -169,8 +168,11 @@ void launch_step_kernels(lbmx_cavity *h, int64_t nsteps)
     const dim3 grid = flat ? dim3((n * n + kFlatBlock - 1) / kFlatBlock, 1, n)
                            : dim3((n + h->bx - 1) / h->bx, (n + h->by - 1) / h->by, n);
     const bool near = near_lattice(h->L.lattice, h->p.storage);
-    const auto kernel = flat ? (near ? k_step<St, kForce, true, kNear> : k_step<St, kForce, true, kFar>)
-                             : (near ? k_step<St, kForce, false, kNear> : k_step<St, kForce, false, kFar>);
+    auto kernel = flat ? (near ? k_step<St, kForce, true, kNear, kFlatBlock> : k_step<St, kForce, true, kFar, kFlatBlock>)
+                       : (near ? k_step<St, kForce, false, kNear, 1024> : k_step<St, kForce, false, kFar, 1024>);
+    if constexpr (kForce == LBMX_FORCE_GUO && sizeof(T) == 8)
+        if (!flat && h->bx * h->by <= 256)
+            kernel = near ? k_step<St, kForce, false, kNear, 256> : k_step<St, kForce, false, kFar, 256>;
     Geometry<T> g = geo;
     for (int64_t s = 0; s < nsteps; ++s) {
         g.step = uint32_t(h->t);

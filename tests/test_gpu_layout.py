@@ -70,3 +70,19 @@ def test_checkpoint_file_holds_slabs(tmp_path, storage, n):
         assert np.array_equal(f[i][inner, inner, inner], w[i] + off), i
         if i < 7:
             assert np.array_equal(g[i][inner, inner, inner], gs[i][up].astype(np.float64)), i
+
+
+@pytest.mark.parametrize("storage", STORAGES)
+@pytest.mark.parametrize("n", [5, 33, 66])
+def test_guo_forcing_does_not_depend_on_the_block(storage, n):
+    """Flat blocks, explicit ones up to 256 threads and above it, bitwise."""
+    print(f"case: Guo blocks {storage} n={n}", flush=True)
+    th = inputs.theta_noise(n, 7, 0.3)
+    out = []
+    for shape in ((0, 0), (min(n, 64), 4), (33, 31)):
+        c = L.Cavity(n=n, wall_type=3, ra=1e4, storage=storage, theta0=th, force_model=2).set_launch(*shape)
+        c.step(4)
+        out.append(c.get_populations())
+        c.close()
+    for f, g in out[1:]:
+        assert np.array_equal(out[0][0], f) and np.array_equal(out[0][1], g)
