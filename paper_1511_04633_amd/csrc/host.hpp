@@ -309,16 +309,46 @@ Geometry<typename St::T> geometry(const View &v)
 // blocks of 256.
 inline dim3 plane_grid(int n) { return dim3((unsigned(n) * unsigned(n) + 255) / 256, unsigned(n)); }
 
-// Whether steps write lattices of so many bytes with kNear: where the lattice and
-// most of the other fit the memory-side cache (measured, kNear / kFar us per step:
-// FP32 108^3, 131 MB, 41.8 / 46.7, 120^3 65.0 / 63.8; f16 / i16 128^3, 109 MB, 36 /
-// 39, 144^3 61 / 57), but not FP32 ones that lie in the L2s with the other (48^3, 11.5
-// MB: 6.6 / 6.15; 44^3 4.9 / 5.5, 54^3 7.6 / 8.1).
-inline bool near_lattice(size_t bytes, int32_t storage)
+// Up to this size the lattice that a step writes, and most of the other, fit the
+// memory-side cache: its stores keep them there (kNear; us per step, kNear / kFar:
+// FP32 108^3, 131 MB, 41.8 / 46.7, 120^3 65.0 / 63.8; f16 / i16 128^3, 109 MB, 36 / 39,
+// 144^3 61 / 57).
+constexpr size_t kNearBytes = size_t(132) << 20;
+
+// The policies of k_step's accesses to lattices of `bytes`.
+// Stores beyond kNearBytes: kFar where they cover whole lines, which the default
+// launch's do (flat), and explicit blocks' if rows are whole lines; else kStream, as
+// with sc1 the parts of a line are written to memory one by one (f16 / i16 200^3 in
+// rows 361 us, 224 with kStream; 150^3 105, 89).
+// Below, kNear but up to 14 MB, from 5.9 MB or FP64 7, where kStream measured faster
+// for reasons that are not known: FP32 41^3 5.7 -> 5.4 us, 48^3 6.6 -> 6.2, 50^3 7.2 ->
+// 6.8, FP64 36^3 6.3 -> 5.9, 40^3 8.1 -> 7.6; not where a plane is a multiple of 8
+// blocks, whose places then stay on one XCD from plane to plane (FP32 44^3 4.97, kStream
+// 5.06), nor for 2-byte flow populations (f16 54^3 5.9, kStream 6.15), whose explicit
+// blocks it helps except with fixed-point energies (f16 54^3 6.8 -> 6.5, bf16 + FP32
+// 50^3 6.3 -> 6.0; f16 / i16 50^3 6.1 -> 6.3).
+// Loads of 8-byte populations do without the cache (nt) beside kStream from 9 MB on
+// (40^3 7.9 us temporal, 7.6 nt; 34^3 5.7, 5.8) and, beyond kNearBytes, where rows are
+// whole lines and only the x-shifted reads share any (128^3 149 -> 146, 256^3 1241 ->
+// 1204; 150^3 240 -> 243).  Narrower ones measured slower with nt.
+struct StepPolicy {
+    int stores;
+    bool nt_loads;
+};
+inline StepPolicy step_policy(size_t bytes, int32_t storage, int n, bool flat)
 {
-    if (storage == LBMX_F32 && bytes > (size_t(10) << 20) && bytes < (size_t(14) << 20))
-        return false;
-    return bytes <= (size_t(132) << 20);
+    constexpr double MB = 1 << 20;
+    const bool f64 = storage == LBMX_F64;
+    const size_t row = size_t(n) * std::min(flow_size(storage), energy_size(storage));
+    const bool lines = row % 128 == 0;
+    if (bytes > kNearBytes)
+        return {flat || lines ? kFar : kStream, f64 && lines};
+    const bool middle = bytes >= (f64 ? 7.0 : 5.9) * MB && bytes < 14.0 * MB;
+    const bool stream = flat ? (f64 || storage == LBMX_F32) && (n * n + kFlatBlock - 1) / kFlatBlock % 8 != 0
+                             : storage != LBMX_F16_I16;
+    if (middle && stream)
+        return {kStream, f64 && bytes >= 9.0 * MB};
+    return {kNear, false};
 }
 
 constexpr uint32_t kAllPops = (1u << 26) - 1;

@@ -260,33 +260,34 @@ __device__ __forceinline__ Buffer make_buffer(const char *base)
 {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(base), short(0), int(0xffffffffu), 0x00020000);
 }
-// Cache policies of the stores.  kNear writes through the XCD's L2 (sc1), so that
-// a kernel's end finds little to write back, and keeps the line in the 256 MB
-// memory-side cache, where the next step reads it if one lattice and most of the
-// other fit.  kFar streams past it (nt; with sc1 for 8- and 2-byte populations,
-// which measured 1 to 8 % faster, 4-byte ones did not).  us per step, nt stores and
-// (FP64) nt loads -> kNear: FP32 64^3 11.8 -> 9.5, 96^3 33.3 -> 28.8, 104^3 41.4 ->
-// 37.4; FP64 50^3 11.6 -> 9.15, 80^3 39 -> 32; f16 / i16 64^3 7.3 -> 6.9, 96^3 20.3 ->
-// 18.3, 128^3 40 -> 36.  Plain stores, written back at the kernel's end: FP32 64^3
-// 9.5, 48^3 6.9 (kNear 6.6), f16 / i16 64^3 8.1.
-constexpr int kNear = 16, kFar = 18;
+// Cache policies of the stores (step_policy chooses).  kNear writes through the XCD's
+// L2 (sc1), so that a kernel's end finds little to write back, and keeps the line in
+// the 256 MB memory-side cache, where the next step reads it if one lattice and most
+// of the other fit.  kStream marks the line as not needed again (nt); kFar is the
+// same with sc1 for 8- and 2-byte populations, which measured 1 to 8 % faster where
+// stores cover whole lines (4-byte ones did not).  us per step, kStream -> kNear:
+// FP32 64^3 11.8 -> 9.5, 96^3 33.3 -> 28.8, 104^3 41.4 -> 37.4; FP64 50^3 11.6 ->
+// 9.15, 80^3 39 -> 32; f16 / i16 64^3 7.3 -> 6.9, 96^3 20.3 -> 18.3, 128^3 40 -> 36.
+// Plain stores, written back at the kernel's end: FP32 64^3 9.5, 48^3 6.9 (kNear
+// 6.6), f16 / i16 64^3 8.1.
+constexpr int kNear = 16, kFar = 18, kStream = 2;
 template <typename S, int kPolicy>
-constexpr int store_bits() { return kPolicy == kFar && sizeof(typename Codec<S>::Raw) == 4 ? 2 : kPolicy; }
+constexpr int store_bits() { return kPolicy == kFar && sizeof(typename Codec<S>::Raw) == 4 ? kStream : kPolicy; }
 
 // Loads return the storage bits (Codec<S>::Raw); Codec<S>::dec converts.
-// They are temporal: a wavefront's x-shifted reads share cache lines with its
-// neighbours'.
-template <typename S>
+// They are temporal, as a wavefront's x-shifted reads share cache lines with its
+// neighbours', except where step_policy asks for nt ones.
+template <typename S, bool kNt = false>
 __device__ __forceinline__ typename Codec<S>::Raw ld(Buffer b, uint32_t lane, uint32_t uniform)
 {
     using R = typename Codec<S>::Raw;
     if constexpr (sizeof(R) == 8) {
         typedef uint32_t u2 __attribute__((ext_vector_type(2)));
-        return __builtin_bit_cast(R, u2(__builtin_amdgcn_raw_buffer_load_b64(b, lane, uniform, 0)));
+        return __builtin_bit_cast(R, u2(__builtin_amdgcn_raw_buffer_load_b64(b, lane, uniform, kNt ? 2 : 0)));
     } else if constexpr (sizeof(R) == 4)
-        return __builtin_bit_cast(R, __builtin_amdgcn_raw_buffer_load_b32(b, lane, uniform, 0));
+        return __builtin_bit_cast(R, __builtin_amdgcn_raw_buffer_load_b32(b, lane, uniform, kNt ? 2 : 0));
     else
-        return __builtin_bit_cast(R, __builtin_amdgcn_raw_buffer_load_b16(b, lane, uniform, 0));
+        return __builtin_bit_cast(R, __builtin_amdgcn_raw_buffer_load_b16(b, lane, uniform, kNt ? 2 : 0));
 }
 template <typename S, int kPolicy>
 __device__ __forceinline__ void st(Buffer b, uint32_t lane, uint32_t uniform, typename Codec<S>::Raw v)
@@ -384,14 +385,15 @@ __device__ __forceinline__ void wall_energy(const Geometry<T> &geo, const Site &
 // address is base + d_i + lane offset with a uniform d_i; a lane at a wall
 // takes the offset that undoes d_i and selects segment ibar.  kLaneZ: z varies
 // over the lanes (base is the lattice) instead of being uniform (base is the
-// plane).  kEdge = false: no lane is at an x or y wall (kLaneZ: at any wall).
+// plane).  kEdge = false: no lane is at an x or y wall (kLaneZ: at any wall).  kNt:
+// the loads' policy.
 template <class St>
 struct RawPops {
     typename Codec<typename St::F>::Raw f[19];
     typename Codec<typename St::G>::Raw g[7];
 };
 
-template <class St, bool kLaneZ, bool kEdge>
+template <class St, bool kLaneZ, bool kEdge, bool kNt = false>
 __device__ __forceinline__ void load_pops(const char *__restrict__ base, int n, const Site &s, RawPops<St> &r)
 {
     Plane<St> pl{uint32_t(n)};
@@ -421,14 +423,14 @@ __device__ __forceinline__ void load_pops(const char *__restrict__ base, int n, 
     for (int i = 0; i < 19; ++i) {
         uint32_t d;
         const uint32_t v = source(ex19(i), ey19(i), ez19(i), i * pl.segF, opp19(i) * pl.segF, pl.bF, vF, d);
-        r.f[i] = ld<typename St::F>(buf, v, d);
+        r.f[i] = ld<typename St::F, kNt>(buf, v, d);
     }
 #pragma unroll
     for (int i = 0; i < 7; ++i) {  // D3Q7 directions are the first 7 of D3Q19
         uint32_t d;
         const uint32_t v = source(ex19(i), ey19(i), ez19(i), pl.offG + i * pl.segG,
                                   pl.offG + opp19(i) * pl.segG, pl.bG, vG, d);
-        r.g[i] = ld<typename St::G>(buf, v, d);
+        r.g[i] = ld<typename St::G, kNt>(buf, v, d);
     }
 }
 
@@ -447,12 +449,12 @@ __device__ __forceinline__ void decode_pops(const RawPops<St> &r, const Geometry
     wall_energy<T, kEdge, kEdge || !kLaneZ>(geo, s, y, g);
 }
 
-template <class St, bool kLaneZ, bool kEdge = true>
+template <class St, bool kLaneZ, bool kEdge = true, bool kNt = false>
 __device__ __forceinline__ void pull(const char *__restrict__ base, const Geometry<typename St::T> &geo,
                                      const Site &s, int y, typename St::T f[19], typename St::T g[7])
 {
     RawPops<St> r;
-    load_pops<St, kLaneZ, kEdge>(base, geo.n, s, r);
+    load_pops<St, kLaneZ, kEdge, kNt>(base, geo.n, s, r);
     decode_pops<St, kLaneZ, kEdge>(r, geo, s, y, f, g);
 }
 
@@ -503,11 +505,11 @@ __device__ __forceinline__ uint32_t div_small(uint32_t c, uint32_t n, float inv_
 // nodes in storage order, so that every wavefront but the last is full for any
 // n (rows of 300 nodes in blocks of 256 would leave 41 % of the lanes idle);
 // otherwise a block covers (bx, by) nodes over (x, y).  kForce is the force
-// model (LBMX_FORCE_*).  kThreads bounds the block: within the 128 registers that
+// model (LBMX_FORCE_*), kPolicy and kNt the policies of its stores and loads.  kThreads bounds the block: within the 128 registers that
 // 1024 threads leave each, FP64 under Guo's forcing spills 36 (48^3 15.0 us against
 // 8.8 us with blocks of 256, 256^3 1724 against 1230); the others fit.
 constexpr int kFlatBlock = 256;
-template <class St, int kForce, bool kFlat, int kPolicy, int kThreads>
+template <class St, int kForce, bool kFlat, int kThreads, int kPolicy, bool kNt>
 __global__ __launch_bounds__(kThreads) void k_step(const char *__restrict__ src, char *__restrict__ dst,
                                                    Geometry<typename St::T> geo,
                                                    Rates<typename St::T> rates, float inv_n)
@@ -525,7 +527,7 @@ __global__ __launch_bounds__(kThreads) void k_step(const char *__restrict__ src,
     const size_t plane = size_t(Plane<St>(uint32_t(geo.n)).bytes) * z;
     const Site s = site_in_plane<St>(geo.n, x, y, z);
     T f[19], g[7];
-    pull<St, false>(src + plane, geo, s, y, f, g);
+    pull<St, false, true, kNt>(src + plane, geo, s, y, f, g);
     collide<T, kForce>(f, g, rates);
     put<St, kPolicy>(dst + plane, s, uint32_t(x) + uint32_t(geo.n) * (uint32_t(y) + uint32_t(geo.n) * z), geo.step,
             geo, f, g);

@@ -125,7 +125,7 @@ int64_t launch_step_pairs(lbmx_cavity *h, int64_t nsteps, Geometry<typename St::
                           const Rates<typename St::T> &rates)
 {
     using T = typename St::T;
-    const Step2Plan p = plan_step2<T>(h->p.n, h->cus, near_lattice(h->L.lattice, h->p.storage));
+    const Step2Plan p = plan_step2<T>(h->p.n, h->cus, h->L.lattice <= kNearBytes);
     if (p.kind == Step2Plan::kSingle)
         return 0;
     auto run = [&](auto kernel, int threads, auto... args) {
@@ -150,6 +150,21 @@ int64_t launch_step_pairs(lbmx_cavity *h, int64_t nsteps, Geometry<typename St::
     return nsteps / 2 * 2;
 }
 
+// The instance of k_step for the cavity's policy (step_policy).
+template <class St, int kForce, bool kFlat, int kThreads>
+auto step_kernel(const lbmx_cavity *h)
+{
+    const StepPolicy p = step_policy(h->L.lattice, h->p.storage, h->p.n, kFlat);
+    if (p.stores == kNear)
+        return k_step<St, kForce, kFlat, kThreads, kNear, false>;
+    if constexpr (sizeof(typename St::F) == 8)
+        if (p.nt_loads)
+            return p.stores == kFar ? k_step<St, kForce, kFlat, kThreads, kFar, true>
+                                    : k_step<St, kForce, kFlat, kThreads, kStream, true>;
+    return p.stores == kFar ? k_step<St, kForce, kFlat, kThreads, kFar, false>
+                            : k_step<St, kForce, kFlat, kThreads, kStream, false>;
+}
+
 template <class St, int kForce>
 void launch_step_kernels(lbmx_cavity *h, int64_t nsteps)
 {
@@ -167,12 +182,10 @@ void launch_step_kernels(lbmx_cavity *h, int64_t nsteps)
     const dim3 block = flat ? dim3(kFlatBlock) : dim3(h->bx, h->by);
     const dim3 grid = flat ? dim3((n * n + kFlatBlock - 1) / kFlatBlock, 1, n)
                            : dim3((n + h->bx - 1) / h->bx, (n + h->by - 1) / h->by, n);
-    const bool near = near_lattice(h->L.lattice, h->p.storage);
-    auto kernel = flat ? (near ? k_step<St, kForce, true, kNear, kFlatBlock> : k_step<St, kForce, true, kFar, kFlatBlock>)
-                       : (near ? k_step<St, kForce, false, kNear, 1024> : k_step<St, kForce, false, kFar, 1024>);
+    auto kernel = flat ? step_kernel<St, kForce, true, kFlatBlock>(h) : step_kernel<St, kForce, false, 1024>(h);
     if constexpr (kForce == LBMX_FORCE_GUO && sizeof(T) == 8)
         if (!flat && h->bx * h->by <= 256)
-            kernel = near ? k_step<St, kForce, false, kNear, 256> : k_step<St, kForce, false, kFar, 256>;
+            kernel = step_kernel<St, kForce, false, 256>(h);
     Geometry<T> g = geo;
     for (int64_t s = 0; s < nsteps; ++s) {
         g.step = uint32_t(h->t);
@@ -803,7 +816,7 @@ lbmx_status lbmx_get_steps_per_pass(const lbmx_cavity *h, int32_t *steps)
         return s;
     if (!steps)
         return fail(LBMX_EINVAL, "NULL output");
-    const bool near = near_lattice(h->L.lattice, h->p.storage);
+    const bool near = h->L.lattice <= kNearBytes;
     const bool able = h->bx == 0 && h->p.force_model != LBMX_FORCE_GUO;
     const bool two = able && ((h->p.storage == LBMX_F32 &&
                                plan_step2<float>(h->p.n, h->cus, near).kind != Step2Plan::kSingle) ||

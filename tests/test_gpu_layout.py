@@ -86,3 +86,32 @@ def test_guo_forcing_does_not_depend_on_the_block(storage, n):
         c.close()
     for f, g in out[1:]:
         assert np.array_equal(out[0][0], f) and np.array_equal(out[0][1], g)
+
+
+# one size for each policy of the step kernel's stores and loads, by lattice bytes, rows of
+# whole lines and blocks per plane; `other` brings a batch's total across the 132 MB at which
+# its stores change
+@pytest.mark.parametrize("storage,n,other", [
+    ("f64", 30, 90), ("f64", 34, 90), ("f64", 38, 90), ("f64", 43, 90), ("f64", 90, 24), ("f64", 96, 24),
+    ("f32", 38, 112), ("f32", 42, 112), ("f32", 44, 112), ("f32", 60, 112), ("f32", 111, 24), ("f32", 128, 24),
+    ("f16", 56, 140), ("f16", 150, 24), ("f16", 192, 24), ("bf16_f32", 50, 132), ("bf16_f32", 132, 24),
+    ("f16_i16", 56, 140), ("f16_i16", 150, 24)])
+def test_access_policies_give_the_same_steps(storage, n, other):
+    print(f"case: access policy {storage} n={n}", flush=True)
+    th = inputs.theta_noise(n, 9, 0.3)
+    kw = dict(wall_type=3, ra=1e5)
+    out = []
+    for shape in ((0, 0), (min(n, 256), max(1, 256 // n)), (64, 3)):
+        c = L.Cavity(n=n, storage=storage, theta0=th, **kw).set_launch(*shape)
+        for _ in range(3):  # one at a time: no step by the kernels that take two
+            c.step(1)
+        out.append(c.read_macro())
+        c.close()
+    for sizes in ([n], [n, other]):
+        b = L.Batch([dict(n=m, **kw) for m in sizes], storage=storage)
+        b.init_rest(0, th)
+        b.step(3)
+        out.append(b.read_macro(0))
+        b.close()
+    for fields in out[1:]:
+        assert all(np.array_equal(p, q) for p, q in zip(out[0], fields))
