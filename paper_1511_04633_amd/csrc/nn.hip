@@ -906,36 +906,18 @@ k_conv_wgrad(ConvIn src, const bf *__restrict__ gout, float *__restrict__ gw, fl
     int g0 = 0, q = 0;  // ring places of the chunk's input group and gout group
     auto in_at = [&](int k) { return ((g0 + k) & 3) * (WB_ILOADS * 512); };
     auto go_at = [&](int k) { return 4 * WB_ILOADS * 512 + (q + k < 3 ? q + k : q + k - 3) * (WB_GLOADS * 512); };
-    // One chunk.  What arrives and what is read are different places of the ring
-    // between two barriers, which restrict tells the compiler: without it, it
-    // waits for everything on its way before the first transposing read.
-    auto chunk = [&](bf *__restrict__ arrive, const bf *__restrict__ ring, int c) {
-        const int colm = c / nbz, cz = c - colm * nbz, z0 = cz * WB_Z;
-        const int rest = min(c1 - c, nbz - cz);  // chunks left of the range in this column
-        auto load_set = [&](int k) {  // what chunk c + k needs and c + k - 1 does not
-            load_input(z0 + (k + 1) * WB_Z, arrive + in_at(k + 1));
-            load_gout(z0 + k * WB_Z, arrive + go_at(k));
-        };
-        if (c == c0 || cz == 0) {  // a new column
-            int zero;
-            grid.at(colm, WB_X, WB_Y, 1, b, x0, y0, zero);
-            lds_barrier();  // the previous chunk's reads are done
-            load_input(z0, arrive + in_at(0));
-            load_set(0);
-            if (rest > 1)
-                load_set(1);
-        }
-        if (kDirect && rest > 1) {  // all but the next chunk's
-            if (wave < WB_GLOADS - WB_WAVES)
-                wait_loads<WB_IITERS + 2>();
-            else
-                wait_loads<WB_IITERS + 1>();
-        } else {
-            wait_loads();
-        }
-        lds_barrier();
+    auto load_set = [&](bf *to, int z0, int k) {  // what the k-th chunk from the one at z0 needs anew
+        load_input(z0 + (k + 1) * WB_Z, to + in_at(k + 1));
+        load_gout(z0 + k * WB_Z, to + go_at(k));
+    };
+    // One chunk, whose input and gout groups lie in LDS.  What it requests and what
+    // it reads are different places of the ring, which restrict tells the compiler:
+    // without it, it waits for everything on its way before the first transposing
+    // read.  Requests for what this call reads, their wait and the barrier are
+    // therefore outside.
+    auto chunk = [&](bf *__restrict__ arrive, const bf *__restrict__ ring, int z0, int rest) {
         if (rest > 2)
-            load_set(2);
+            load_set(arrive, z0, 2);
         const bf *const gq = ring + go_at(0) + gp, *const in0 = ring + in_at(0) + ip, *const in1 = ring + in_at(1) + ip;
         bf8v a[WB_Z];  // the team's two rows of gout plane z
 #pragma unroll
@@ -963,8 +945,29 @@ k_conv_wgrad(ConvIn src, const bf *__restrict__ gout, float *__restrict__ gw, fl
     };
     int none = 0;  // not known to the compiler, which would pass a known address by itself and lose restrict
     asm volatile("" : "+s"(none));
-    for (int c = c0; c < c1; ++c)
-        chunk(lds.ring + none, lds.ring + none, c);
+    for (int c = c0; c < c1; ++c) {
+        const int colm = c / nbz, cz = c - colm * nbz, z0 = cz * WB_Z;
+        const int rest = min(c1 - c, nbz - cz);  // chunks left of the range in this column
+        if (c == c0 || cz == 0) {                // a new column
+            int zero;
+            grid.at(colm, WB_X, WB_Y, 1, b, x0, y0, zero);
+            lds_barrier();  // the previous chunk's reads are done
+            load_input(z0, lds.ring + in_at(0));
+            load_set(lds.ring, z0, 0);
+            if (rest > 1)
+                load_set(lds.ring, z0, 1);
+        }
+        if (kDirect && rest > 1) {  // all but the next chunk's
+            if (wave < WB_GLOADS - WB_WAVES)
+                wait_loads<WB_IITERS + 2>();
+            else
+                wait_loads<WB_IITERS + 1>();
+        } else {
+            wait_loads();
+        }
+        lds_barrier();
+        chunk(lds.ring + none, lds.ring + none, z0, rest);
+    }
     // The teams' sums in LDS, each [tap][co][ci] and then the bias; every thread
     // adds its share of their total to the global gradient, blocks starting at
     // different places (from the same one they queue at the same addresses).

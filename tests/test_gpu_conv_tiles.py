@@ -215,3 +215,25 @@ def test_weight_gradient_upsampled_input():
     ref, bound = N.conv3d_wgrad(x, g), N.conv3d_wgrad(np.abs(x), np.abs(g))
     for a, r, b in zip((gw, gb), ref, bound):
         assert np.all(np.abs(a.cpu().numpy() - r) <= 2e-5 * b + 1e-6)
+
+
+# chunks of 16 x 8 x 4 voxels down columns: depths about whole chunks with remainders in x and
+# y, rows of one to four teams, plain and 2 bytes off a 16-byte boundary (loads through registers)
+@pytest.mark.parametrize("shape", [(1, 3, 1, 15), (2, 4, 2, 17), (1, 5, 3, 16), (1, 8, 6, 31), (2, 9, 7, 33),
+                                   (1, 13, 8, 1), (1, 16, 9, 18), (3, 12, 4, 16)])
+@pytest.mark.parametrize("aligned", [True, False])
+def test_weight_gradient_chunks_of_a_column(shape, aligned):
+    import torch
+    print(f"case: wgrad chunks {shape} aligned {aligned}", flush=True)
+    ci, co = 32, 16
+    x, g = rnd(shape + (ci,), 71), rnd(shape + (co,), 72)
+    ref, bound = N.conv3d_wgrad(x, g), N.conv3d_wgrad(np.abs(x), np.abs(g))
+    t = []
+    for a in (to_bf(x), to_bf(g)):
+        if not aligned:
+            flat = torch.empty(a.numel() + 1, dtype=a.dtype, device="cuda")
+            flat[1:] = a.flatten()
+            a = flat[1:].view(a.shape)
+        t.append(a)
+    for a, r, b in zip(wgrad(*t), ref, bound):
+        assert np.all(np.abs(a.cpu().numpy() - r) <= 2e-5 * b + 1e-6), shape
