@@ -910,14 +910,14 @@ k_conv_wgrad(ConvIn src, const bf *__restrict__ gout, float *__restrict__ gw, fl
         load_input(z0 + (k + 1) * WB_Z, to + in_at(k + 1));
         load_gout(z0 + k * WB_Z, to + go_at(k));
     };
-    // One chunk, whose input and gout groups lie in LDS.  What it requests and what
-    // it reads are different places of the ring, which restrict tells the compiler:
-    // without it, it waits for everything on its way before the first transposing
-    // read.  Requests for what this call reads, their wait and the barrier are
-    // therefore outside.
-    auto chunk = [&](bf *__restrict__ arrive, const bf *__restrict__ ring, int z0, int rest) {
-        if (rest > 2)
-            load_set(arrive, z0, 2);
+    // Between two barriers: the request for what a later chunk needs, and the products
+    // of one whose groups lie in LDS.  The one writes no place of the ring that the
+    // other reads, and nothing else is written meanwhile, which restrict tells the
+    // compiler: without it, it waits for everything on its way before the first
+    // transposing read.  What the next chunk reads is requested, waited for and
+    // separated by a barrier outside of both.
+    auto request = [&](bf *__restrict__ arrive, int z0) { load_set(arrive, z0, 2); };
+    auto products = [&](const bf *__restrict__ ring) {
         const bf *const gq = ring + go_at(0) + gp, *const in0 = ring + in_at(0) + ip, *const in1 = ring + in_at(1) + ip;
         bf8v a[WB_Z];  // the team's two rows of gout plane z
 #pragma unroll
@@ -940,8 +940,6 @@ k_conv_wgrad(ConvIn src, const bf *__restrict__ gout, float *__restrict__ gw, fl
                             __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[Z - kz], v, acc[kz * 3 + Y], 0, 0, 0);
             }
         }
-        g0 = (g0 + 1) & 3;
-        q = q == 2 ? 0 : q + 1;
     };
     int none = 0;  // not known to the compiler, which would pass a known address by itself and lose restrict
     asm volatile("" : "+s"(none));
@@ -966,7 +964,12 @@ k_conv_wgrad(ConvIn src, const bf *__restrict__ gout, float *__restrict__ gw, fl
             wait_loads();
         }
         lds_barrier();
-        chunk(lds.ring + none, lds.ring + none, z0, rest);
+        if (rest > 2)
+            request(lds.ring + none, z0);
+        if (y0 + 2 * team < d.H)  // else both rows lie outside the volume
+            products(lds.ring + none);
+        g0 = (g0 + 1) & 3;
+        q = q == 2 ? 0 : q + 1;
     }
     // The teams' sums in LDS, each [tap][co][ci] and then the bias; every thread
     // adds its share of their total to the global gradient, blocks starting at

@@ -237,3 +237,21 @@ def test_weight_gradient_chunks_of_a_column(shape, aligned):
         t.append(a)
     for a, r, b in zip(wgrad(*t), ref, bound):
         assert np.all(np.abs(a.cpu().numpy() - r) <= 2e-5 * b + 1e-6), shape
+
+
+@pytest.mark.parametrize("H", [2, 4, 6, 12])
+def test_weight_gradient_leaves_rows_outside_alone(H):
+    """An infinite input in the last row enters no tap that pairs it with a row
+    outside the volume, where the output gradient counts as zero (rows are taken
+    in pairs: of an odd number the last has one outside beside it)."""
+    import torch
+    print(f"case: wgrad non-finite input, {H} rows", flush=True)
+    shape, ci, co = (1, 4, H, 16), 16, 16
+    x, g = to_bf(rnd(shape + (ci,), 81)), to_bf(rnd(shape + (co,), 82))
+    want = wgrad(x, g)[0]
+    x[0, 1, H - 1, 5, 3] = float("inf")
+    got = wgrad(x, g)[0]
+    # taps with y offset -1 pair input row y with output row y + 1
+    assert torch.equal(got[:, [t for t in range(27) if t // 3 % 3 == 0]],
+                       want[:, [t for t in range(27) if t // 3 % 3 == 0]])
+    assert not torch.isfinite(got[:, 13, 3]).any()
