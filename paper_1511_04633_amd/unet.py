@@ -256,7 +256,9 @@ class UNet:
         s = stream_ptr()
         m = self.m
         if self.fused and not train and self.record is None:
-            return self._infer(cond, B, s)
+            levels = self._levels()
+            if levels is not None:
+                return self._infer(cond, B, s, levels)
         cache, h = self._trunk(cond, B)
         pred = torch.empty((B, m ** 3, 16), dtype=torch.float32, device="cuda")
         call("lbmx_nn_conv3d_fwd", P(h), P(self.head.wb), P(self.head.b), P(pred), 1, B, m, m, m,
@@ -264,12 +266,27 @@ class UNet:
         self._cache = (cache, h, B) if train else None
         return pred
 
-    def _infer(self, cond, B, s):
+    def _levels(self):
+        """Channels per level if the layers, which a program may have replaced, are
+        those that lbmx_nn_unet_forward runs; else None."""
+        levels = [b.co for _, b in self.enc]
+        shapes, ci = [], NFEAT
+        for c in levels:
+            shapes += [(ci, c), (c, c)]
+            ci = c
+        for c in reversed(levels[:-1]):
+            shapes += [(ci + c, c), (c, c)]
+            ci = c
+        shapes.append((ci, 16))
+        same = [(c.ci, c.co) for c in self.convs()] == shapes
+        return levels if same and len(levels) <= 8 else None
+
+    def _infer(self, cond, B, s, levels):
         """forward() without a cache: every launch from one native call."""
         import torch
 
         convs = self.convs()
-        levels = (ctypes.c_int32 * len(self.LEVELS))(*self.LEVELS)
+        levels = (ctypes.c_int32 * len(levels))(*levels)
         ptrs = _vp * len(convs)
         size = ctypes.c_size_t()
         call("lbmx_nn_unet_workspace", levels, len(levels), B, self.m, ctypes.byref(size))

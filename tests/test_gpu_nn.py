@@ -819,3 +819,18 @@ def test_inference_refuses_odd_levels():
     for train in (False, True):
         with pytest.raises(lbmx.LbmxError):
             net.forward(cond, 1, train=train)
+
+
+def test_inference_runs_replaced_layers():
+    """Layers of other widths than the network is built with, inside a level (the
+    one native call runs only the usual ones)."""
+    import torch
+    from paper_1511_04633_amd import unet
+    print("case: inference with a wider layer pair", flush=True)
+    net = unet.UNet(seed=5, m=16)
+    rng = np.random.default_rng(6)
+    net.enc[1] = (unet.Conv(16, 48, rng), unet.Conv(48, 32, rng))
+    cond = unet.cond_tensor([4.2, 5.1], [1, 3])
+    ref = net.forward(cond, 2, train=True).clone()
+    net._cache = None
+    assert torch.equal(net.forward(cond, 2), ref)
