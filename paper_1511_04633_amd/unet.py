@@ -634,7 +634,7 @@ def predict_fields(net, log10_ra, wall_type, u_c=1.0):
     m = net.m
     cond = cond_tensor([log10_ra], [wall_type])
     pred = net.forward(cond, 1)
-    sc = net.scale.clone()
+    sc = net.scale.to(device="cuda", dtype=torch.float32).expand(NOUT).clone()
     sc[:3] *= u_c
     out = torch.empty((NOUT, m ** 3), dtype=torch.float32, device="cuda")
     call("lbmx_nn_layout", P(pred), P(out), 1, m ** 3, NOUT, 16, 0, P(sc), stream_ptr())
