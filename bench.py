@@ -253,9 +253,10 @@ def warm_start_192(net, ra: float = 3e5, wall_type: int = 2, n: int = 192, coars
                                  time_ratio=round(ex["seconds"] / rest["seconds"], 3))}
 
 
-def counter_traffic(storage: str, n: int):
-    """HBM bytes per step launch measured by rocprofv3 counters (profiles/traffic.json),
-    or None when no measurement exists or the kernel sources changed since."""
+def counter_traffic(storage: str, n: int, steps_per_pass: int):
+    """HBM bytes per time step measured by rocprofv3 counters (profiles/traffic.json)
+    under the default launch, or None when no measurement exists, it is of kernels
+    that take another number of steps per pass, or the sources changed since."""
     from paper_1511_04633_amd import profiling
 
     path = os.path.join(ROOT, "profiles", "traffic.json")
@@ -266,8 +267,7 @@ def counter_traffic(storage: str, n: int):
         return None
     if not entry or entry.get("source_sha256") != profiling.kernel_source_hash():
         return None
-    return entry
-
+    return entry if entry.get("steps_per_pass") == steps_per_pass else None
 
 
 
@@ -368,12 +368,13 @@ def main():
         int(n ** 3 * lbmx.bytes_per_cell(args.storage)) // 2)
     cells = n ** 3
     mlups = cells * args.steps / wall / 1e6
-    # the bytes a step cannot do without: two lattices per pass, over its steps
+    # the bytes a step cannot do without: two lattices per pass, over its steps (an
+    # odd step is a pass of its own)
     spp = cav.steps_per_pass()
-    bpc = lbmx.bytes_per_cell(args.storage) // spp
+    bpc = lbmx.bytes_per_cell(args.storage) * -(-args.steps // spp) / args.steps
     kernel_s = ev_ms / 1e3 / args.steps
     achieved = cells * bpc / kernel_s / 1e9
-    tr = None if variant else counter_traffic(args.storage, n)
+    tr = None if variant or args.launch or args.steps % spp else counter_traffic(args.storage, n, spp)
     dtype = {"f64": "f64", "f32": "f32", "f16": "f16-storage/f32", "bf16": "bf16-storage/f32",
              "f16_f32": "f16-flow+f32-energy-storage/f32",
              "bf16_f32": "bf16-flow+f32-energy-storage/f32",
@@ -394,12 +395,12 @@ def main():
         "config": {"workload": f"double-MRT cubic cavity {n}^3, Type {args.wall_type}, "
                                f"Ra {args.ra:g}, Pr 0.71, Ma 0.1",
                    "n": n, "cells": cells, "storage": args.storage,
-                   "launch": list(cav.get_launch())},
+                   "launch": list(cav.get_launch()) if spp == 1 else "two steps per pass"},
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                      "traffic": None if tr is None else tr["traffic_bytes"],
                      "traffic_over_algorithmic": None if tr is None else tr["traffic_over_algorithmic"],
-                     "algorithmic_bytes": cells * bpc, "bytes_per_cell": bpc, "steps_per_pass": spp,
+                     "algorithmic_bytes": round(cells * bpc), "bytes_per_cell": bpc, "steps_per_pass": spp,
                      "kernel_us": round(kernel_s * 1e6, 2),
                      "copy_achieved": None if copy_gbs is None else round(copy_gbs, 1)},
         "nu3d_after": nu["nu3d"],

@@ -21,7 +21,8 @@ import statistics
 import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
-KERNEL_SOURCES = ["csrc/collide.hpp", "csrc/fused.hpp", "csrc/kernels.hpp", "csrc/lbmx.hip"]
+# the kernels, and the rules that choose them and their access policies
+KERNEL_SOURCES = ["csrc/collide.hpp", "csrc/fused.hpp", "csrc/host.hpp", "csrc/kernels.hpp", "csrc/lbmx.hip"]
 # element bytes of the (flow, energy) populations per storage format
 BYTES = {"f64": (8, 8), "f32": (4, 4), "f16": (2, 2), "bf16": (2, 2), "f16_f32": (2, 4),
          "bf16_f32": (2, 4), "f16_i16": (2, 2)}
@@ -60,7 +61,7 @@ def traffic_entry(fetch_csv, write_csv, storage, n):
     f_kib = statistics.median(fetch[step]) * s_fetch / per_pass
     w_kib = statistics.median(write[step]) * s_write / per_pass
     algo = 2 * lattice_bytes(storage, n) // per_pass
-    return {"storage": storage, "n": n, "kernel": step,
+    return {"storage": storage, "n": n, "kernel": step, "steps_per_pass": per_pass,
             "fetch_kib_raw": statistics.median(fetch[step]),
             "write_kib_raw": statistics.median(write[step]),
             "scale_fetch": round(s_fetch, 5), "scale_write": round(s_write, 5),
