@@ -68,11 +68,6 @@ struct Dims {
     int Ci, Co;      // channels (multiples of 16)
 };
 
-__device__ __forceinline__ long long nvox_of(const Dims &d)
-{
-    return (long long)d.B * d.D * d.H * d.W;
-}
-
 // ------------------------------------------------------------- convolution
 // out[p][co] = bias[co] + sum_{tap, ci} W[co][tap][ci] in[p + off(tap)][ci].
 //
@@ -1508,8 +1503,18 @@ bool aligned16(const P *...p)
     return ((reinterpret_cast<uintptr_t>(p) | ... | 0) & 15) == 0;
 }
 
+// Compute units of the current device.
+int compute_units()
+{
+    int dev = 0, cus = 256;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
+        cus = 256;
+    return cus;
+}
+
 template <int NCO, int RZ, FcOut kOut, int KS, bool kDirect>
-void launch_fwd_as(ConvIn src, const bf *w, const float *bias, void *out, Dims d, hipStream_t s, Epilogue ep,
+void launch_fwd_as(ConvIn src, const bf *w, const float *bias, void *out, Dims d, int cus, hipStream_t s, Epilogue ep,
                    LossEp ls = LossEp{})
 {
     const int nbx = (d.W + FC_X - 1) / FC_X, nby = (d.H + FC_Y - 1) / FC_Y, nbz = (d.D + 4 * RZ - 1) / (4 * RZ);
@@ -1528,10 +1533,6 @@ void launch_fwd_as(ConvIn src, const bf *w, const float *bias, void *out, Dims d
             nb = 1;
         return nb < 1 ? 1 : nb;
     }();
-    int dev = 0, cus = 256;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
-        cus = 256;
     const unsigned resident = unsigned(per_cu) * unsigned(cus) / groups;
     unsigned grid = std::max(1u, std::min(bricks, resident));
     if (kOut == kLoss)  // one partial sum per block
@@ -1543,7 +1544,7 @@ void launch_fwd_as(ConvIn src, const bf *w, const float *bias, void *out, Dims d
 }
 
 template <int NCO, int RZ, int KS = 1, bool kDirect = true>
-void launch_fwd(ConvIn src, const bf *w, const float *bias, void *out, int out_f32, Dims d, hipStream_t s,
+void launch_fwd(ConvIn src, const bf *w, const float *bias, void *out, int out_f32, Dims d, int cus, hipStream_t s,
                 Epilogue ep)
 {
     const auto run = out_f32   ? launch_fwd_as<NCO, RZ, kF32, KS, kDirect>
@@ -1551,7 +1552,7 @@ void launch_fwd(ConvIn src, const bf *w, const float *bias, void *out, int out_f
                                      : launch_fwd_as<NCO, RZ, kSilu, KS, kDirect>
                      : ep.gate ? launch_fwd_as<NCO, 1, kGate, KS, kDirect>  // 8 rows leave no registers for the gate
                                : launch_fwd_as<NCO, RZ, kBf16, KS, kDirect>;
-    run(src, w, bias, out, d, s, ep, LossEp{});
+    run(src, w, bias, out, d, cus, s, ep, LossEp{});
 }
 
 // Rejects planes whose brick-relative element offsets (a few planes of
@@ -1617,25 +1618,25 @@ lbmx_status conv_fwd(ConvIn src, const void *w, const float *bias, void *out, in
     // 16-byte aligned take the smallest tile with the same split.
     const long long bricks =
         (long long)B * ((W + FC_X - 1) / FC_X) * ((H + FC_Y - 1) / FC_Y) * ((D + 3) / 4);
-    const int tiles = Co / 16;
+    const int tiles = Co / 16, cus = compute_units();
     const bool far = 2LL * (4 * 2 + 3) * (H + 1) * (W + 2) * Ci >= (long long)kRange;
-    const bool two = tiles % 2 == 0 && bricks * (tiles / 2) >= 512;
-    const bool split = !two && Ci >= 32 && bricks * tiles <= 256;
+    const bool two = tiles % 2 == 0 && bricks * (tiles / 2) >= 2 * cus;
+    const bool split = !two && Ci >= 32 && bricks * tiles <= cus;
     if (!aligned16(src.in, src.low, wb, reinterpret_cast<bf *>(out), ep.act, ep.gate, ep.out2)) {
         if (split)
-            launch_fwd<1, 1, 2, false>(src, wb, bias, out, out_f32, d, s, ep);
+            launch_fwd<1, 1, 2, false>(src, wb, bias, out, out_f32, d, cus, s, ep);
         else
-            launch_fwd<1, 1, 1, false>(src, wb, bias, out, out_f32, d, s, ep);
+            launch_fwd<1, 1, 1, false>(src, wb, bias, out, out_f32, d, cus, s, ep);
     } else if (two)
-        launch_fwd<2, 1>(src, wb, bias, out, out_f32, d, s, ep);
-    else if (tiles % 3 == 0 && bricks * (tiles / 3) >= 512)
-        launch_fwd<3, 1>(src, wb, bias, out, out_f32, d, s, ep);
+        launch_fwd<2, 1>(src, wb, bias, out, out_f32, d, cus, s, ep);
+    else if (tiles % 3 == 0 && bricks * (tiles / 3) >= 2 * cus)
+        launch_fwd<3, 1>(src, wb, bias, out, out_f32, d, cus, s, ep);
     else if (split)
-        launch_fwd<1, 1, 2>(src, wb, bias, out, out_f32, d, s, ep);
-    else if (!far && bricks * tiles >= 2048)
-        launch_fwd<1, 2>(src, wb, bias, out, out_f32, d, s, ep);
+        launch_fwd<1, 1, 2>(src, wb, bias, out, out_f32, d, cus, s, ep);
+    else if (!far && bricks * tiles >= 8 * cus)
+        launch_fwd<1, 2>(src, wb, bias, out, out_f32, d, cus, s, ep);
     else
-        launch_fwd<1, 1>(src, wb, bias, out, out_f32, d, s, ep);
+        launch_fwd<1, 1>(src, wb, bias, out, out_f32, d, cus, s, ep);
     HIP_TRY(hipGetLastError());
     return LBMX_OK;
 }
@@ -1785,7 +1786,7 @@ lbmx_status lbmx_nn_conv3d_mse(const void *in, const void *w, const float *bias,
     const bf *const wb = reinterpret_cast<const bf *>(w);
     const auto run = aligned16(src.in, wb, pred, ls.grad) ? launch_fwd_as<1, 1, kLoss, 1, true>
                                                           : launch_fwd_as<1, 1, kLoss, 1, false>;
-    run(src, wb, bias, pred, Dims{B, D, H, W, Ci, Co}, S(stream), Epilogue{}, ls);
+    run(src, wb, bias, pred, Dims{B, D, H, W, Ci, Co}, compute_units(), S(stream), Epilogue{}, ls);
     HIP_TRY(hipGetLastError());
     return LBMX_OK;
 }
@@ -1934,10 +1935,7 @@ lbmx_status conv_wgrad(ConvIn src, const void *gout, float *gw, float *gb, int32
     const int nbx = (W + WB_X - 1) / WB_X, nby = (H + WB_Y - 1) / WB_Y, nbz = (D + WB_Z - 1) / WB_Z;
     const long long nchunks = (long long)B * nbx * nby * nbz;
     const int pairs = (Co / 16) * (Ci / 16);
-    int dev = 0, cus = 256;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
-        cus = 256;
+    const int cus = compute_units();
     // Blocks of one round (a block takes a whole CU, and every block adds its sums
     // to the same gradient elements) and of two chunks or more,
     // and where that costs little a multiple of 8 or 2: the blocks of all pairs that
