@@ -328,10 +328,10 @@ struct Plane {
     }
 };
 
-// Where a thread's node lies: the uniform address `base` and the lane's byte
-// offsets from it in a flow and in an energy segment 0.  Either base is the
-// node's plane (z uniform over the block) or the lattice (z per lane, whose
-// offsets then include z planes; the lattice is below 4 GiB).
+// Where a thread's node lies: the lane's byte offsets in a flow and in an energy
+// segment 0 from an address that is uniform over the block, and the walls it is
+// at.  The address is the node's plane (z uniform) or the lattice (z per lane,
+// whose offsets then include z planes; the lattice is below 4 GiB).
 struct Site {
     uint32_t vF, vG;
     bool xl, xh, yl, yh, zl, zh;  // on the walls x = 0, x = H, ...

@@ -10,21 +10,23 @@
 // Convolution = implicit GEMM on the matrix cores: out[p][co] =
 // sum_{tap, ci} W[co][tap][ci] in[p + off(tap)][ci] with M = co, N = voxels,
 // K = (tap, ci), FP32 accumulation.  Both convolution kernels run on
-// v_mfma_f32_16x16x32_bf16 (gfx950) over bricks of voxels staged in LDS (forward:
-// 16 x 4 x 4), so that each staged element serves all 27 taps; blocks walk the
-// bricks in an XCD-aware order (brick_walk):
+// v_mfma_f32_16x16x32_bf16 (gfx950) over bricks of voxels staged in LDS, so that
+// each staged element serves all 27 taps, in an order in which the blocks of one
+// XCD work on neighbours:
 //   - forward (and the data gradient, the same convolution of the output
 //     gradient with the flipped, transposed weights W'[ci][26-tap][co] =
-//     W[co][tap][ci]): a block stages its brick's input with a one-voxel halo
-//     and the weights of all taps per 16 input channels, channel-last; K = 32
+//     W[co][tap][ci]): a block walks bricks of 16 x 4 x 4 or 16 x 4 x 8 voxels
+//     (brick_walk) and stages a brick's input with a one-voxel halo and the
+//     weights of all taps per 16 input channels, channel-last; K = 32
 //     covers two taps of the 16 channels; the epilogue can apply SiLU, its
 //     derivative, a channel split or the squared-error loss; the input can be
 //     a decoder's upsampled-and-concatenated tensor read in place; details
 //     at k_conv_fwd;
 //   - weight gradient: a block owns one (output-channel tile, input-channel
-//     tile) pair, walks bricks of 16 x 8 x 8 voxels and brings output gradient
-//     and input halo into LDS as they lie in memory; transposing LDS reads give
-//     the operands, K = 32 covering two rows of voxels; the bias gradient is one
+//     tile) pair and streams a range of chunks of 16 x 8 x 4 voxels down columns,
+//     bringing output gradient and input halo into LDS as they lie in memory;
+//     transposing LDS reads give the operands, K = 32 covering two rows of voxels;
+//     the bias gradient is one
 //     more MFMA against ones; the block's sums are added to the global gradient
 //     atomically; details at k_conv_wgrad.
 // MFMA operand layout of v_mfma_f32_16x16x32_bf16 (checked on the device):
@@ -311,8 +313,8 @@ __device__ __forceinline__ v2u load_vec(const void *base, int range, uint32_t of
 // the loss.
 enum FcOut { kF32, kBf16, kAct, kSilu, kGate, kLoss };
 
-// Occupancy is register-bound: 4 waves per SIMD for one channel tile, 2 for
-// two and for the loss variant.
+// Occupancy is register-bound: 4 waves per SIMD for one channel tile (3 for its
+// bricks of 8 planes), 2 for more and for the loss variant.
 //
 // KS > 1 (layers with several rounds on small grids): the block has KS
 // groups of FC_THREADS threads, each with its own LDS tiles; group g takes
@@ -1612,8 +1614,9 @@ lbmx_status conv_fwd(ConvIn src, const void *w, const float *bias, void *out, in
     // three.  Bricks of 8 planes with one tile from eight blocks per CU on and as
     // far as 32-bit offsets over their halo go: 16 -> 16 at 64^3 29.1 -> 26.8 us,
     // 48 -> 16 59 -> 52, but at batch 1 17.6 -> 19.9, and with a gate, whose loads no
-    // register is free for during the products, 29.7 -> 31.3 (with two tiles the
-    // registers spill: no gain).  Two groups per block that split the rounds when
+    // register is free for during the products, 29.7 -> 31.3 (they fill the 168
+    // registers of three waves per SIMD and spill 7 or 8 of them; with two tiles the
+    // spills cost what the bricks gain).  Two groups per block that split the rounds when
     // one tile per block leaves at most one block per CU.  Operands that are not
     // 16-byte aligned take the smallest tile with the same split.
     const long long bricks =

@@ -40,8 +40,8 @@ def wgrad(x, g):
     return gw, gb
 
 
-# one brick (16 x 8 x 8) exactly, one voxel less and more per axis, two bricks
-# with a one-voxel second one, quarters (4 x 4 of y, z) partly and wholly empty
+# volumes of two chunks (16 x 8 x 4) in a column exactly, one voxel less and more per
+# axis, columns of one voxel and row, teams (two rows) partly and wholly outside
 @pytest.mark.parametrize("shape", [(1, 8, 8, 16), (1, 7, 9, 15), (2, 9, 7, 17), (1, 1, 1, 1), (1, 4, 5, 33),
                                    (3, 12, 16, 32), (1, 17, 3, 16)])
 @pytest.mark.parametrize("ci,co", [(16, 16), (32, 48)])

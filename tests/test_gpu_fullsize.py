@@ -108,3 +108,20 @@ def test_sampled_step_at_256cube(storage):
     for k in ("nu3d", "nu2d", "numax"):
         assert abs(nu_gpu[k] - nu_ora[k]) <= 1e-12 * abs(nu_ora[k]), (k, nu_gpu[k], nu_ora[k])
     assert np.abs(nu_gpu["map"] - nu_ora["map"]).max() <= 1e-11 * np.abs(nu_ora["map"]).max()
+
+
+@pytest.mark.parametrize("storage", ["f32", "f64"])
+def test_two_steps_per_pass_at_256cube(storage):
+    """The kernel that the default launch runs here takes two steps per pass: its
+    populations equal, bit for bit, those of the one-step kernel, which the sampled
+    test above holds to the oracle."""
+    print(f"case: full size 256^3 T1 Ra1e6 {storage}, two steps per pass", flush=True)
+    th = inputs.theta_noise(N, 20151115, 0.3)
+    out = []
+    for shape in ((0, 0), (256, 1)):
+        cav = L.Cavity(n=N, wall_type=1, ra=1e6, storage=storage, theta0=th).set_launch(*shape)
+        assert cav.steps_per_pass() == (2 if shape == (0, 0) else 1)
+        cav.step(6)
+        out.append(cav.get_populations())
+        cav.close()
+    assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])

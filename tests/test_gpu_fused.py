@@ -82,3 +82,17 @@ def test_store_policies_give_the_same_steps(n, storage):
     b.step(5)
     for p, q in zip(cav.read_macro(), b.read_macro(0)):
         assert np.array_equal(p, q)
+
+
+def test_the_compared_launches_differ():
+    """The default launch takes two steps per pass at the sizes compared above and
+    explicit shapes one; sizes between the tiles and the columns take one."""
+    two = [("f32", n) for n in SMALL if n <= 40] + [("f64", n) for n in SMALL if n <= 32] + LARGE
+    for storage, n in two + [("f32", 41), ("f64", 33), ("f32", 64), ("f64", 64), ("f16", 112)]:
+        print(f"case: steps per pass {storage} n={n}", flush=True)
+        c = L.Cavity(n=n, wall_type=1, ra=1e4, storage=storage)
+        assert c.steps_per_pass() == (2 if (storage, n) in two else 1), (storage, n)
+        assert c.set_launch(min(n, 256), 1).steps_per_pass() == 1
+        c.close()
+    guo = L.Cavity(n=112, wall_type=1, ra=1e4, storage="f32", force_model=2)
+    assert guo.steps_per_pass() == 1

@@ -78,3 +78,13 @@ def test_large_reads_on_a_per_thread_stream():
         cav.close()
     for a, b in zip(*got):
         assert np.array_equal(a, b)
+
+
+def test_fields_at_the_largest_single_copy():
+    """One field of 127^3 is copied in one piece, the five together by threads."""
+    n = 127
+    assert 8 * n ** 3 < 16 << 20 < 5 * 8 * n ** 3
+    print(f"case: readback n={n}", flush=True)
+    cav = started(n, "f32", n)
+    for k, a in enumerate(cav.read_macro()):
+        assert np.array_equal(a, alone(cav, k)), k
