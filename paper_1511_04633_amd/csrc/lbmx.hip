@@ -174,8 +174,9 @@ void launch_step_kernels(lbmx_cavity *h, int64_t nsteps)
     const int n = h->p.n;
     if constexpr (kForce != LBMX_FORCE_GUO && (std::is_same<St, Store<float, float>>::value ||
                                                std::is_same<St, Store<double, double>>::value)) {
+        const bool keep = nsteps > 0 && keeps_lattice(h);  // asked also where no pair is taken
         if (h->bx == 0 && nsteps >= 2)
-            nsteps -= launch_step_pairs<St, kForce>(h, keeps_lattice(h) ? nsteps / 4 * 4 : nsteps, geo, rates);
+            nsteps -= launch_step_pairs<St, kForce>(h, keep ? nsteps / 4 * 4 : nsteps, geo, rates);
     }
     const float inv_n = 1.0f / float(n);
     const bool flat = h->bx == 0;  // the default launch

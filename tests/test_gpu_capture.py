@@ -69,3 +69,34 @@ def test_odd_captures_alternate_between_the_lattices():
             assert np.array_equal(a, b)
     cav.close()
     ref.close()
+
+
+@pytest.mark.parametrize("shape", [(0, 0), (16, 8)])
+def test_single_steps_captured_in_pairs(shape):
+    """Two steps captured one by one, under the default launch or an explicit shape,
+    with eager pairs of the default launch between the replays."""
+    import torch
+    n = 16
+    print(f"case: two captured steps, shape {shape}", flush=True)
+    s = torch.cuda.Stream()
+    th = inputs.theta_noise(n, 7, 0.3)
+    with torch.cuda.stream(s):
+        cav, ref = (L.Cavity(n=n, wall_type=1, ra=1e5, storage="f32", stream=s) for _ in range(2))
+    cav.step(1)
+    cav.init_rest(th)
+    ref.init_rest(th)
+    cav.set_launch(*shape)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=s):
+        cav.step(1)
+        cav.step(1)
+    cav.set_launch(0, 0)
+    for _ in range(3):
+        with torch.cuda.stream(s):
+            graph.replay()
+        cav.step(2)
+        ref.step(4)
+        for a, b in zip(cav.read_macro(), ref.read_macro()):
+            assert np.array_equal(a, b)
+    cav.close()
+    ref.close()
