@@ -1,11 +1,11 @@
 """Lattices above 4 GiB, which the step, pull, read, Nu and initialisation
-kernels address by 64-bit plane bases and 32-bit offsets in them.
-FP64 at 328^3 (7.3 GB per lattice) and FP32 at 416^3 (7.5 GB per lattice), started from smooth random fields so that every
-population carries a distinct value, are checked one step at a time on
-sampled nodes against the oracle (as the 256^3 test does), including nodes
-whose populations lie beyond the first 4 GiB; the Nu family of the state
-against the oracle's; and the macroscopic read-back against the
-populations it is defined from (Eqs. 20, 25, 30)."""
+kernels address by 64-bit plane bases and 32-bit offsets in them.  FP64 at
+328^3 (7.3 GB per lattice) and FP32 at 416^3 (7.5 GB per lattice), started
+from smooth random fields so that every population carries a distinct value,
+are checked one step at a time on sampled nodes against the oracle (as the
+256^3 test does), including nodes whose populations lie beyond the first
+4 GiB; the Nu family of the state against the oracle's; and the macroscopic
+read-back against the populations it is defined from (Eqs. 20, 25, 30)."""
 import gc
 
 import numpy as np
