@@ -132,7 +132,8 @@ k_step2_tile(const char *__restrict__ src, char *__restrict__ dst, Geometry<type
 // 773 us; 128^3 FP32 74 -> 63 us.  64 x 13 tiles rather than 32 x 28 or
 // 32 x 13: the rows' end columns cost a memory line each (FP32 256^3 with an
 // earlier alignment: 405, 477 and 430 us); loading the next plane before step A
-// instead spills registers.
+// instead spills vector registers.  As it is, the uniform values of the loop's two
+// copies (with and without walls) spill: 52 scalar registers in FP32, 107 in FP64.
 __device__ __forceinline__ constexpr int slot19(int i)
 {
     constexpr int v[19] = {5, 6, 7, 8, 9, 14, 0, 10, 11, 12, 13, 15, 16, 1, 2, 17, 18, 3, 4};
