@@ -316,10 +316,11 @@ inline dim3 plane_grid(int n) { return dim3((unsigned(n) * unsigned(n) + 255) / 
 constexpr size_t kNearBytes = size_t(132) << 20;
 
 // The policies of k_step's accesses to lattices of `bytes`.
-// Stores beyond kNearBytes: kFar where they cover whole lines, which the default
-// launch's do (flat), and explicit blocks' if rows are whole lines; else kStream, as
-// with sc1 the parts of a line are written to memory one by one (f16 / i16 200^3 in
-// rows 361 us, 224 with kStream; 150^3 105, 89).
+// Stores beyond kNearBytes: kFar under the default launch (flat), whose stores cover
+// whole lines; explicit blocks take kStream, as with sc1 the parts of a line are
+// written to memory one by one (f16 / i16 200^3 in rows 361 us, 224 with kStream; 150^3
+// 105, 89; 256^3, whole lines, 283, 284), but FP64 whose rows are whole lines (256^3
+// 1209, 1229).
 // Below, kNear but up to 14 MB, from 5.9 MB or FP64 7, where kStream measured faster
 // for reasons that are not known: FP32 41^3 5.7 -> 5.4 us, 48^3 6.6 -> 6.2, 50^3 7.2 ->
 // 6.8, FP64 36^3 6.3 -> 5.9, 40^3 8.1 -> 7.6; not where a plane is a multiple of 8
@@ -342,7 +343,7 @@ inline StepPolicy step_policy(size_t bytes, int32_t storage, int n, bool flat)
     const size_t row = size_t(n) * std::min(flow_size(storage), energy_size(storage));
     const bool lines = row % 128 == 0;
     if (bytes > kNearBytes)
-        return {flat || lines ? kFar : kStream, f64 && lines};
+        return {flat || (f64 && lines) ? kFar : kStream, f64 && lines};
     const bool middle = bytes >= (f64 ? 7.0 : 5.9) * MB && bytes < 14.0 * MB;
     const bool stream = flat ? (f64 || storage == LBMX_F32) && (n * n + kFlatBlock - 1) / kFlatBlock % 8 != 0
                              : storage != LBMX_F16_I16;

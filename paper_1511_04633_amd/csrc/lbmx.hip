@@ -154,15 +154,22 @@ int64_t launch_step_pairs(lbmx_cavity *h, int64_t nsteps, Geometry<typename St::
 template <class St, int kForce, bool kFlat, int kThreads>
 auto step_kernel(const lbmx_cavity *h)
 {
+    using SF = typename St::F;
     const StepPolicy p = step_policy(h->L.lattice, h->p.storage, h->p.n, kFlat);
     if (p.stores == kNear)
         return k_step<St, kForce, kFlat, kThreads, kNear, false>;
-    if constexpr (sizeof(typename St::F) == 8)
+    if constexpr (std::is_same<SF, double>::value) {
         if (p.nt_loads)
             return p.stores == kFar ? k_step<St, kForce, kFlat, kThreads, kFar, true>
                                     : k_step<St, kForce, kFlat, kThreads, kStream, true>;
-    return p.stores == kFar ? k_step<St, kForce, kFlat, kThreads, kFar, false>
-                            : k_step<St, kForce, kFlat, kThreads, kStream, false>;
+        if constexpr (kFlat)
+            if (p.stores == kFar)
+                return k_step<St, kForce, kFlat, kThreads, kFar, false>;
+    }
+    // the policy that is left: of the other storages only the default launch of 2-byte
+    // flow populations takes kFar, and then never kStream (of 4-byte ones they are one)
+    constexpr int kLeft = kFlat && sizeof(SF) == 2 ? kFar : kStream;
+    return k_step<St, kForce, kFlat, kThreads, kLeft, false>;
 }
 
 template <class St, int kForce>
