@@ -18,6 +18,7 @@ about 1.16 M parameters.
 from __future__ import annotations
 
 import ctypes
+import functools
 import math
 
 import numpy as np
@@ -135,6 +136,23 @@ class Conv:
         call("lbmx_nn_adam", P(self.b), P(self.gb), P(self.mb), P(self.vb), None,
              self.b.numel(), lr, b1, b2, eps, step, 0.0, s)
         call("lbmx_nn_conv3d_flip", P(self.wb), P(self.wflip), self.ci, self.co, s)
+
+
+@functools.lru_cache(maxsize=16)
+def native_shapes(levels):
+    """(ci, co) of the layers that lbmx_nn_unet_forward runs for these channels per
+    level, in forward order; None if it takes no such network.  (A program may have
+    replaced a network's layers.)"""
+    if len(levels) > 8:
+        return None
+    shapes, ci = [], NFEAT
+    for c in levels:
+        shapes += [(ci, c), (c, c)]
+        ci = c
+    for c in reversed(levels[:-1]):
+        shapes += [(ci + c, c), (c, c)]
+        ci = c
+    return shapes + [(ci, 16)]
 
 
 class UNet:
@@ -256,9 +274,10 @@ class UNet:
         s = stream_ptr()
         m = self.m
         if self.fused and not train and self.record is None:
-            levels = self._levels()
-            if levels is not None:
-                return self._infer(cond, B, s, levels)
+            convs = self.convs()
+            levels = tuple([b.co for _, b in self.enc])
+            if [(c.ci, c.co) for c in convs] == native_shapes(levels):
+                return self._infer(cond, B, s, levels, convs)
         cache, h = self._trunk(cond, B)
         pred = torch.empty((B, m ** 3, 16), dtype=torch.float32, device="cuda")
         call("lbmx_nn_conv3d_fwd", P(h), P(self.head.wb), P(self.head.b), P(pred), 1, B, m, m, m,
@@ -266,26 +285,10 @@ class UNet:
         self._cache = (cache, h, B) if train else None
         return pred
 
-    def _levels(self):
-        """Channels per level if the layers, which a program may have replaced, are
-        those that lbmx_nn_unet_forward runs; else None."""
-        levels = [b.co for _, b in self.enc]
-        shapes, ci = [], NFEAT
-        for c in levels:
-            shapes += [(ci, c), (c, c)]
-            ci = c
-        for c in reversed(levels[:-1]):
-            shapes += [(ci + c, c), (c, c)]
-            ci = c
-        shapes.append((ci, 16))
-        same = [(c.ci, c.co) for c in self.convs()] == shapes
-        return levels if same and len(levels) <= 8 else None
-
-    def _infer(self, cond, B, s, levels):
+    def _infer(self, cond, B, s, levels, convs):
         """forward() without a cache: every launch from one native call."""
         import torch
 
-        convs = self.convs()
         levels = (ctypes.c_int32 * len(levels))(*levels)
         ptrs = _vp * len(convs)
         size = ctypes.c_size_t()
