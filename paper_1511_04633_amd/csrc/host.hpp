@@ -14,6 +14,7 @@
 #include <cstddef>
 #include <cstdint>
 #include <cstring>
+#include <mutex>
 #include <new>
 #include <thread>
 #include <vector>
@@ -398,8 +399,10 @@ lbmx_status launch_pops(const View &v, int first, int count, double *out)
 }
 
 // Pinned memory of one handle through which large results travel to the host,
-// allocated by the first such read and released with the handle.
+// allocated by the first such read and released with the handle.  A batch's cavities
+// may be read by several threads at once: one uses it at a time.
 struct Staging {
+    std::mutex busy;
     char *p = nullptr;
     size_t bytes = 0;
     Staging() = default;
@@ -469,6 +472,9 @@ try {
     if (total >= kLeast && stream != hipStreamPerThread && sched_getaffinity(0, sizeof set, &set) == 0)
         threads = std::min(kThreads, CPU_COUNT(&set));
     const size_t chunk = std::min(kChunk, std::max<size_t>(256u << 10, total / (4 * size_t(threads)) >> 12 << 12));
+    std::unique_lock<std::mutex> mine(staging.busy, std::defer_lock);
+    if (threads >= 2)
+        mine.lock();
     const bool direct = threads < 2 || !staging.reserve(2 * threads * chunk);
     for (int i = 0; i < count; ++i)
         if (direct || known[i])
@@ -532,9 +538,9 @@ try {
         (void)hipStreamSynchronize(stream);  // nothing is on its way to the staging memory
     HIP_TRY(hipError_t(first_error.load()));
     return LBMX_OK;
-} catch (const std::bad_alloc &) {
+} catch (const std::exception &e) {
     (void)hipStreamSynchronize(stream);
-    return fail(LBMX_ENOMEM, "host allocation failed");
+    return fail(LBMX_ENOMEM, "copying results to the host: %s", e.what());
 }
 
 // Doubles per node the spare lattice can stage (at least 6).

@@ -175,6 +175,27 @@ static int copies(hipStream_t s, const std::vector<size_t> &sizes, size_t pins =
     return host == dev && host[0][0] == 0.0 ? 0 : 1;
 }
 
+// Several threads read through one handle's staging memory at once.
+static int together(hipStream_t s, int count)
+{
+    Staging staging;
+    const std::vector<size_t> sizes = {700001, 2500003};
+    std::atomic<int> bad{0};
+    std::vector<std::thread> pool;
+    for (int t = 0; t < count; ++t)
+        pool.emplace_back([&, t] {
+            for (int round = 0; round < 4; ++round) {
+                std::vector<double> dev(sizes[(t + round) % 2], 1000.0 * t + round), host(dev.size(), -1.0);
+                const HostCopy c{host.data(), dev.data(), dev.size() * sizeof(double)};
+                if (copies_to_host(s, staging, &c, 1) != LBMX_OK || hipStreamSynchronize(s) != hipSuccess || host != dev)
+                    ++bad;
+            }
+        });
+    for (std::thread &t : pool)
+        t.join();
+    return bad.load() ? 1 : 0;
+}
+
 int main(int argc, char **argv)
 {
     const std::string c = argc > 1 ? argv[1] : "";
@@ -186,6 +207,8 @@ int main(int argc, char **argv)
         return copies(own, large);
     if (c == "per_thread_stream")
         return copies(hipStreamPerThread, large) + copies(hipStreamPerThread, small);
+    if (c == "several_threads")
+        return together(own, 4);
     if (c == "pinned")  // nothing is staged
         return copies(own, large, large.size()) + (staged == 0 ? 0 : 4);
     if (c == "partly_pinned")

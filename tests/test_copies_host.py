@@ -23,7 +23,8 @@ def exe(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("case", ["small", "large", "per_thread_stream", "other_device", "pinned", "partly_pinned"])
+@pytest.mark.parametrize("case", ["small", "large", "per_thread_stream", "other_device", "pinned", "partly_pinned",
+                                  "several_threads"])
 def test_copies_arrive_whole_and_in_order(exe, case):
     for _ in range(5):
         r = subprocess.run([exe, case], capture_output=True, text=True, timeout=60)
