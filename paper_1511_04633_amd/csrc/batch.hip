@@ -11,6 +11,8 @@
 #include <cstring>
 #include <fstream>
 #include <map>
+#include <memory>
+#include <mutex>
 #include <new>
 #include <sstream>
 #include <string>
@@ -60,6 +62,7 @@ struct lbmx_batch {
     uint32_t gtiles = 0;
     int cus = 256;
     Staging staging;
+    std::unique_ptr<std::mutex[]> reading;  // of cavity k: its spare lattice holds a read's results
 };
 
 namespace {
@@ -401,6 +404,7 @@ lbmx_status lbmx_batch_create(const lbmx_params *p, int32_t count, void *stream,
     }
     b->cur.assign(count, 0);
     b->state.assign(count, ST_ACTIVE);
+    b->reading = std::make_unique<std::mutex[]>(count);
     b->t.assign(count, 0);
     b->last.assign(count, lbmx_nu{});
     b->ws_bytes = total;
@@ -636,6 +640,7 @@ lbmx_status lbmx_batch_read_macro(lbmx_batch *b, int32_t k, double *rho, double 
     lbmx_status s = check(b, k);
     if (s != LBMX_OK)
         return s;
+    std::lock_guard<std::mutex> mine(b->reading[k]);
     return LBMX_DISPATCH(b->storage, macro_to_host, view_of(b, k), b->staging, rho, ux, uy, uz, theta);
 }
 
@@ -650,6 +655,7 @@ lbmx_status lbmx_batch_resample(lbmx_batch *b, int32_t k, int32_t out_n, float *
     const size_t cells = size_t(n) * n * n, mc = size_t(out_n) * out_n * out_n;
     // the fields are staged in the spare lattice, and the result behind them if it fits
     const View v = view_of(b, k);
+    std::lock_guard<std::mutex> mine(b->reading[k]);
     const size_t fields = 4 * cells * sizeof(double), result = 4 * mc * sizeof(float);
     DevBuf outb;
     if (v.spare_bytes < fields + result)

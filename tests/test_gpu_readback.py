@@ -88,3 +88,31 @@ def test_fields_at_the_largest_single_copy():
     cav = started(n, "f32", n)
     for k, a in enumerate(cav.read_macro()):
         assert np.array_equal(a, alone(cav, k)), k
+
+
+def test_a_batch_is_read_by_several_threads():
+    """Fields and resampled fields of different cavities and of the same one."""
+    from paper_1511_04633_amd import inputs, lbmx
+    print("case: batch readback from eight threads", flush=True)
+    sizes = (76, 80, 64)
+    b = lbmx.Batch([dict(n=n, wall_type=1, ra=1e5) for n in sizes])
+    for k, n in enumerate(sizes):
+        b.init_rest(k, inputs.theta_noise(n, k, 0.3))
+    b.step(5)
+    jobs = [(b.read_macro, (k,)) for k in range(3)] + [(b.resample, (k, m)) for k in range(3) for m in (20, 112)]
+    want = [f(*a) for f, a in jobs]
+    got = [[None] * len(jobs) for _ in range(8)]
+
+    def run(t):
+        for i in range(len(jobs)):
+            j = (i + t) % len(jobs)
+            got[t][j] = jobs[j][0](*jobs[j][1])
+
+    ts = [threading.Thread(target=run, args=(t,)) for t in range(8)]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join()
+    for row in got:
+        for a, w in zip(row, want):
+            assert all(np.array_equal(p, q) for p, q in zip(a, w))
