@@ -101,8 +101,9 @@ lbmx_status upload_cavs(lbmx_batch *b)
         c.geo = geometry<St>(make_view(c.lat[0], c.lat[1], b->L[k].lattice, b->p[k], b->d[k],
                                        b->stream));
         c.rates = make_rates<T>(&b->p[k], b->d[k]);
-        c.cells = uint32_t(b->p[k].n) * b->p[k].n * b->p[k].n;
+        c.plane = plane_slots(uint32_t(b->p[k].n));
         c.inv_n = 1.0f / float(b->p[k].n);
+        c.inv_plane = 1.0f / float(c.plane);
     }
     if (b->d_cavs)
         (void)hipFree(b->d_cavs);
@@ -112,15 +113,15 @@ lbmx_status upload_cavs(lbmx_batch *b)
     return LBMX_OK;
 }
 
-// Work list of the active cavities, tiles of b->block nodes.
+// Work list of the active cavities, tiles of b->block slots.
 lbmx_status build_tiles(lbmx_batch *b)
 {
     std::vector<Tile> tiles;
     for (int k = 0; k < b->count; ++k) {
         if (b->state[k] != ST_ACTIVE)
             continue;
-        const uint32_t cells = uint32_t(b->p[k].n) * b->p[k].n * b->p[k].n;
-        for (uint32_t s = 0; s < cells; s += uint32_t(b->block))
+        const uint32_t slots = uint32_t(b->p[k].n) * plane_slots(uint32_t(b->p[k].n));
+        for (uint32_t s = 0; s < slots; s += uint32_t(b->block))
             tiles.push_back(Tile{uint32_t(k), s});
     }
     drop_graph(b);

@@ -2,15 +2,16 @@
 // parameters by one time step (same node update as k_step: pull streaming
 // with the wall rules of Eqs. 6-10, double-MRT collision of Sec. 3).
 //
-// Work list: every active cavity's n^3 nodes are cut, in storage order, into
-// tiles of blockDim.x consecutive nodes; tile t is {cavity, first node}.  A
-// block takes tiles blockIdx.x, blockIdx.x + gridDim.x, ... (grid-stride
-// "persistent" blocks when gridDim.x is smaller than the tile count, one
-// tile per block when equal).  Consecutive nodes of a tile are consecutive
-// in every population segment (up to a plane boundary), so loads and stores
-// stay coalesced across row boundaries, and every wavefront is full except
-// at the end of a cavity.  The per-cavity table (lattice pointers, geometry,
-// relaxation rates) is read with wavefront-uniform loads.
+// Work list: every active cavity's nodes, in storage order and each plane filled up
+// to whole wavefronts (slots), are cut into tiles of blockDim.x slots; tile t is
+// {cavity, first slot}.  A block takes tiles blockIdx.x, blockIdx.x + gridDim.x, ...
+// (grid-stride "persistent" blocks when gridDim.x is smaller than the tile count, one
+// tile per block when equal).  A wavefront's nodes are consecutive in every
+// population segment and start on a memory line, so its stores cover whole lines,
+// and it is full except at the end of a plane.  (Tiles over the nodes alone put
+// wavefronts across lines where n^2 is no multiple of 64: us per step, FP16, 6 of
+// 50^3 20.5, 3 of 100^3 72.2; here 16.6 and 54.8.)  The per-cavity table (lattice pointers,
+// geometry, relaxation rates) is read with wavefront-uniform loads.
 #pragma once
 
 #include "kernels.hpp"
@@ -22,13 +23,16 @@ struct BatchCav {
     char *lat[2];        // the cavity's two lattices
     Geometry<T> geo;
     Rates<T> rates;
-    uint32_t cells;      // n^3 (< 2^24)
-    float inv_n;         // 1/n, for the quotient below
+    uint32_t plane;      // slots of a plane: n^2 up to a multiple of 64 (n of them < 2^24)
+    float inv_n, inv_plane;  // their reciprocals, for the quotients below
 };
+
+// Slots of a plane of n^2 nodes.
+__host__ __device__ constexpr uint32_t plane_slots(uint32_t n) { return (n * n + 63) / 64 * 64; }
 
 struct Tile {
     uint32_t cav;        // index into the cavity table
-    uint32_t start;      // first node (flat index x + n (y + n z))
+    uint32_t start;      // first slot
 };
 
 // Each cavity's time step lives on the device, in two arrays used by turns:
@@ -51,13 +55,12 @@ __global__ __launch_bounds__(1024) void k_step_batch(const BatchCav<typename St:
         const uint32_t step = t_in[tile.cav];
         if (tile.start == 0 && threadIdx.x == 0)
             t_out[tile.cav] = step + 1u;
-        const uint32_t c = tile.start + threadIdx.x;
-        if (c >= cv->cells)
+        const uint32_t n = uint32_t(cv->geo.n), slot = tile.start + threadIdx.x;
+        const uint32_t z = div_small(slot, cv->plane, cv->inv_plane), cp = slot - z * cv->plane;
+        if (cp >= n * n || z >= n)
             continue;
-        const uint32_t n = uint32_t(cv->geo.n);
-        const uint32_t q = div_small(c, n, cv->inv_n);
-        const uint32_t z = div_small(q, n, cv->inv_n);
-        const int x = int(c - q * n), y = int(q - z * n);
+        const uint32_t q = div_small(cp, n, cv->inv_n);
+        const int x = int(cp - q * n), y = int(q);
         const Geometry<T> geo = cv->geo;
         Site s = site_in_plane<St>(int(n), x, y, int(z));
         const uint32_t plane = z * Plane<St>(n).bytes;
@@ -66,7 +69,7 @@ __global__ __launch_bounds__(1024) void k_step_batch(const BatchCav<typename St:
         T f[19], g[7];
         pull<St, true>(cv->lat[parity], geo, s, y, f, g);
         collide<T, kForce>(f, g, cv->rates);
-        put<St, kPolicy>(cv->lat[parity ^ 1], s, c, step, geo, f, g);
+        put<St, kPolicy>(cv->lat[parity ^ 1], s, cp + n * n * z, step, geo, f, g);
     }
 }
 

@@ -182,3 +182,26 @@ def test_batch_rejects_bad_input():
         b.set_launch(256, 0, 3)
     with pytest.raises(L.LbmxError):
         b.info(5)
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32", "f16", "f16_i16"])
+@pytest.mark.parametrize("block,grid", [(64, 0), (256, 0), (1024, 0), (256, 5)])
+def test_planes_that_end_inside_a_wavefront(storage, block, grid):
+    """Sizes whose planes are no multiple of 64 nodes (and one that is), in blocks that
+    end inside planes: bitwise the cavities stepped alone, also in the rounding, which
+    goes by the node's number."""
+    sizes = (4, 5, 8, 17, 33, 50)
+    print(f"case: ragged planes {storage} block {block} grid {grid}", flush=True)
+    kw = [dict(n=n, wall_type=1 + k % 3, ra=1e4) for k, n in enumerate(sizes)]
+    b = L.Batch(kw, storage=storage)
+    b.set_launch(block, grid, 0)
+    for k, n in enumerate(sizes):
+        b.init_rest(k, inputs.theta_noise(n, k, 0.3))
+    b.step(5)
+    for k, n in enumerate(sizes):
+        c = L.Cavity(storage=storage, theta0=inputs.theta_noise(n, k, 0.3), **kw[k])
+        c.step(5)
+        for p, q in zip(b.read_macro(k), c.read_macro()):
+            assert np.array_equal(p, q), n
+        c.close()
+    b.close()
