@@ -22,7 +22,8 @@
  *     f[i*n^3 + index], i in the paper's order (Eqs. 12, 28), 0-based.
  *   - Device work is enqueued on the cavity's HIP stream; calls that return
  *     host data synchronise that stream before returning.
- *   - A cavity handle may be used by one host thread at a time.
+ *   - A cavity handle may be used by one host thread at a time; the cavities of a
+ *     batch may be read (lbmx_batch_read_macro, lbmx_batch_resample) by several.
  *   - Time: a fresh or re-initialised cavity is at t = 0; lbmx_step advances
  *     t.  Every read returns the state at the current t (pre-collision
  *     populations, i.e. after streaming and wall conditions).
@@ -33,7 +34,8 @@
  *     cavity after lbmx_create allocates device memory (lbmx_save and
  *     lbmx_load use a pinned host buffer of up to 64 MB; reads of 16 MB and
  *     more go through up to 32 MB of pinned host memory, kept until the
- *     handle is destroyed, and up to 8 threads for the call's duration).
+ *     handle is destroyed, and up to 8 threads for the call's duration, unless
+ *     the caller has pinned the destination or the stream is hipStreamPerThread).
  *   - Failed cavities: a cavity fails when a Nu evaluation finds non-finite
  *     values (LBMX_EUNSTABLE: the run diverged) or when a device call fails
  *     while its state is being changed.  Until an initialisation succeeds
